@@ -214,7 +214,8 @@ int compute_energy_forces_virial(const dpa4c_model* model, const double* pos,
  * equal to float32 rounding).  One compute_energy_forces call with the same
  * species beforehand gives this entry point the folded tables.  The model's
  * own workspace, and so the list that verlet_step carries between calls, is
- * untouched.  Synchronises ``stream`` once (the species present).
+ * untouched (but for the rows its readout and MLP pass between each other,
+ * which no call leaves anything in).  Synchronises ``stream`` once (the species present).
  */
 int compute_energy_forces_noalloc(const dpa4c_model* model, const double* pos,
                                   const int32_t* species, int64_t N, const double cell[9],

@@ -189,7 +189,7 @@ int ensure_workspace(dpa4c_model* m, int64_t n, int64_t cap) {
   DPA4C_TRY(w.fidx.ensure(4 * nn));
   DPA4C_TRY(w.fold_mask.ensure(4 * sizeof(uint32_t)));
   DPA4C_TRY(w.check.ensure(2 * sizeof(int64_t)));
-  return 0;
+  return ensure_mlp_rows(m, nn);
 }
 
 // the model workspace as the buffers of an evaluation
@@ -336,7 +336,8 @@ int dpa4c_model_create(const void* blob, size_t nbytes, int device, dpa4c_model*
     *out = nullptr;
     return DPA4C_ERR_HIP;
   }
-  rc = noalloc_setup(device);
+  rc = ensure_mlp_rows(*out, kMlpRowsFirst);
+  if (rc == 0) rc = noalloc_setup(device);
   if (rc) {
     dpa4c_model_destroy(*out);
     *out = nullptr;
@@ -349,10 +350,11 @@ void dpa4c_model_destroy(dpa4c_model* m) {
   DeviceGuard guard(m->device);
   hipDeviceSynchronize();
   m->params.release();
+  m->wsplit_buf.release();
   Workspace& w = m->ws;
   DevBuf* bufs[] = {&w.skin_row, &w.skin_j, &w.skin_shift, &w.skin_rev, &w.qbuild, &w.ecount,
                     &w.edge,     &w.cskin,  &w.node,
-                    &w.desc,     &w.node_grad, &w.epart,  &w.flags,      &w.inv_mass, &w.mass,
+                    &w.mlp_buf,  &w.desc,     &w.node_grad, &w.epart,  &w.flags,      &w.inv_mass, &w.mass,
                     &w.eatom,    &w.tailpart,  &w.backup,  &w.ftab,      &w.fold_map, &w.fold_mask,  &w.fidx,
                     &w.check,
                     &w.nb.qpos,  &w.nb.wrap, &w.nb.cell_of, &w.nb.cell_cnt, &w.nb.cell_start,

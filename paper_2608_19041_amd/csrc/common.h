@@ -83,6 +83,19 @@ struct Profile {
   static_assert(kWave % LPE == 0, "edge groups");
 };
 
+// Padded descriptor width of the MLP's operands: whole blocks of 32 inputs.
+constexpr int mlp_width(int dout) { return (dout + 31) / 32 * 32; }
+
+// Powers of two and bounds that keep the MLP's split float16 operands in
+// range (mlp_chain.hip); set up with the model from its weights.
+struct MlpScales {
+  float w_undo[3];       // 2^-e of Theta_t
+  float p_up[3];         // 2^e of the backward operands p1, p2, p3
+  float p_undo[3];       // 2^-(e + e_W) of their products with Theta_t^T
+  // |h1| <= min(d_max |D|_inf, d_norm |D|_2) + d_add, |h2| <= h2_mul |h1| + h2_add
+  float d_max, d_norm, d_add, h2_mul, h2_add;
+};
+
 // The compiled profiles: the five DPA4C variants of Supplementary Table S3,
 // each with its MLP width.
 using NanoProfile = Profile<8, 2, 0>;      // MLP width 96
@@ -152,6 +165,7 @@ struct ModelDev {
   const float* inv_sigma;   // [D_out]
   const float* cpl;         // [kCouplings]: C123 then C233 (symmetric in m2, m3), or null
   const float* E_ref;       // [T+1]
+  const float* row_tab;     // per-lane tables of the readout (readout_row.h)
   // pair-folded tables (fold.hip), used when fold_n > 0:
   // [fold_n^2 pairs][n_rows] rows of kFoldWords C0 words in the order of
   // load_fold_row, pair (fa, fb) at fa * fold_n + fb; c_inv = the inverse

@@ -264,6 +264,14 @@ __device__ inline void cubic_monomials(float x, float y, float z, float* m) {
 }
 
 // species index clamped into the type table (the padding type for bad input)
+// The exponent e of an operand of the MLP whose entries are at most b: the
+// largest that keeps b 2^e below 2^15 (half of the float16 range), no more
+// than 2^100 so that 2^e and what it is undone by stay finite.
+__device__ inline int operand_exponent(float b) {
+  const int e = 15 - __builtin_amdgcn_frexp_expf(fminf(b, 3.0e38f));
+  return e < 100 ? e : 100;
+}
+
 __device__ inline int clamp_type(int a, int n_types1) {
   return static_cast<unsigned>(a) < static_cast<unsigned>(n_types1) ? a : n_types1 - 1;
 }

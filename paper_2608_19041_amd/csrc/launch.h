@@ -56,10 +56,37 @@ int prepare_species(dpa4c_model* m, const int32_t* species, int64_t n, uint32_t*
 // compaction of every skin row (compact.h) and the forward pass
 int launch_forward(const dpa4c_model* m, int64_t n, const int32_t* species, const int32_t* fidx,
                    const int64_t* row_ptr, const CompactArgs& ca, float* node, hipStream_t st);
-// readout + MLP + head + MLP gradient + readout VJP on 16-atom tiles;
-// desc_out (float [N][D_out]) receives D when not null
+// readout, MLP with head and input gradient, readout VJP, in stretches of
+// the atoms that the model's rows hold (Workspace::mlp_rows); desc_out (float
+// [N][D_out]) receives D when not null
 int launch_atoms(const dpa4c_model* m, int64_t n, const int32_t* species, const float* node,
                  float* node_grad, double* e_atom, float* desc_out, hipStream_t st);
+// the stages of launch_atoms on atoms [0, n) (readout.hip, mlp_chain.hip):
+// rows of mlp_width(D_out) floats and one float2 per atom between them
+int launch_readout(const dpa4c_model* m, int64_t n, const int32_t* species, const float* node,
+                   float* desc, float2* meta, float* desc_out, hipStream_t st);
+int launch_chain(const dpa4c_model* m, int64_t n, const int32_t* species, float* desc,
+                 const float2* meta, double* e_atom, hipStream_t st);
+int launch_readout_vjp(const dpa4c_model* m, int64_t n, const float* node, const float* desc,
+                       float* node_grad, hipStream_t st);
+// the readout's per-lane tables (readout_row.h; none at degree four)
+size_t row_table_floats(const dpa4c_model* m);
+void build_row_table(const dpa4c_model* m, const float* W1, const float* W2, const float* A1,
+                     const float* A2, const float* cpl, float* out);
+// a weight matrix [K][N] in the chain's split fragment order
+// (entry (k, n) at w[k sk + n sn])
+int launch_split_weights(const float* w, int K, int N, int sk, int sn, int blocks, int tiles,
+                         float scale, void* out, hipStream_t st);
+// Rows between the readout and the MLP.  An evaluation of more atoms than
+// kMlpRows goes through them in stretches: 65,536 rows of the full width are
+// 143 MB, which the 256 MB last-level cache holds between the three kernels
+// (1 M copper atoms: 16,384 rows at a time 14.5 ms, 65,536 13.5, 131,072
+// 13.3), and four full rounds of 64-atom workgroups.  kMlpRowsFirst come with the model.
+constexpr int64_t kMlpRows = 65536, kMlpRowsFirst = 4096;
+// grows the rows to what ``n`` atoms can use; where that would leave less
+// than 8 GiB of device memory free the rows stay as they are (more, shorter
+// stretches, the same results), so that the largest systems keep the memory
+int ensure_mlp_rows(dpa4c_model* m, int64_t n);
 // the gradient dE/dr_ij of compact slot c of row i goes to the skin position
 // of that edge, edge[row_ptr[i] + cskin[row_ptr[i] + c]] (x, y, z = the
 // gradient, w = the bits of j as before), over the compact records, which

@@ -300,6 +300,124 @@ int check_blob_header(const void* blob, size_t nbytes) {
   return read_header(blob, nbytes, &m, widths);
 }
 
+namespace {
+
+// The MLP's weights as the operands of its products (mlp_chain.hip), and the
+// scales and bounds of MlpScales, from the host copies of the weights.
+int split_weights(dpa4c_model* m, const float* const* theta, const float* const* bias,
+                  const float* w_head) {
+  if (m->n_layers != 3) return 0;   // the per-atom stage refuses the model
+  const int F = m->F, D = m->D_out, KP = mlp_width(D);
+  // largest entry, and over the columns (rows: of the transpose) the largest
+  // 1-norm and 2-norm
+  struct Norms {
+    double big = 0, sum = 0, two = 0, sum_t = 0, two_t = 0;
+  };
+  auto norms = [](const float* w, int K, int N) {
+    Norms r;
+    std::vector<double> s(N, 0.0), q(N, 0.0);
+    for (int k = 0; k < K; ++k) {
+      double rs = 0, rq = 0;
+      for (int c = 0; c < N; ++c) {
+        const double a = std::fabs(double(w[size_t(k) * N + c]));
+        r.big = std::max(r.big, a);
+        s[c] += a;
+        q[c] += a * a;
+        rs += a;
+        rq += a * a;
+      }
+      r.sum_t = std::max(r.sum_t, rs);
+      r.two_t = std::max(r.two_t, std::sqrt(rq));
+    }
+    for (int c = 0; c < N; ++c) {
+      r.sum = std::max(r.sum, s[c]);
+      r.two = std::max(r.two, std::sqrt(q[c]));
+    }
+    return r;
+  };
+  const Norms n1 = norms(theta[0], D, F), n2 = norms(theta[1], F, F), n3 = norms(theta[2], F, F);
+  auto top = [&](const float* v) {
+    double b = 0;
+    for (int c = 0; c < F; ++c) b = std::max(b, std::fabs(double(v[c])));
+    return b;
+  };
+  // exponent that maps a bound below 2^lim
+  auto exponent = [](double b, int lim) {
+    int e = 0;
+    if (b > 0 && std::isfinite(b)) std::frexp(b, &e);
+    return std::max(-100, std::min(100, lim - e));
+  };
+  const double kUp = 1.001;          // float32 rounding of what the bounds stand for
+  MlpScales& sc = m->scales;
+  const int ew[3] = {exponent(n1.big, 14), exponent(n2.big, 14), exponent(n3.big, 14)};
+  for (int t = 0; t < 3; ++t) sc.w_undo[t] = static_cast<float>(std::ldexp(1.0, -ew[t]));
+  sc.d_max = static_cast<float>(n1.sum * kUp);
+  sc.d_norm = static_cast<float>(n1.two * kUp);
+  sc.d_add = static_cast<float>(top(bias[0]) * kUp);
+  sc.h2_mul = static_cast<float>((1.0 + n2.sum) * kUp);
+  sc.h2_add = static_cast<float>(top(bias[1]) * kUp);
+  // backward operands: |SiLU'| < 1.1
+  double w2 = 0;
+  for (int c = 0; c < F; ++c) w2 += double(w_head[c]) * w_head[c];
+  const double wmax = top(w_head);
+  const double p3 = 1.1 * wmax;
+  const double hb2 = wmax + std::min(p3 * n3.sum_t, 1.1 * std::sqrt(w2) * n3.two_t);
+  const double p2 = 1.1 * hb2;
+  const double p1 = 1.1 * (hb2 + p2 * n2.sum_t);
+  const double pb[3] = {p1 * kUp, p2 * kUp, p3 * kUp};
+  for (int t = 0; t < 3; ++t) {
+    const int e = exponent(pb[t], 15);
+    sc.p_up[t] = static_cast<float>(std::ldexp(1.0, e));
+    sc.p_undo[t] = static_cast<float>(std::ldexp(1.0, -(e + ew[t])));
+  }
+  // 2 KB per feature tile and block of 32 inputs
+  const int ft = F / 16, fb = F / 32, dt = KP / 16, db = KP / 32;
+  const size_t unit = 2048;
+  const size_t bytes[6] = {ft * db * unit, ft * fb * unit, ft * fb * unit,
+                           dt * fb * unit, ft * fb * unit, ft * fb * unit};
+  size_t total = 0;
+  for (size_t b : bytes) total += b;
+  DPA4C_TRY(m->wsplit_buf.ensure(total));
+  char* at = m->wsplit_buf.as<char>();
+  for (int t = 0; t < 3; ++t) {
+    m->wsplit[t] = at;
+    at += bytes[t];
+  }
+  for (int t = 0; t < 3; ++t) {
+    m->wsplitT[t] = at;
+    at += bytes[3 + t];
+  }
+  // the float32 matrices, needed only here
+  DevBuf raw;
+  const size_t words[3] = {size_t(D) * F, size_t(F) * F, size_t(F) * F};
+  int rc = raw.ensure(4 * (words[0] + words[1] + words[2]));
+  float* src = raw.as<float>();
+  for (int t = 0; t < 3 && rc == 0; ++t) {
+    const int fin = t == 0 ? D : F, fin_blocks = t == 0 ? db : fb, fin_tiles = t == 0 ? dt : ft;
+    const float up = static_cast<float>(std::ldexp(1.0, ew[t]));
+    const hipError_t e = hipMemcpy(src, theta[t], 4 * words[t], hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      set_error(std::string("upload of the MLP weights: ") + hipGetErrorString(e));
+      rc = DPA4C_ERR_HIP;
+      break;
+    }
+    rc = launch_split_weights(src, fin, F, F, 1, fin_blocks, ft, up, m->wsplit[t], nullptr);
+    if (rc == 0)
+      rc = launch_split_weights(src, F, fin, 1, F, fb, fin_tiles, up, m->wsplitT[t], nullptr);
+    src += words[t];
+  }
+  const hipError_t e = hipDeviceSynchronize();
+  raw.release();
+  if (rc == 0 && e != hipSuccess) {
+    set_error(std::string("split of the MLP weights: ") + hipGetErrorString(e));
+    rc = DPA4C_ERR_HIP;
+  }
+  if (rc) return rc;
+  return 0;
+}
+
+}  // namespace
+
 int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out) {
   if (!out) {
     set_error("dpa4c_model_create: null blob/out or blob shorter than its header");
@@ -451,11 +569,12 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
   }
 
   // ---- one device block for every parameter array ---------------------
-  std::vector<float> inv_sigma(D);
+  // mu and 1/sigma padded with zeros to whole blocks of MLP inputs
+  std::vector<float> inv_sigma(mlp_width(D), 0.0f), mu_pad(mlp_width(D), 0.0f);
+  std::copy(mu, mu + D, mu_pad.begin());
   for (int k = 0; k < D; ++k) inv_sigma[k] = 1.0f / sigma[k];
   struct Piece { void** dst; const void* src; size_t bytes; };
   std::vector<Piece> pieces;
-  std::vector<std::vector<float>> transposed(m->n_layers);
   auto add = [&](void** dst, const void* src, size_t bytes) { pieces.push_back({dst, src, bytes}); };
   add((void**)&m->gtab, gtab.data(), gtab.size() * 4);
   add((void**)&m->qtab, qtab.data(), qtab.size() * 4);
@@ -464,54 +583,16 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
   add((void**)&m->W2, Wa2, size_t(C2) * C2 * 4);
   if (A1) add((void**)&m->A1, A1, size_t(C1) * K1 * 4);
   add((void**)&m->A2, A2, size_t(C2) * K2 * 4);
-  add((void**)&m->mu, mu, size_t(D) * 4);
-  add((void**)&m->inv_sigma, inv_sigma.data(), size_t(D) * 4);
+  add((void**)&m->mu, mu_pad.data(), mu_pad.size() * 4);
+  add((void**)&m->inv_sigma, inv_sigma.data(), inv_sigma.size() * 4);
   add((void**)&m->E_ref, E_ref, size_t(T1) * 4);
-  // Theta_1 is padded with zero rows to a multiple of 16 input features (the
-  // descriptor row stride); every Theta_t is also stored transposed for the
-  // input-gradient products of the backward pass
-  const int Dp = (D + 15) / 16 * 16;
-  std::vector<std::vector<float>> padded(m->n_layers);
-  fan = D;
-  for (int t = 0; t < m->n_layers; ++t) {
-    const int fin = t == 0 ? Dp : F;
-    auto& fw = padded[t];
-    fw.assign(size_t(fin) * F, 0.0f);
-    for (int r = 0; r < fan; ++r)
-      for (int c = 0; c < F; ++c) fw[size_t(r) * F + c] = theta[t][size_t(r) * F + c];
-    add((void**)&m->theta[t], fw.data(), fw.size() * 4);
-    auto& tr = transposed[t];
-    tr.assign(size_t(fin) * F, 0.0f);
-    for (int r = 0; r < fan; ++r)
-      for (int c = 0; c < F; ++c) tr[size_t(c) * fin + r] = theta[t][size_t(r) * F + c];
-    add((void**)&m->thetaT[t], tr.data(), tr.size() * 4);
-    add((void**)&m->bias[t], bias[t], size_t(F) * 4);
-    fan = F;
-  }
-  // fragment order for the fused MLP kernel: for output tile T and k-block kb
-  // lane l holds W[kb*16 + 4*(l/16) + s][T*16 + l%16], s = 0..3
-  auto fragment = [](const std::vector<float>& src, int K, int N) {
-    std::vector<float> out(size_t(K) * N);
-    const int kbs = K / 16;
-    for (int T = 0; T < N / 16; ++T)
-      for (int kb = 0; kb < kbs; ++kb)
-        for (int l = 0; l < 64; ++l)
-          for (int s = 0; s < 4; ++s)
-            out[((size_t(T) * kbs + kb) * 64 + l) * 4 + s] =
-                src[size_t(kb * 16 + (l / 16) * 4 + s) * N + T * 16 + (l % 16)];
-    return out;
-  };
-  std::vector<std::vector<float>> frags(2 * m->n_layers);
-  for (int t = 0; t < m->n_layers; ++t) {
-    const int fin = t == 0 ? Dp : F;
-    frags[2 * t] = fragment(padded[t], fin, F);
-    frags[2 * t + 1] = fragment(transposed[t], F, fin);
-    add((void**)&m->wfrag[t], frags[2 * t].data(), frags[2 * t].size() * 4);
-    add((void**)&m->wfragT[t], frags[2 * t + 1].data(), frags[2 * t + 1].size() * 4);
-  }
+  for (int t = 0; t < m->n_layers; ++t) add((void**)&m->bias[t], bias[t], size_t(F) * 4);
   add((void**)&m->w_head, w_head, size_t(F) * 4);
   m->b_head = b_head[0];
   if (!cpl.empty()) add((void**)&m->cpl, cpl.data(), cpl.size() * 4);
+  std::vector<float> row_tab(row_table_floats(m.get()));
+  build_row_table(m.get(), Wa1, Wa2, A1, A2, cpl.data(), row_tab.data());
+  if (!row_tab.empty()) add((void**)&m->row_tab, row_tab.data(), row_tab.size() * 4);
   // raw pair-network weights, used once by the pair-cache kernel
   const float* raw_wp_in = nullptr;
   const float* raw_wp_out = nullptr;
@@ -540,6 +621,8 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
   DPA4C_HIP_TRY(hipMemcpy(base + first, host.data(), hoff, hipMemcpyHostToDevice));
   int rc = launch_pair_cache(m.get(), raw_wp_in, raw_wp_out);
   if (rc) return rc;
+  rc = split_weights(m.get(), theta, bias, w_head);
+  if (rc) return rc;
   DPA4C_HIP_TRY(hipDeviceSynchronize());
   *out = m.release();
   return 0;
@@ -566,6 +649,7 @@ dpa4c::ModelDev dpa4c_model::dev() const {
   d.inv_sigma = inv_sigma;
   d.cpl = cpl;
   d.E_ref = E_ref;
+  d.row_tab = row_tab;
   d.ftab = ws.ftab.as<float>();
   d.fold_n = fold_n > 0 ? fold_n : 0;
   for (int q = 0; q < 4; ++q) d.c_inv[q] = 1.0f / c_scale[q];

@@ -78,6 +78,12 @@ struct Workspace {
   // per-atom state
   DevBuf node;          // float [N][NS]
   DevBuf node_grad;     // float [N][NS]: dE/d(node state)
+  // rows between the readout and the MLP: mlp_rows atoms, each a row of
+  // mlp_width(D_out) floats, then each a float2 (kMlpRowsFirst of them from
+  // the model's creation on, so that an evaluation without allocation has
+  // some; grown by ensure_mlp_rows)
+  DevBuf mlp_buf;
+  int64_t mlp_rows = 0;
   DevBuf desc;          // float [N][D_out]: D, written only for stage checks
   DevBuf epart;         // double partial sums
   DevBuf flags;         // int64 [8] device flags
@@ -148,11 +154,12 @@ struct dpa4c_model {
   float* mu = nullptr;
   float* inv_sigma = nullptr;
   float* E_ref = nullptr;
-  float* theta[8] = {};             // Theta_t [in][F]
-  float* thetaT[8] = {};            // Theta_t^T [F][in]
   float* bias[8] = {};
-  float* wfrag[8] = {};             // Theta_t in MFMA fragment order
-  float* wfragT[8] = {};            // Theta_t^T in MFMA fragment order
+  dpa4c::DevBuf wsplit_buf;         // the split weights below
+  void* wsplit[3] = {};             // Theta_t split in fragment order (mlp_chain.hip)
+  void* wsplitT[3] = {};            // Theta_t^T
+  dpa4c::MlpScales scales{};
+  float* row_tab = nullptr;         // per-lane tables of the readout (readout_row.h)
   float* w_head = nullptr;
   float b_head = 0;
   float* cpl = nullptr;             // dense (1,2,3) and (2,3,3) couplings (degree three only)

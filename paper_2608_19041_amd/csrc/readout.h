@@ -120,7 +120,7 @@ __device__ void stage_readout_params(ReadoutParams<P>& rp, const ModelDev& md, i
 // Rows that are read as 16-byte vectors are 16-byte aligned: the node state
 // starts 8 bytes into the (aligned) block, so that its Y blocks are.
 template <class P>
-struct alignas(16) ReadoutLds {
+struct alignas(16) ReadoutFwdLds {
   float ypad_[2];
   float y[P::NS];                 // [S0, S1, Y]
   alignas(16) float xt1[3 * P::C1];   // aligned features, Eq. (alignment)
@@ -140,7 +140,11 @@ struct alignas(16) ReadoutLds {
   // T224[m1][m2] = C224 . Z4, T244[m1] = C244 : Z4 Z4
   float xt4[P::L >= 4 ? 9 : 1], t134[P::L >= 4 ? 3 : 1], t224[P::L >= 4 ? 25 : 1],
       t244[P::L >= 4 ? 5 : 1];
-  // backward only
+};
+
+// the same with what the vector-Jacobian product adds
+template <class P>
+struct alignas(16) ReadoutLds : ReadoutFwdLds<P> {
   alignas(16) float gxt1[3 * P::C1];
   alignas(16) float gxt2[5 * P::C2];
   // the Gram adjoints as full symmetric matrices, weights included:
@@ -212,7 +216,7 @@ __device__ inline float half_sum(float v) {
 // Forward intermediates from s.y: M, aligned features, probes, Q, Qv and the
 // partial contractions T, U, W, V of the generic couplings.
 template <class P>
-__device__ inline void readout_intermediates(DPA4C_LDS ReadoutLds<P>& s,
+__device__ inline void readout_intermediates(DPA4C_LDS ReadoutFwdLds<P>& s,
                                              const DPA4C_LDS ReadoutParams<P>& rp, float* M0,
                                              float* M1) {
   const DPA4C_LDS float* cpl = rp.cpl;
@@ -347,7 +351,7 @@ __device__ inline void readout_intermediates(DPA4C_LDS ReadoutLds<P>& s,
 // row ``d`` (P::DSTR entries, zero padded).  s.y must hold the node state and
 // ``x0`` is the atom's row of the type table (Eq. (init-features)).
 template <class P>
-__device__ __attribute__((noinline)) void readout_forward(DPA4C_LDS ReadoutLds<P>& s,
+__device__ __attribute__((noinline)) void readout_forward(DPA4C_LDS ReadoutFwdLds<P>& s,
                                                           const DPA4C_LDS ReadoutParams<P>& rp,
                                                           const float* __restrict__ x0,
                                                           DPA4C_LDS float* d) {

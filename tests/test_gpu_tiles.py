@@ -1,0 +1,79 @@
+"""The per-atom stage at the edges of its tiles, through the C ABI.
+
+The stage takes 16, 32, 48 or 64 atoms a workgroup, whichever leaves the
+fewest rounds, in stretches of at most 65,536 atoms; an atom's E_i and dE/dD
+do not depend on which tile, lane or stretch it falls into.  So
+
+* open clusters of every size around the tile edges equal the oracle, and
+* a crystal tiled from one jittered 108-atom cell, at sizes that take every
+  workgroup shape and more than one stretch, has the E_i and forces of that
+  cell in every copy.  The copies' positions are the cell's plus whole cell
+  vectors, rounded to float64 (at most 6e-14 A in 500 A), which float32 edge
+  vectors turn into at most one rounding of a component (6e-8 of 6 A) for the
+  few edges that round differently, of the 78 of an atom: E_i may differ by a
+  few 1e-6 of the forces' scale, held to 2e-6 eV and 2e-5 eV/A.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import model as om
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dp():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_2608_19041_amd as m
+    m.library()
+    return m
+
+
+def evaluate(dp, model, pos, species, cell, pbc):
+    pos = torch.tensor(pos, dtype=torch.float64, device="cuda")
+    species = torch.tensor(species, dtype=torch.int32, device="cuda")
+    rows = dp.build_neighbors(pos, cell, pbc, 6.0)
+    e, f, _ = model.compute_energy_forces(pos, species, cell, pbc, 6.0, *rows)
+    torch.cuda.synchronize()
+    return e.cpu().numpy(), f.cpu().numpy()
+
+
+@pytest.mark.parametrize("name", ["nano", "mini", "air", "full", "plus_l4"])
+def test_open_clusters_around_the_tile_edges(dp, name):
+    spec, w = synth.model_weights(name)
+    model = dp.Model(synth.pack_blob(spec, w))
+    oracle = om.Oracle(spec, w)
+    s = synth.fcc_copper(3, 0.08, seed=11)
+    pbc = np.zeros(3, np.int32)
+    for n in (1, 2, 15, 16, 17, 33, 63, 64, 65):
+        pos, species = s.pos[:n], s.species[:n]
+        e, f = evaluate(dp, model, pos, species, s.cell, pbc)
+        ref_e, ref_f = oracle.energy_forces(pos, species, s.cell, pbc)
+        assert np.abs(e - ref_e).max() < 1e-5 and np.abs(f - ref_f).max() < 1e-4, n
+
+
+@pytest.mark.parametrize("name,reps", [
+    ("full", [(3, 3, 4), (3, 5, 5), (4, 5, 5), (5, 5, 5), (6, 6, 7), (8, 9, 9)]),
+    ("air", [(4, 5, 6), (6, 6, 7)]),
+    ("mini", [(5, 5, 5)]),
+    ("nano", [(6, 6, 7)]),
+])
+def test_tiled_crystal_repeats_its_cell(dp, name, reps):
+    spec, w = synth.model_weights(name)
+    model = dp.Model(synth.pack_blob(spec, w))
+    s = synth.fcc_copper(3, 0.08, seed=12)
+    e0, f0 = evaluate(dp, model, s.pos, s.species, s.cell, s.pbc)
+    ref_e, ref_f = om.Oracle(spec, w).energy_forces(s.pos, s.species, s.cell, s.pbc)
+    assert np.abs(e0 - ref_e).max() < 1e-5 and np.abs(f0 - ref_f).max() < 1e-4
+    for r in reps:
+        shift = np.stack(np.meshgrid(*(np.arange(k) for k in r), indexing="ij"), -1).reshape(-1, 3)
+        pos = (s.pos[None] + (shift @ s.cell)[:, None]).reshape(-1, 3)
+        e, f = evaluate(dp, model, pos, np.tile(s.species, len(shift)), s.cell * np.array(r)[:, None],
+                        s.pbc)
+        de = np.abs(e.reshape(len(shift), -1) - e0).max()
+        df = np.abs(f.reshape(len(shift), -1, 3) - f0).max()
+        print(f"{name} {len(pos)} atoms: copies differ by {de:.1e} eV, {df:.1e} eV/A", flush=True)
+        assert de < 2e-6 and df < 2e-5, (r, de, df)
