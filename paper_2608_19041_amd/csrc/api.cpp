@@ -187,8 +187,6 @@ int ensure_workspace(dpa4c_model* m, int64_t n, int64_t cap) {
   DPA4C_TRY(w.flags.ensure(8 * 8));
   DPA4C_TRY(w.eatom.ensure(8 * nn));
   DPA4C_TRY(w.fidx.ensure(4 * nn));
-  DPA4C_TRY(w.fold_mask.ensure(4 * sizeof(uint32_t)));
-  DPA4C_TRY(w.check.ensure(2 * sizeof(int64_t)));
   return ensure_mlp_rows(m, nn);
 }
 
@@ -203,8 +201,6 @@ EvalBufs ws_bufs(Workspace& w) {
   b.node_grad = w.node_grad.as<float>();
   b.epart = w.epart.as<double>();
   b.fidx = w.fidx.as<int32_t>();
-  b.fold_mask = w.fold_mask.as<uint32_t>();
-  b.check = w.check.as<int64_t>();
   return b;
 }
 
@@ -356,9 +352,8 @@ void dpa4c_model_destroy(dpa4c_model* m) {
                     &w.edge,     &w.cskin,  &w.node,
                     &w.mlp_buf,  &w.desc,     &w.node_grad, &w.epart,  &w.flags,      &w.inv_mass, &w.mass,
                     &w.eatom,    &w.tailpart,  &w.backup,  &w.ftab,      &w.fold_map, &w.fold_mask,  &w.fidx,
-                    &w.check,
                     &w.nb.qpos,  &w.nb.wrap, &w.nb.cell_of, &w.nb.cell_cnt, &w.nb.cell_start,
-                    &w.nb.cell_fill, &w.nb.cell_rec, &w.nb.long_keys, &w.nb.counts,
+                    &w.nb.cell_rec, &w.nb.long_keys, &w.nb.counts,
                     &w.nb.partials,
                     &w.virpart,  &w.nvt,     &w.watom,     &w.nb.extent};
   for (DevBuf* b : bufs) b->release();
@@ -426,12 +421,8 @@ int build_neighbors(const double* pos, int64_t N, const double cell[9], const in
     return 0;
   }
   int64_t* flags = fl->as<int64_t>();
-  DPA4C_HIP_TRY(hipMemsetAsync(flags, 0, 64, st));
-  rc = build_skin_list(*nb, pos, N, g, row_ptr, flags, st);
+  rc = build_skin_list(*nb, pos, N, g, row_ptr, flags, true, hflag, st);
   if (rc) return rc;
-  DPA4C_HIP_TRY(hipMemcpyAsync(hflag, row_ptr + N, 8, hipMemcpyDeviceToHost, st));
-  DPA4C_HIP_TRY(hipMemcpyAsync(hflag + 1, flags, 8, hipMemcpyDeviceToHost, st));
-  DPA4C_HIP_TRY(hipMemcpyAsync(hflag + 2, flags + 3, 8, hipMemcpyDeviceToHost, st));
   DPA4C_HIP_TRY(hipStreamSynchronize(st));
   if (hflag[1] & kFlagNonFinite) return flags_to_error(hflag[1]);
   *n_pairs = hflag[0];
@@ -440,9 +431,9 @@ int build_neighbors(const double* pos, int64_t N, const double cell[9], const in
               " edges");
     return DPA4C_ERR_CAPACITY;
   }
-  rc = fill_skin_list(*nb, N, g, row_ptr, nbr_j, nbr_shift, cap, flags, hflag[2], nullptr, st);
+  rc = fill_skin_list(*nb, N, g, row_ptr, nbr_j, nbr_shift, cap, flags, hflag[2], nullptr,
+                      hflag + 1, st);
   if (rc) return rc;
-  DPA4C_HIP_TRY(hipMemcpyAsync(hflag + 1, flags, 8, hipMemcpyDeviceToHost, st));
   DPA4C_HIP_TRY(hipStreamSynchronize(st));
   return flags_to_error(hflag[1]);
 }
@@ -457,7 +448,7 @@ void eval_buf_sizes(int64_t n, int64_t cap, int ns, size_t sizes[kEvalBufs]) {
   const size_t raw[kEvalBufs] = {4 * nn,       16 * cc,      4 * cc,
                                  8 * cc,       4 * nn * size_t(ns),
                                  4 * nn * size_t(ns),        8 * (size_t(partial_count(int64_t(nn))) + 8),
-                                 4 * nn,       4 * sizeof(uint32_t), 2 * sizeof(int64_t)};
+                                 4 * nn};
   for (int k = 0; k < kEvalBufs; ++k) sizes[k] = r256(raw[k]);
 }
 
@@ -513,22 +504,17 @@ int energy_forces_core(const dpa4c_model* m, const double* pos, const int32_t* s
   if (own) w.list_valid = false;   // the reverse index now describes the caller's list
   {
     StageScope t(m, kStSkinRev, st, own);
-    // the reverse search's samples live in the edge records, which the
-    // forward kernel rewrites before reading them
-    rc = launch_zero_i64(B.check, 2, st);
-    if (rc) return rc;
+    // the reverse search's samples live in the edge records and the partial
+    // masks and counts in the node state; the forward kernel rewrites both
+    // before anything reads them
+    const ListCheck lc{species, m->n_types + 1, B.node, w.fold_host};
     rc = launch_skin_rev(row_ptr, nbr_j, nbr_shift, N, n_pairs, reinterpret_cast<int32_t*>(B.edge),
-                         false, B.skin_rev, B.check, nullptr, st);
+                         false, B.skin_rev, &lc, nullptr, st);
     if (rc) return rc;
   }
-  // the list's size and the pairs found come back with the species mask
-  // (prepare_species synchronises the stream)
-  int64_t* hcheck = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(w.fold_host) + 16);
-  DPA4C_HIP_TRY(hipMemcpyAsync(hcheck, row_ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  DPA4C_HIP_TRY(hipMemcpyAsync(hcheck + 1, B.check, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  bool use_fold = false;
-  rc = prepare_species(mm, species, N, B.fold_mask, B.fidx, own, &use_fold, st);
-  if (rc) return rc;
+  DPA4C_HIP_TRY(hipStreamSynchronize(st));
+  const int64_t* hcheck =
+      reinterpret_cast<const int64_t*>(reinterpret_cast<const char*>(w.fold_host) + 16);
   if (hcheck[0] > n_pairs || hcheck[0] < 0) {
     set_error("compute_energy_forces: the list holds row_ptr[N] = " + std::to_string(hcheck[0]) +
               " entries, outside [0, n_pairs = " + std::to_string(n_pairs) + "]");
@@ -540,6 +526,11 @@ int energy_forces_core(const dpa4c_model* m, const double* pos, const int32_t* s
               " entries have no reverse (j -> i, -n))");
     return DPA4C_ERR_INVALID_ARG;
   }
+  uint32_t mask[4];
+  std::memcpy(mask, w.fold_host, sizeof(mask));
+  bool use_fold = false;
+  rc = prepare_species(mm, mask, species, N, B.fidx, own, &use_fold, st);
+  if (rc) return rc;
   VirialOut vo{};
   if (virial) {
     if (own) {
@@ -636,24 +627,33 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
 
   // masses on the device
   const int np_tail = tail_partial_count(N);
-  DPA4C_TRY(w.inv_mass.ensure(8 * T1));
-  DPA4C_TRY(w.mass.ensure(8 * T1));
   DPA4C_TRY(w.flags.ensure(64));
   DPA4C_TRY(w.tailpart.ensure(32 * size_t(np_tail)));
   DPA4C_TRY(w.skin_row.ensure(8 * (N + 1)));
   DPA4C_TRY(w.qbuild.ensure(8 * 3 * N));
   if (!w.host_flags) DPA4C_HIP_TRY(hipHostMalloc((void**)&w.host_flags, 64, hipHostMallocDefault));
-  {
+  // (uploaded only when their values changed since the last call)
+  if (w.host_mass.size() != size_t(T1) ||
+      std::memcmp(w.host_mass.data(), mass_by_species, 8 * size_t(T1)) != 0) {
+    w.host_mass.clear();
+    DPA4C_TRY(w.inv_mass.ensure(8 * T1));
+    DPA4C_TRY(w.mass.ensure(8 * T1));
     std::vector<double> im(T1);
     for (int t = 0; t < T1; ++t) im[t] = 1.0 / (mass_by_species[t] * (1.66053906660e-17 / 1.602176634e-19));
     DPA4C_HIP_TRY(hipMemcpyAsync(w.inv_mass.p, im.data(), 8 * T1, hipMemcpyHostToDevice, st));
     DPA4C_HIP_TRY(hipMemcpyAsync(w.mass.p, mass_by_species, 8 * T1, hipMemcpyHostToDevice, st));
+    DPA4C_HIP_TRY(hipStreamSynchronize(st));   // ``im`` and the values are complete on the device
+    w.host_mass.assign(mass_by_species, mass_by_species + T1);
   }
   DPA4C_TRY(w.fidx.ensure(4 * size_t(N)));
-  DPA4C_TRY(w.fold_mask.ensure(4 * sizeof(uint32_t)));
+  DPA4C_TRY(w.fold_mask.ensure(16 * 256));
   bool use_fold = false;
-  rc = prepare_species(mm, species, N, w.fold_mask.as<uint32_t>(), w.fidx.as<int32_t>(), true,
-                       &use_fold, st);
+  rc = launch_presence(species, N, T1, w.fold_mask.as<uint32_t>(), w.fold_host, st);
+  if (rc) return rc;
+  DPA4C_HIP_TRY(hipStreamSynchronize(st));
+  uint32_t mask[4];
+  std::memcpy(mask, w.fold_host, sizeof(mask));
+  rc = prepare_species(mm, mask, species, N, w.fidx.as<int32_t>(), true, &use_fold, st);
   if (rc) return rc;
   const int32_t* fidx = use_fold ? w.fidx.as<int32_t>() : nullptr;
   int64_t* flags = w.flags.as<int64_t>();
@@ -697,13 +697,10 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
     }
     {
       StageScope t(m, kStNeighbor, st);
-      r = build_skin_list(w.nb, pos, N, g_list, w.skin_row.as<int64_t>(), flags, st);
+      r = build_skin_list(w.nb, pos, N, g_list, w.skin_row.as<int64_t>(), flags, false,
+                          w.host_flags, st);
       if (r) return r;
     }
-    DPA4C_HIP_TRY(hipMemcpyAsync(w.host_flags, w.skin_row.as<int64_t>() + N, 8,
-                                 hipMemcpyDeviceToHost, st));
-    DPA4C_HIP_TRY(hipMemcpyAsync(w.host_flags + 1, flags, 8, hipMemcpyDeviceToHost, st));
-    DPA4C_HIP_TRY(hipMemcpyAsync(w.host_flags + 2, flags + 3, 8, hipMemcpyDeviceToHost, st));
     DPA4C_HIP_TRY(hipStreamSynchronize(st));
     if (w.host_flags[1]) return flags_to_error(w.host_flags[1]);
     const int64_t need = w.host_flags[0];
@@ -722,7 +719,7 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
     // forward kernel rewrites before reading them
     r = fill_skin_list(w.nb, N, g_list, w.skin_row.as<int64_t>(), w.skin_j.as<int32_t>(),
                        w.skin_shift.as<int32_t>(), w.cap, flags, w.host_flags[2],
-                       w.edge.as<int32_t>(), st);
+                       w.edge.as<int32_t>(), nullptr, st);
     if (r) return r;
     r = launch_skin_rev(w.skin_row.as<int64_t>(), w.skin_j.as<int32_t>(), w.skin_shift.as<int32_t>(),
                         N, w.cap, w.edge.as<int32_t>(), true, w.skin_rev.as<int64_t>(), nullptr,
@@ -774,9 +771,7 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
       a.e_thermo = nvt->e_thermo + prev;
       a.virial = nvt->virial ? nvt->virial + 9 * prev : nullptr;
     } else {
-      int r = launch_kinetic(vel, species, w.mass.as<double>(), T1, N, kin_part, st);
-      if (r) return r;
-      a.part_k = kin_part;
+      a.part_k = kin_part;   // of the current velocities
       a.np = npk;
     }
     a.open_next = open ? 1 : 0;
@@ -798,7 +793,11 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
         if (prev >= 0) {
           int r = chain_launch(prev, false);
           if (r) return r;
-          r = launch_scale(vel, N, nvt_state + 2 * nvt->length, st);
+          r = launch_scale_kinetic(vel, species, w.mass.as<double>(), T1, N,
+                                   nvt_state + 2 * nvt->length, kin_part, st);
+          if (r) return r;
+        } else {
+          int r = launch_kinetic(vel, species, w.mass.as<double>(), T1, N, kin_part, st);
           if (r) return r;
         }
         int r = chain_launch(-1, true);
@@ -863,12 +862,14 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
   // steps before this call's first)
   int64_t last_build = reuse ? -1 - w.list_steps_since_build : 0, batch = 8;
   double growth = 0.0;   // A per step since the last build, from the last batch
+  bool read = false;     // the flags hold nothing that was not read back
   for (int64_t s = reuse ? 0 : 1; s < nsteps;) {
     if (rebuild_every > 0 && s % rebuild_every == 0) {
       rc = one_step(s, true, true, -1, false, false);
       if (rc) return rc;
       rc = finish(s);
       if (rc) return rc;
+      read = false;
       last_build = s++;
       continue;
     }
@@ -877,14 +878,8 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
       const int64_t next_forced = (s / rebuild_every + 1) * rebuild_every;
       if (next_forced < e) e = next_forced;
     }
-    DPA4C_HIP_TRY(hipMemcpyAsync(bk, pos, state, hipMemcpyDeviceToDevice, st));
-    DPA4C_HIP_TRY(hipMemcpyAsync(bk + 3 * N, vel, state, hipMemcpyDeviceToDevice, st));
-    DPA4C_HIP_TRY(hipMemcpyAsync(bk + 6 * N, forces, state, hipMemcpyDeviceToDevice, st));
-    if (nvt)
-      DPA4C_HIP_TRY(hipMemcpyAsync(nvt_backup, nvt_state, 8 * nvt_words, hipMemcpyDeviceToDevice, st));
-    rc = launch_set_flag(flags, 4, INT64_MAX, st);
-    if (rc) return rc;
-    rc = launch_set_flag(flags, 5, 0, st);
+    rc = launch_batch_start(pos, vel, forces, N, bk, nvt_state, nvt_backup,
+                            static_cast<int>(nvt_words), flags, st);
     if (rc) return rc;
     for (int64_t t = s; t < e; ++t) {
       rc = one_step(t, true, false, t > s ? t - 1 : -1, t > s, t + 1 < e);
@@ -897,7 +892,8 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
     rc = flags_to_error(w.host_flags[0]);
     if (rc) return rc;
     const int64_t v = w.host_flags[4];
-    if (v == INT64_MAX) {
+    read = v == INT64_MAX;
+    if (read) {
       // no violation: size the next batch from the displacement growth
       const double d = std::sqrt(double(w.host_flags[5])) / kQScale;
       growth = d / double(e - last_build);
@@ -941,8 +937,10 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
   if (nvt)
     DPA4C_HIP_TRY(hipMemcpyAsync(nvt->chain, nvt_state, 16 * size_t(nvt->length),
                                  hipMemcpyDeviceToDevice, st));
-  DPA4C_HIP_TRY(hipMemcpyAsync(w.host_flags, flags, 64, hipMemcpyDeviceToHost, st));
-  DPA4C_HIP_TRY(hipStreamSynchronize(st));
+  if (!read) {
+    DPA4C_HIP_TRY(hipMemcpyAsync(w.host_flags, flags, 64, hipMemcpyDeviceToHost, st));
+    DPA4C_HIP_TRY(hipStreamSynchronize(st));
+  }
   if (n_rebuilds) *n_rebuilds = rebuilds;
   if (nsteps > 0) w.list_steps_since_build = nsteps - 1 - last_build;
   return flags_to_error(w.host_flags[0]);

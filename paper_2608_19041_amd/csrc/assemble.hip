@@ -53,9 +53,51 @@ __global__ void __launch_bounds__(kRedBlock) final_sum_kernel(const double* __re
   if (threadIdx.x == 0) *out = tot;
 }
 
+// Both passes in one launch for up to kSumOne slices: four groups of
+// kRedBlock threads take a slice each, in the order and tree of
+// partial_sum_kernel, then the first group adds the partials as
+// final_sum_kernel does, so the sum has the same bits.
+constexpr int kSumGroups = 4;
+constexpr int kSumOne = 2 * kSumGroups;   // 32,768 values: above, one block takes longer than two launches
+__global__ void __launch_bounds__(kSumGroups * kRedBlock) sum_one_kernel(const double* __restrict__ x,
+                                                                         int64_t n, int np,
+                                                                         double* __restrict__ out) {
+  __shared__ double sh[kSumGroups][kRedBlock];
+  __shared__ double part[kSumOne];
+  const int t = threadIdx.x % kRedBlock, g = threadIdx.x / kRedBlock;
+  auto tree = [&](double v) {
+    sh[g][t] = v;
+    __syncthreads();
+    for (int off = kRedBlock / 2; off > 0; off >>= 1) {
+      if (t < off) sh[g][t] += sh[g][t + off];
+      __syncthreads();
+    }
+    return sh[g][0];
+  };
+  for (int b = 0; b < np; b += kSumGroups) {
+    const int64_t base = (b + g) * int64_t(kRedBlock * kRedPer) + t;
+    double s = 0.0;
+    for (int q = 0; q < kRedPer; ++q) {
+      const int64_t i = base + int64_t(q) * kRedBlock;
+      if (i < n) s += x[i];
+    }
+    const double tot = tree(s);
+    if (t == 0 && b + g < np) part[b + g] = tot;
+    __syncthreads();
+  }
+  const double tot = tree(g == 0 && t < np ? part[t] : 0.0);
+  if (threadIdx.x == 0) *out = tot;
+}
+
 int fixed_sum(const double* x, int64_t n, double* partials, double* out, hipStream_t st) {
   int64_t np = (n + kRedBlock * kRedPer - 1) / (kRedBlock * kRedPer);
   if (np < 1) np = 1;
+  if (np <= kSumOne) {
+    hipLaunchKernelGGL(sum_one_kernel, dim3(1), dim3(kSumGroups * kRedBlock), 0, st, x, n,
+                       static_cast<int>(np), out);
+    DPA4C_HIP_TRY(hipGetLastError());
+    return 0;
+  }
   hipLaunchKernelGGL(partial_sum_kernel, dim3(np), dim3(kRedBlock), 0, st, x, n, partials);
   hipLaunchKernelGGL(final_sum_kernel, dim3(1), dim3(kRedBlock), 0, st, partials, np, out);
   DPA4C_HIP_TRY(hipGetLastError());
@@ -129,13 +171,16 @@ __device__ inline DriftCheck merge(DriftCheck a, const DriftCheck& b) {
 // one set of atomics for the merged checks of several atoms of step
 // ``step``: flags[0] bit 3 marks a bad position, flags[1] a violation,
 // flags[4] takes the smallest violating step and flags[5] the largest |dq|^2
+// (an atomic on one word takes 12 ns after the other, so the maximum is looked
+// at first and most blocks leave it alone)
 __device__ inline void record_check(const DriftCheck& c, int64_t* __restrict__ flags, int64_t step) {
   if (c.bad) atomicOr(reinterpret_cast<unsigned long long*>(flags), 8ull);
   if (c.viol) {
     atomicOr(reinterpret_cast<unsigned long long*>(flags + 1), 1ull);
     atomicMin(reinterpret_cast<unsigned long long*>(flags + 4), (unsigned long long)step);
   }
-  if (c.d2 > 0) atomicMax(reinterpret_cast<unsigned long long*>(flags + 5), (unsigned long long)c.d2);
+  if (c.d2 > 0 && c.d2 > __hip_atomic_load(flags + 5, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(reinterpret_cast<unsigned long long*>(flags + 5), (unsigned long long)c.d2);
 }
 
 // v += dt/2 F/m (after v *= *scale when a scale is given) and optionally the
@@ -230,6 +275,7 @@ __global__ void __launch_bounds__(kBlock) forces_kernel(int64_t n, const int64_t
   const int sub = threadIdx.x % kLanesPerAtom, slot = threadIdx.x / kLanesPerAtom;
   const int64_t groups = (n + APG - 1) / APG;
   double blk_e = 0.0, blk_k = 0.0, blk_v = 0.0;   // the block's partials (threads 0, 0..8)
+  DriftCheck blk_c{0, 0, 0};
   for (int64_t grp = xcd_block(blockIdx.x, nblk); grp < groups; grp += nblk) {
     const int64_t k = grp * APG + slot;
     // the step's per-atom inputs, requested before the row so that their
@@ -315,7 +361,7 @@ __global__ void __launch_bounds__(kBlock) forces_kernel(int64_t n, const int64_t
         }
         blk_e += se;
         blk_k += sk;
-        if (tl.kick_next) record_check(c, tl.flags, tl.next_step);
+        blk_c = merge(blk_c, c);
       }
       if (VIR && threadIdx.x < 9) {
         const int c = threadIdx.x;
@@ -330,6 +376,7 @@ __global__ void __launch_bounds__(kBlock) forces_kernel(int64_t n, const int64_t
   if (TAIL && threadIdx.x == 0) {
     tl.part_e[blockIdx.x] = blk_e;
     tl.part_k[blockIdx.x] = blk_k;
+    if (tl.kick_next) record_check(blk_c, tl.flags, tl.next_step);
   }
   if (VIR && threadIdx.x < 9) vo.part_v[9 * blockIdx.x + threadIdx.x] = blk_v;
 }
@@ -366,12 +413,31 @@ __device__ double chain_half_step(const NhcArgs& a, double* xi, double* v, doubl
   return s;
 }
 
-// fixed-order sum over p < np of part[stride p + c] by one block
-__device__ inline double sum_strided(const double* __restrict__ part, int64_t np, int stride, int c,
-                                     double* sh) {
-  double s = 0.0;
-  for (int64_t p = threadIdx.x; p < np; p += kBlock) s += part[stride * p + c];
-  return block_sum(s, sh);
+// Sums over p < np of part[stride p + c], each in the order and tree of
+// sum_partials: a block of kSumGroups x kBlock threads takes kSumGroups sums
+// at a time, one for each group of kBlock threads.  get(q, &part, &stride, &c)
+// names sum q < nsum (null part: zero); out[q] in LDS or memory.
+template <class Get>
+__device__ inline void grouped_sums(int nsum, int64_t np, double* out, Get&& get) {
+  __shared__ double sh[kSumGroups][kBlock];
+  const int t = threadIdx.x % kBlock, g = threadIdx.x / kBlock;
+  for (int q0 = 0; q0 < nsum; q0 += kSumGroups) {
+    const int q = q0 + g;
+    const double* part = nullptr;
+    int stride = 1, c = 0;
+    if (q < nsum) get(q, &part, &stride, &c);
+    double s = 0.0;
+    if (part)
+      for (int64_t p = t; p < np; p += kBlock) s += part[stride * p + c];
+    sh[g][t] = s;
+    __syncthreads();
+    for (int off = kBlock / 2; off > 0; off >>= 1) {
+      if (t < off) sh[g][t] += sh[g][t + off];
+      __syncthreads();
+    }
+    if (t == 0 && q < nsum) out[q] = sh[g][0];
+    __syncthreads();
+  }
 }
 
 // One block.  Closing a step: its kinetic energy K (partials part_k), the
@@ -379,22 +445,22 @@ __device__ inline double sum_strided(const double* __restrict__ part, int64_t np
 // the thermostat energy and the virial of the step.  Opening a step: the
 // chain half step for the current K.  state[2M] = the product of the scales
 // of both, which the next kick (or launch_scale) applies.
-__global__ void __launch_bounds__(kBlock) nhc_kernel(NhcArgs a) {
-  __shared__ double sh[kBlock];
-  double ke = sum_strided(a.part_k, a.np, 1, 0, sh);
-  __syncthreads();
-  double pe = 0.0, vir[9];
-  if (a.close_prev && a.e_pot) {
-    pe = sum_strided(a.part_e, a.np, 1, 0, sh);
-    __syncthreads();
-  }
-  for (int c = 0; c < 9; ++c) {
-    vir[c] = 0.0;
-    if (a.close_prev && a.virial) {
-      vir[c] = sum_strided(a.part_v, a.np, 9, c, sh);
-      __syncthreads();
-    }
-  }
+// Eleven sums: kinetic energy, potential energy, nine of the virial.
+__global__ void __launch_bounds__(kSumGroups * kBlock) nhc_kernel(NhcArgs a) {
+  __shared__ double sums[11];
+  grouped_sums(a.close_prev ? (a.virial ? 11 : 2) : 1, a.np, sums,
+               [&](int q, const double** part, int* stride, int* c) {
+                 if (q == 0) *part = a.part_k;
+                 else if (q == 1) *part = a.e_pot ? a.part_e : nullptr;
+                 else {
+                   *part = a.part_v;
+                   *stride = 9;
+                   *c = q - 2;
+                 }
+               });
+  double ke = sums[0];
+  const double pe = sums[1];
+  const double* vir = sums + 2;
   if (threadIdx.x != 0) return;
   double* xi = a.state;
   double* v = a.state + a.M;
@@ -435,6 +501,32 @@ __global__ void __launch_bounds__(kBlock) kinetic_kernel(const double* __restric
   if (threadIdx.x == 0) part_k[blockIdx.x] = tk;
 }
 
+// v *= *scale, then the partials of kinetic_kernel (the same arithmetic)
+__global__ void __launch_bounds__(kBlock) scale_kinetic_kernel(double* __restrict__ vel,
+                                                               const int32_t* __restrict__ species,
+                                                               const double* __restrict__ mass,
+                                                               int n_types1, int64_t n,
+                                                               const double* __restrict__ scale,
+                                                               double* __restrict__ part_k) {
+  __shared__ double sh[kBlock];
+  const int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x;
+  double ek = 0.0;
+  if (i < n) {
+    const double s = *scale;
+    int a0 = species[i];
+    a0 = static_cast<unsigned>(a0) < static_cast<unsigned>(n_types1) ? a0 : n_types1 - 1;
+    double v2 = 0.0;
+    for (int a = 0; a < 3; ++a) {
+      const double v = __dmul_rn(vel[3 * i + a], s);
+      vel[3 * i + a] = v;
+      v2 += v * v;
+    }
+    ek = 0.5 * mass[a0] * v2 * (1.66053906660e-17 / 1.602176634e-19);
+  }
+  const double tk = block_sum(ek, sh);
+  if (threadIdx.x == 0) part_k[blockIdx.x] = tk;
+}
+
 __global__ void __launch_bounds__(kBlock) scale_kernel(double* __restrict__ vel, int64_t n3,
                                                        const double* __restrict__ scale) {
   const int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x;
@@ -459,8 +551,28 @@ __global__ void __launch_bounds__(kBlock) snapshot_kernel(const double* __restri
   qbuild[i] = qfix(pos[i]);
 }
 
-__global__ void set_flag_kernel(int64_t* flags, int idx, int64_t value) {
-  if (threadIdx.x == 0) flags[idx] = value;
+// the start of a batch: positions, velocities, forces (and the chain state)
+// saved, the violation step and the largest displacement reset
+__global__ void __launch_bounds__(kBlock) batch_start_kernel(const double* __restrict__ pos,
+                                                             const double* __restrict__ vel,
+                                                             const double* __restrict__ forces,
+                                                             int64_t n3, double* __restrict__ saved,
+                                                             const double* __restrict__ chain,
+                                                             double* __restrict__ chain_saved,
+                                                             int words, int64_t* __restrict__ flags) {
+  const int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x;
+  if (i < n3) {
+    saved[i] = pos[i];
+    saved[n3 + i] = vel[i];
+    saved[2 * n3 + i] = forces[i];
+  }
+  if (blockIdx.x == 0) {
+    if (static_cast<int>(threadIdx.x) < words) chain_saved[threadIdx.x] = chain[threadIdx.x];
+    if (threadIdx.x == 0) {
+      flags[4] = INT64_MAX;
+      flags[5] = 0;
+    }
+  }
 }
 
 __global__ void __launch_bounds__(kBlock) zero_i64_kernel(int64_t* __restrict__ p, int64_t n) {
@@ -501,21 +613,18 @@ int launch_forces(int64_t n, const int64_t* row_ptr, const int32_t* ecount, cons
 
 // out[c] = sum over p < np of part[ncomp p + c], c < ncomp, in a fixed order
 // (one block)
-__global__ void __launch_bounds__(kRedBlock) sum_components_kernel(const double* __restrict__ part,
-                                                                   int64_t np, int ncomp,
-                                                                   double* __restrict__ out) {
-  __shared__ double sh[kRedBlock];
-  for (int c = 0; c < ncomp; ++c) {
-    double s = 0.0;
-    for (int64_t p = threadIdx.x; p < np; p += kRedBlock) s += part[ncomp * p + c];
-    const double tot = block_sum(s, sh);
-    if (threadIdx.x == 0) out[c] = tot;
-    __syncthreads();
-  }
+__global__ void __launch_bounds__(kSumGroups * kBlock) sum_components_kernel(
+    const double* __restrict__ part, int64_t np, int ncomp, double* __restrict__ out) {
+  grouped_sums(ncomp, np, out, [&](int q, const double** from, int* stride, int* c) {
+    *from = part;
+    *stride = ncomp;
+    *c = q;
+  });
 }
 
 int launch_sum_components(const double* part, int64_t np, int ncomp, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(sum_components_kernel, dim3(1), dim3(kRedBlock), 0, st, part, np, ncomp, out);
+  hipLaunchKernelGGL(sum_components_kernel, dim3(1), dim3(kSumGroups * kBlock), 0, st, part, np,
+                     ncomp, out);
   DPA4C_HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -537,7 +646,7 @@ int launch_kick_drift(double* pos, double* vel, const double* forces, const int3
 
 int launch_nhc(const NhcArgs& a, hipStream_t st) {
   if (a.M < 1 || a.M > kMaxChain || !a.state || !a.part_k || a.np < 1) return DPA4C_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(nhc_kernel, dim3(1), dim3(kBlock), 0, st, a);
+  hipLaunchKernelGGL(nhc_kernel, dim3(1), dim3(kSumGroups * kBlock), 0, st, a);
   DPA4C_HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -548,6 +657,14 @@ int launch_kinetic(const double* vel, const int32_t* species, const double* mass
                    int64_t n, double* part_k, hipStream_t st) {
   hipLaunchKernelGGL(kinetic_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, st, vel, species, mass,
                      n_types1, n, part_k);
+  DPA4C_HIP_TRY(hipGetLastError());
+  return 0;
+}
+
+int launch_scale_kinetic(double* vel, const int32_t* species, const double* mass, int n_types1,
+                         int64_t n, const double* scale, double* part_k, hipStream_t st) {
+  hipLaunchKernelGGL(scale_kinetic_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, st, vel, species,
+                     mass, n_types1, n, scale, part_k);
   DPA4C_HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -577,8 +694,11 @@ int launch_snapshot_q(const double* pos, int64_t n, int64_t* qbuild, hipStream_t
   return 0;
 }
 
-int launch_set_flag(int64_t* flags, int idx, int64_t value, hipStream_t st) {
-  hipLaunchKernelGGL(set_flag_kernel, dim3(1), dim3(64), 0, st, flags, idx, value);
+int launch_batch_start(const double* pos, const double* vel, const double* forces, int64_t n,
+                       double* saved, const double* chain, double* chain_saved, int words,
+                       int64_t* flags, hipStream_t st) {
+  hipLaunchKernelGGL(batch_start_kernel, dim3(blocks_for(3 * n)), dim3(kBlock), 0, st, pos, vel,
+                     forces, 3 * n, saved, chain, chain_saved, words, flags);
   DPA4C_HIP_TRY(hipGetLastError());
   return 0;
 }

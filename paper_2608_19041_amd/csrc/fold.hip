@@ -46,23 +46,6 @@ namespace dpa4c {
 
 namespace {
 
-// species bitmask: each thread collects the bits of its atoms, a wave merges
-// them and issues one atomic per word
-__global__ void presence_kernel(const int32_t* __restrict__ species, int64_t n, int n_types1,
-                                uint32_t* __restrict__ mask) {
-  uint32_t m[4] = {0u, 0u, 0u, 0u};
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const int a = clamp_type(species[i], n_types1);
-    m[a >> 5] |= 1u << (a & 31);
-  }
-  for (int off = 1; off < kWave; off <<= 1)
-    for (int w = 0; w < 4; ++w) m[w] |= __shfl_xor(m[w], off);
-  if ((threadIdx.x & (kWave - 1)) == 0)
-    for (int w = 0; w < 4; ++w)
-      if (m[w]) atomicOr(&mask[w], m[w]);
-}
-
 __global__ void fold_index_kernel(const int32_t* __restrict__ species, int64_t n, int n_types1,
                                   const int32_t* __restrict__ map, int32_t* __restrict__ fidx) {
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n;
@@ -110,10 +93,6 @@ __global__ void fold_build_kernel(const float* __restrict__ gtab, const float* _
   }
 }
 
-__global__ void zero_u32_kernel(uint32_t* p, int n) {
-  if (static_cast<int>(threadIdx.x) < n) p[threadIdx.x] = 0u;
-}
-
 int grid_for(int64_t n) {
   int64_t b = (n + 255) / 256;
   return static_cast<int>(b < 4096 ? (b < 1 ? 1 : b) : 4096);
@@ -121,27 +100,19 @@ int grid_for(int64_t n) {
 
 }  // namespace
 
-int prepare_species(dpa4c_model* m, const int32_t* species, int64_t n, uint32_t* mask_dev,
+int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* species, int64_t n,
                     int32_t* fidx, bool may_alloc, bool* use_fold, hipStream_t st) {
   Workspace& w = m->ws;
   const int T1 = m->n_types + 1;
   *use_fold = false;
   if (n <= 0) return 0;
-  // the type map and the pinned host words ([0, 16) the presence mask,
-  // [64, 64 + 4 T1) the type map) are allocated with the model
+  // the type map and the pinned host words ([64, 64 + 4 T1): the type map) are
+  // allocated with the model
   if (!w.fold_host || !w.fold_map.p) {
     set_error("prepare_species: the model's species buffers are missing");
     return DPA4C_ERR_INVALID_ARG;
   }
-  hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, st, mask_dev, 4);
-  hipLaunchKernelGGL(presence_kernel, dim3(grid_for(n)), dim3(256), 0, st, species, n, T1, mask_dev);
-  DPA4C_HIP_TRY(hipGetLastError());
-  DPA4C_HIP_TRY(hipMemcpyAsync(w.fold_host, mask_dev, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost,
-                               st));
-  DPA4C_HIP_TRY(hipStreamSynchronize(st));
-  uint32_t mask[4];
-  std::memcpy(mask, w.fold_host, sizeof(mask));
-  const bool same = m->fold_n >= 0 && std::memcmp(mask, m->fold_types_mask, sizeof(mask)) == 0;
+  const bool same = m->fold_n >= 0 && std::memcmp(mask, m->fold_types_mask, sizeof(m->fold_types_mask)) == 0;
   if (!same) {
     FoldTypes used{};
     int n_used = 0;
@@ -157,13 +128,13 @@ int prepare_species(dpa4c_model* m, const int32_t* species, int64_t n, uint32_t*
     const size_t per_pair = size_t(m->n_rows) * m->C0 * kFoldWords;
     const size_t need = 4 * per_pair * size_t(n_used) * size_t(n_used);
     if (!m->fold_allowed || n_used > kMaxFoldTypes || need > kMaxFoldBytes) {
-      std::memcpy(m->fold_types_mask, mask, sizeof(mask));
+      std::memcpy(m->fold_types_mask, mask, sizeof(m->fold_types_mask));
       m->fold_n = 0;   // the separable tables are used
     } else if (!may_alloc && need > w.ftab.bytes) {
       return 0;        // this call only: separable tables, the folded state kept
     } else {
       DPA4C_TRY(w.ftab.ensure(need));
-      std::memcpy(m->fold_types_mask, mask, sizeof(mask));
+      std::memcpy(m->fold_types_mask, mask, sizeof(m->fold_types_mask));
       int32_t* hmap = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(w.fold_host) + 64);
       std::memcpy(hmap, map.data(), 4 * size_t(T1));
       DPA4C_HIP_TRY(hipMemcpyAsync(w.fold_map.p, hmap, 4 * size_t(T1), hipMemcpyHostToDevice, st));

@@ -14,17 +14,20 @@ int launch_pair_cache(dpa4c_model* m, const float* wp_in, const float* wp_out);
 // neighbour lists (orthorhombic, periodic); all on ``st``
 // (CellGrid: model.h)
 int make_grid(const double cell[9], int64_t rq, CellGrid* g);
-// bin, count and scan (row_ptr); flags[3] receives the longest row (an
-// atomic maximum: the caller clears it)
+// bin, count and scan (row_ptr); ``clear_flags`` zeroes the eight flag words
+// first.  host3 (pinned) = (row_ptr[n], flags[0], the longest row), to be
+// read after the next synchronisation
 int build_skin_list(NeighborScratch& nb, const double* pos, int64_t n, const CellGrid& g,
-                    int64_t* row_ptr, int64_t* flags, hipStream_t st);
+                    int64_t* row_ptr, int64_t* flags, bool clear_flags, int64_t* host3,
+                    hipStream_t st);
 // the sorted rows of a counted list; ``max_row`` (the longest row, from the
 // count) above the LDS row size makes the fill use a global scratch for
 // those rows.  With ``jsamp`` (int32 [cap / 16 + 1]) the neighbour index at
 // every 16th position of the list also goes there for launch_skin_rev.
+// host_flag (a pinned word, or null) receives flags[0] after the fill.
 int fill_skin_list(NeighborScratch& nb, int64_t n, const CellGrid& g, const int64_t* row_ptr,
                    int32_t* nbr_j, int32_t* nbr_shift, int64_t cap, int64_t* flags,
-                   int64_t max_row, int32_t* jsamp, hipStream_t st);
+                   int64_t max_row, int32_t* jsamp, int64_t* host_flag, hipStream_t st);
 // per-axis min and max of the fixed-point positions Q(x) (finite ones):
 // host6 = [min x, y, z, max x, y, z]; dev6 is device scratch of 6 int64;
 // synchronises ``st``
@@ -33,22 +36,35 @@ int position_extent(const double* pos, int64_t n, int64_t* dev6, int64_t* host6,
 // nbr_j[s]), or -1;
 // jsamp = scratch of cap / 16 + 1 int32: nbr_j at every 16th position of the
 // list, computed here unless ``jsamp_ready`` (fill_skin_list wrote it);
-// with ``paired`` (device int64, zeroed by the caller) also the number of
-// reverse pairs found, so a symmetric list of E entries gives E / 2; with
-// ``order_of`` (the scratch of the build that made this list) the rows are
-// taken in the build's spatial bin order
+// with ``check`` also the species present, the list's size and the number of
+// reverse pairs found (a symmetric list of E entries gives E / 2), written to
+// pinned host memory; with ``order_of`` (the scratch of the build that made
+// this list) the rows are taken in the build's spatial bin order
 struct NeighborScratch;
+struct ListCheck {
+  const int32_t* species;
+  int n_types1;
+  // device scratch for partial pair counts and masks: 8 bytes for each block of
+  // the search (four atoms, at most 4,096 blocks), and from 32 KB on 4 KB more
+  // when n is above 8,192; the node state, which comes later, has the room
+  void* scratch;
+  uint32_t* host;   // pinned: uint32 mask[4], int64 row_ptr[n], int64 pairs
+};
 int launch_skin_rev(const int64_t* row_ptr, const int32_t* nbr_j, const int32_t* nbr_shift,
                     int64_t n, int64_t cap, int32_t* jsamp, bool jsamp_ready, int64_t* skin_rev,
-                    int64_t* paired, const NeighborScratch* order_of, hipStream_t st);
-// species analysis of a call: builds the pair-folded tables of the species
-// present when they changed (at most kMaxFoldTypes species) and the folded
-// index of every atom into ``fidx`` [n]; ``mask_dev`` is device scratch of 4
-// uint32.  Without ``may_alloc`` the tables are rebuilt only inside the
-// allocation they already have; a species set that needs more runs this call
-// on the separable tables and leaves the model's folded state as it was.
-// *use_fold tells the edge kernels which tables to read.  Synchronises ``st``.
-int prepare_species(dpa4c_model* m, const int32_t* species, int64_t n, uint32_t* mask_dev,
+                    const ListCheck* check, const NeighborScratch* order_of, hipStream_t st);
+// the bitmask of the species present to host[0..3] (pinned); ``masks`` =
+// device scratch of 4 KB
+int launch_presence(const int32_t* species, int64_t n, int n_types1, uint32_t* masks,
+                    uint32_t* host, hipStream_t st);
+// species analysis of a call from the bitmask of the species present: builds
+// the pair-folded tables when the set changed (at most kMaxFoldTypes species)
+// and the folded index of every atom into ``fidx`` [n].  Without
+// ``may_alloc`` the tables are rebuilt only inside the allocation they
+// already have; a species set that needs more runs this call on the separable
+// tables and leaves the model's folded state as it was.  *use_fold tells the
+// edge kernels which tables to read.
+int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* species, int64_t n,
                     int32_t* fidx, bool may_alloc, bool* use_fold, hipStream_t st);
 
 // model stages: the edge kernels read the pair-folded tables with the
@@ -184,6 +200,9 @@ int launch_nhc(const NhcArgs& a, hipStream_t st);
 int kinetic_partial_count(int64_t n);
 int launch_kinetic(const double* vel, const int32_t* species, const double* mass, int n_types1,
                    int64_t n, double* part_k, hipStream_t st);
+// vel *= *scale, then the partials of launch_kinetic
+int launch_scale_kinetic(double* vel, const int32_t* species, const double* mass, int n_types1,
+                         int64_t n, const double* scale, double* part_k, hipStream_t st);
 // vel *= *scale
 int launch_scale(double* vel, int64_t n, const double* scale, hipStream_t st);
 int launch_final_step(StepSums prev, hipStream_t st);
@@ -206,12 +225,10 @@ struct EvalBufs {
   float* node_grad;     // float [N][S+2]
   double* epart;        // double [partial_count(N) + 8]
   int32_t* fidx;        // int32 [N]
-  uint32_t* fold_mask;  // uint32 [4]
-  int64_t* check;       // int64 [2]: reverse pairs found
 };
 // bytes of each EvalBufs array for N atoms, a list of cap entries and a node
 // state of ns floats per atom, each rounded up to 256 (in struct order)
-constexpr int kEvalBufs = 10;
+constexpr int kEvalBufs = 8;
 void eval_buf_sizes(int64_t n, int64_t cap, int ns, size_t sizes[kEvalBufs]);
 // compute_energy_forces(_virial) on the given buffers (null: the model's
 // workspace, grown as needed); ``bufs`` given means no allocation, no timing
@@ -224,8 +241,11 @@ int energy_forces_core(const dpa4c_model* m, const double* pos, const int32_t* s
 // per-device set-up of the no-allocation entry point (noalloc.hip); called
 // with ``device`` current by dpa4c_model_create
 int noalloc_setup(int device);
-// flags[idx] = value
-int launch_set_flag(int64_t* flags, int idx, int64_t value, hipStream_t st);
+// the start of a batch of steps: saved = [pos, vel, forces] (and ``words``, at
+// most 256, of the chain state), flags[4] = INT64_MAX, flags[5] = 0
+int launch_batch_start(const double* pos, const double* vel, const double* forces, int64_t n,
+                       double* saved, const double* chain, double* chain_saved, int words,
+                       int64_t* flags, hipStream_t st);
 int partial_count(int64_t n);
 
 }  // namespace dpa4c

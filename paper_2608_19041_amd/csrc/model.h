@@ -51,7 +51,6 @@ struct NeighborScratch {
   DevBuf cell_of;    // int32 [N]
   DevBuf cell_cnt;   // int32 [ncell]
   DevBuf cell_start; // int32 [ncell+1]
-  DevBuf cell_fill;  // int32 [ncell]
   DevBuf cell_rec;   // 32-byte records [N] in bin order: fixed-point position and atom index
   DevBuf long_keys;  // int64 [cap] keys of rows longer than the fill kernel's LDS row
   DevBuf counts;     // int64 [N]
@@ -94,13 +93,13 @@ struct Workspace {
   DevBuf backup;        // double [3][N][3]: positions, velocities, forces at a batch start
   DevBuf inv_mass;      // double [T+1]: 1 / (m * 103.6427)  (A/fs^2 per eV/A)
   DevBuf mass;          // double [T+1]
+  std::vector<double> host_mass;   // the masses that inv_mass and mass were formed from
   int64_t* host_flags = nullptr;          // pinned [8]
   // pair-folded tables of the species present (fold.hip)
   DevBuf ftab;          // float [fold_n^2][n_rows][C0 * kFoldWords]
   DevBuf fold_map;      // int32 [T+1]: type -> folded index, or -1
-  DevBuf fold_mask;     // uint32 [4]: species present in the last call
+  DevBuf fold_mask;     // uint32 [256][4]: partial masks of the species present
   DevBuf fidx;          // int32 [N]: folded index of every atom
-  DevBuf check;         // int64 [2]: reverse pairs found in a caller's list
   // pinned host words, allocated with the model: [0, 16) the species
   // presence mask, [16, 32) row_ptr[N] and the reverse pairs of a caller's
   // list, [64, 64 + 4 (T+1)) the type map of the folded tables

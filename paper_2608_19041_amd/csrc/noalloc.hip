@@ -11,8 +11,7 @@
 // kernels.
 //
 // Every call on a device shares that device's array and leaves the last
-// call's contents in it; nothing in it needs to start at zero (the only
-// counter is cleared by a fill kernel at the start of each call).  Calls
+// call's contents in it; nothing in it needs to start at zero.  Calls
 // that overlap on one device race on the array.
 #include <hip/hip_runtime.h>
 
@@ -106,8 +105,6 @@ extern "C" int compute_energy_forces_noalloc(const dpa4c_model* m, const double*
   b.node_grad = reinterpret_cast<float*>(take(5));
   b.epart = reinterpret_cast<double*>(take(6));
   b.fidx = reinterpret_cast<int32_t*>(take(7));
-  b.fold_mask = reinterpret_cast<uint32_t*>(take(8));
-  b.check = reinterpret_cast<int64_t*>(take(9));
   return energy_forces_core(m, pos, species, N, cell, pbc, r_c, row_ptr, nbr_j, nbr_shift, n_pairs,
                             e_atom, forces, e_total, nullptr, nullptr, &b, stream);
 }
