@@ -208,11 +208,12 @@ int compute_energy_forces_virial(const dpa4c_model* model, const double* pos,
  * shares that device's array, so calls that overlap on one device (other
  * streams, other threads, other models) race; calls on one stream do not.
  *
- * The pair-folded radial tables are built only inside the allocation a
- * previous call on the model left: with a species set whose tables do not
- * fit it, this call reads the separable tables (the same model, results
- * equal to float32 rounding).  One compute_energy_forces call with the same
- * species beforehand gives this entry point the folded tables.  The model's
+ * The pair-folded radial tables are built only inside the allocation the
+ * model holds: two species from its creation, more once another call needed
+ * them.  With a species set whose tables do not fit it, this call reads the
+ * separable tables (the same model, results equal to float32 rounding).  One
+ * compute_energy_forces call with the same species beforehand gives this
+ * entry point the folded tables.  The model's
  * own workspace, and so the list that verlet_step carries between calls, is
  * untouched (but for the rows its readout and MLP pass between each other,
  * which no call leaves anything in).  Synchronises ``stream`` once (the species present).
