@@ -85,7 +85,7 @@ int launch_chain(const dpa4c_model* m, int64_t n, const int32_t* species, float*
                  const float2* meta, double* e_atom, hipStream_t st);
 int launch_readout_vjp(const dpa4c_model* m, int64_t n, const float* node, const float* desc,
                        float* node_grad, hipStream_t st);
-// the readout's per-lane tables (readout_row.h; none at degree four)
+// the readout's per-lane tables (readout_row.h)
 size_t row_table_floats(const dpa4c_model* m);
 void build_row_table(const dpa4c_model* m, const float* W1, const float* W2, const float* A1,
                      const float* A2, const float* cpl, float* out);

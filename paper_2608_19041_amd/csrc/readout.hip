@@ -1,13 +1,16 @@
-// The invariant readout (readout.h) as kernels of its own: node state in,
+// The invariant readout (readout_row.h) as kernels of its own: node state in,
 // calibrated descriptor out as the operand planes of the MLP (mlp_chain.hip),
-// and dE/dD in, dE/d(node state) out.  Half a wavefront serves an atom.  Kept
-// apart from the MLP, whose workgroups hold one CU each, the readouts run
-// with as many atoms in flight as their own LDS records allow.
+// and dE/dD in, dE/d(node state) out.  Kept apart from the MLP, whose
+// workgroups hold one CU each, the readouts run with as many atoms in flight
+// as their descriptor rows in LDS allow.  Per 65,536 atoms at full width the
+// readout takes 76 us and its VJP 82 us (degree four: 98 and 120 us), against
+// 40 and 52 us for the bytes they move at the rate of a large copy; what bounds
+// them is the chain of LDS reads and rotations of one atom, with three and two
+// waves on a SIMD to hide it.
 #include <hip/hip_runtime.h>
 
 #include "../../include/dpa4c.h"
 #include "launch.h"
-#include "readout.h"
 #include "readout_row.h"
 
 namespace dpa4c {
@@ -15,127 +18,17 @@ namespace dpa4c {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kAtoms = kThreads / kHalf;   // atoms of a workgroup
-
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
-
-// half-wave maximum (butterfly)
-__device__ inline float half_max(float v) {
-  for (int off = 1; off < kHalf; off <<= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
-}
-
-// desc: one row of KP floats per atom, written as KP halves hi, then KP
-// halves lo, of D 2^e (split as mlp_chain.hip states); meta = (2^-e, a bound
-// of |h1| of the atom's first layer).
-template <class P, int KP>
-__global__ void __launch_bounds__(kThreads) readout_kernel(ModelDev md, MlpScales sc, int64_t n,
-                                                           const int32_t* __restrict__ species,
-                                                           const float* __restrict__ node,
-                                                           float* __restrict__ desc,
-                                                           float2* __restrict__ meta,
-                                                           float* __restrict__ desc_out) {
-  __shared__ ReadoutFwdLds<P> rl_all[kAtoms];
-  __shared__ __align__(16) float row_all[kAtoms][P::DSTR];
-  __shared__ ReadoutParams<P> rp;
-  const int hl = threadIdx.x & (kHalf - 1), ra = threadIdx.x / kHalf;
-  DPA4C_LDS ReadoutFwdLds<P>& rl = *(DPA4C_LDS ReadoutFwdLds<P>*)(&rl_all[ra]);
-  const DPA4C_LDS ReadoutParams<P>& rpl = *(DPA4C_LDS ReadoutParams<P>*)(&rp);
-  DPA4C_LDS float* row = (DPA4C_LDS float*)(&row_all[ra][0]);
-  stage_readout_params<P>(rp, md, threadIdx.x, kThreads);
-  __syncthreads();
-  for (int64_t g = blockIdx.x; g * kAtoms < n; g += gridDim.x) {
-    const int64_t i = g * kAtoms + ra;
-    const bool ok = i < n;
-    if (ok) {
-      const float* ny = node + size_t(i) * P::NS;
-      for (int t = hl; t < P::NS; t += kHalf) rl.y[t] = ny[t];
-    } else {
-      for (int t = hl; t < P::NS; t += kHalf) rl.y[t] = 0.0f;
-    }
-    const float* x0 =
-        md.type_embed + size_t(ok ? clamp_type(species[i], md.n_types1) : 0) * P::C0;
-    wave_sync();
-    readout_forward<P>(rl, rpl, x0, row);
-    // the row's norms, its scale and the bound of the first layer
-    float big = 0.0f, sq = 0.0f;
-    for (int t = hl; t < P::DOUT; t += kHalf) {
-      big = fmaxf(big, fabsf(row[t]));
-      sq = fmaf(row[t], row[t], sq);
-    }
-    big = half_max(big);
-    sq = half_sum(sq);
-    const int e = operand_exponent(big);
-    const float up = __builtin_amdgcn_ldexpf(1.0f, e);
-    if (ok) {
-      v2h* hi = reinterpret_cast<v2h*>(desc + size_t(i) * KP);
-      v2h* lo = hi + KP / 2;
-      for (int t = 2 * hl; t < KP; t += 2 * kHalf) {
-        v2h a, b;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const float x = t + c < P::DSTR ? row[t + c] * up : 0.0f;
-          a[c] = static_cast<_Float16>(x);
-          b[c] = static_cast<_Float16>(x - static_cast<float>(a[c]));
-        }
-        hi[t / 2] = a;
-        lo[t / 2] = b;
-      }
-      if (hl == 0)
-        meta[i] = make_float2(__builtin_amdgcn_ldexpf(1.0f, -e),
-                              fminf(big * sc.d_max, sqrtf(sq) * sc.d_norm) * 1.001f + sc.d_add);
-      if (desc_out)
-        for (int t = hl; t < P::DOUT; t += kHalf) desc_out[size_t(i) * P::DOUT + t] = row[t];
-    }
-    wave_sync();
-  }
-}
-
-template <class P, int KP>
-__global__ void __launch_bounds__(kThreads) readout_vjp_kernel(ModelDev md, int64_t n,
-                                                               const float* __restrict__ node,
-                                                               const float* __restrict__ desc,
-                                                               float* __restrict__ node_grad) {
-  __shared__ ReadoutLds<P> rl_all[kAtoms];
-  __shared__ __align__(16) float row_all[kAtoms][P::DSTR];
-  __shared__ ReadoutParams<P> rp;
-  const int hl = threadIdx.x & (kHalf - 1), ra = threadIdx.x / kHalf;
-  DPA4C_LDS ReadoutLds<P>& rl = *(DPA4C_LDS ReadoutLds<P>*)(&rl_all[ra]);
-  const DPA4C_LDS ReadoutParams<P>& rpl = *(DPA4C_LDS ReadoutParams<P>*)(&rp);
-  DPA4C_LDS float* row = (DPA4C_LDS float*)(&row_all[ra][0]);
-  stage_readout_params<P>(rp, md, threadIdx.x, kThreads);
-  __syncthreads();
-  for (int64_t g = blockIdx.x; g * kAtoms < n; g += gridDim.x) {
-    const int64_t i = g * kAtoms + ra;
-    if (i < n) {
-      const float* ny = node + size_t(i) * P::NS;
-      const float* nd = desc + size_t(i) * KP;
-      for (int t = hl; t < P::NS; t += kHalf) rl.y[t] = ny[t];
-      // dE/dD~ = dE/dD / sigma, Eq. (calibration)
-      for (int t = hl; t < P::DSTR; t += kHalf) row[t] = nd[t] * rpl.inv_sigma[t];
-    } else {
-      for (int t = hl; t < P::NS; t += kHalf) rl.y[t] = 0.0f;
-      for (int t = hl; t < P::DSTR; t += kHalf) row[t] = 0.0f;
-    }
-    wave_sync();
-    float M0, M1;
-    readout_intermediates<P>(rl, rpl, &M0, &M1);
-    readout_backward<P>(rl, rpl, row);
-    if (i < n) {
-      float* gout = node_grad + size_t(i) * P::NS;
-      for (int t = hl; t < P::NS; t += kHalf) gout[t] = rl.gy[t];
-    }
-    wave_sync();
-  }
-}
-
-constexpr int kRowAtoms = kThreads / kRow;   // atoms of a workgroup of the row kernels
+constexpr int kRowAtoms = kThreads / kRow;   // atoms of a workgroup
+// workgroups of a launch: each stages its tables once and strides over the
+// atoms; about what runs at once
+constexpr int64_t kRowGrid = 1024;
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 // the lane's features of one atom
 template <class P>
 __device__ __forceinline__ void load_features(const float* y, const RowLane<P>& k, float (&y1)[3],
-                                              float (&y2)[5], float (&y3)[P::L >= 3 ? 7 : 1]) {
+                                              float (&y2)[5], float (&y3)[P::L >= 3 ? 7 : 1],
+                                              float (&y4)[P::L >= 4 ? 9 : 1]) {
 #pragma unroll
   for (int m = 0; m < 3; ++m) y1[m] = y[P::Y1 + m * P::C1 + k.c];
 #pragma unroll
@@ -144,10 +37,14 @@ __device__ __forceinline__ void load_features(const float* y, const RowLane<P>& 
 #pragma unroll
     for (int m = 0; m < 7; ++m) y3[m] = y[P::Y3 + m];
   }
+  if constexpr (P::L >= 4) {
+#pragma unroll
+    for (int m = 0; m < 9; ++m) y4[m] = y[P::Y4 + m];
+  }
 }
 
 template <class P, int KP>
-__global__ void __launch_bounds__(kThreads, 3)
+__global__ void __launch_bounds__(kThreads, P::L >= 4 ? 2 : 3)
     row_readout_kernel(ModelDev md, MlpScales sc, int64_t n, const int32_t* __restrict__ species,
                        const float* __restrict__ node, float* __restrict__ desc,
                        float2* __restrict__ meta, float* __restrict__ desc_out) {
@@ -173,8 +70,8 @@ __global__ void __launch_bounds__(kThreads, 3)
     const bool ok = want < n;
     const float* y = node + size_t(i) * P::NS;
     const float* x0 = md.type_embed + size_t(clamp_type(species[i], md.n_types1)) * P::C0;
-    float y1[3], y2[5], y3[P::L >= 3 ? 7 : 1], y0[kY0], e0[kY0];
-    load_features<P>(y, k, y1, y2, y3);
+    float y1[3], y2[5], y3[P::L >= 3 ? 7 : 1], y4[P::L >= 4 ? 9 : 1], y0[kY0], e0[kY0];
+    load_features<P>(y, k, y1, y2, y3, y4);
 #pragma unroll
     for (int q = 0; q < kY0; ++q) {
       const int t = k.l + q * kRow;
@@ -182,7 +79,7 @@ __global__ void __launch_bounds__(kThreads, 3)
       e0[q] = t < P::C0 ? x0[t] : 0.0f;
     }
     RowFwd<P> f;
-    row_forward<P>(f, k, tab, y[0], y[1], y1, y2, y3);
+    row_forward<P>(f, k, tab, y[0], y[1], y1, y2, y3, y4);
     row_descriptor<P>(f, k, at, row);
 #pragma unroll
     for (int q = 0; q < kY0; ++q) {
@@ -274,8 +171,8 @@ __global__ void __launch_bounds__(kThreads, 2)
     const bool ok = want < n;
     const float* y = node + size_t(i) * P::NS;
     const float* nd = desc + size_t(i) * KP;
-    float y1[3], y2[5], y3[P::L >= 3 ? 7 : 1], y0[kY0];
-    load_features<P>(y, k, y1, y2, y3);
+    float y1[3], y2[5], y3[P::L >= 3 ? 7 : 1], y4[P::L >= 4 ? 9 : 1], y0[kY0];
+    load_features<P>(y, k, y1, y2, y3, y4);
     const float s0 = y[0], s1 = y[1];
 #pragma unroll
     for (int q = 0; q < kY0; ++q) {
@@ -291,10 +188,12 @@ __global__ void __launch_bounds__(kThreads, 2)
                                                *reinterpret_cast<const row_f4*>(md.inv_sigma + t0);
     }
     RowFwd<P> f;
-    row_forward<P>(f, k, tab, s0, s1, y1, y2, y3);
+    row_forward<P>(f, k, tab, s0, s1, y1, y2, y3, y4);
     wave_sync();
-    float xb1[3], xb2[5], xb3;
-    row_vjp<P>(f, k, b, tab, row, xb1, xb2, xb3);
+    float xb1[3], xb2[5], xb3, xb4;
+    row_vjp<P>(f, k, b, tab, row, xb1, xb2, xb3, xb4);
+    formed(xb3);
+    formed(xb4);
     // the normalisation X = Y / M: sums of Xbar Y per normaliser
     float part0 = 0.0f, part1 = 0.0f;
     float* go = node_grad + size_t(i) * P::NS;
@@ -323,6 +222,10 @@ __global__ void __launch_bounds__(kThreads, 2)
       part1 = fmaf(xb3, f.z3l * f.m1, part1);
       if (ok && k.l < 7) go[P::Y3 + k.l] = xb3 * f.i1;
     }
+    if constexpr (P::L >= 4) {
+      part1 = fmaf(xb4, f.z4l * f.m1, part1);
+      if (ok && k.l < 9) go[P::Y4 + k.l] = xb4 * f.i1;
+    }
     part0 = row_sum(part0);
     part1 = row_sum(part1);
     if (ok && k.l == 0) {
@@ -339,7 +242,7 @@ size_t row_table_floats(const dpa4c_model* m) {
   size_t k = 0;
   with_profile(m->C0, m->L, m->R, m->F, [&](auto p, auto) {
     using P = decltype(p);
-    if constexpr (P::L <= 3) k = RowTable<P>::floats(RowTable<P>::kAll);
+    k = RowTable<P>::floats(RowTable<P>::kAll);
     return 0;
   });
   return k;
@@ -349,27 +252,19 @@ void build_row_table(const dpa4c_model* m, const float* W1, const float* W2, con
                      const float* A2, const float* cpl, float* out) {
   with_profile(m->C0, m->L, m->R, m->F, [&](auto p, auto) {
     using P = decltype(p);
-    if constexpr (P::L <= 3) RowTable<P>::build(W1, W2, A1, A2, cpl, out);
+    RowTable<P>::build(W1, W2, A1, A2, cpl, out);
     return 0;
   });
 }
 
 int launch_readout(const dpa4c_model* m, int64_t n, const int32_t* species, const float* node,
                    float* desc, float2* meta, float* desc_out, hipStream_t st) {
+  const int64_t groups = (n + kRowAtoms - 1) / kRowAtoms;
+  const unsigned grid = static_cast<unsigned>(groups < kRowGrid ? groups : kRowGrid);
   return with_profile(m->C0, m->L, m->R, m->F, [&](auto p, auto) {
     using P = decltype(p);
-    constexpr int KP = mlp_width(P::DOUT);
-    if constexpr (P::L <= 3) {
-      const int64_t groups = (n + kRowAtoms - 1) / kRowAtoms;
-      const unsigned grid = static_cast<unsigned>(groups < 1024 ? groups : 1024);
-      hipLaunchKernelGGL((row_readout_kernel<P, KP>), dim3(grid), dim3(kThreads), 0, st, m->dev(),
-                         m->scales, n, species, node, desc, meta, desc_out);
-    } else {
-      const int64_t groups = (n + kAtoms - 1) / kAtoms;
-      const unsigned grid = static_cast<unsigned>(groups < 4096 ? groups : 4096);
-      hipLaunchKernelGGL((readout_kernel<P, KP>), dim3(grid), dim3(kThreads), 0, st, m->dev(),
-                         m->scales, n, species, node, desc, meta, desc_out);
-    }
+    hipLaunchKernelGGL((row_readout_kernel<P, mlp_width(P::DOUT)>), dim3(grid), dim3(kThreads), 0,
+                       st, m->dev(), m->scales, n, species, node, desc, meta, desc_out);
     DPA4C_HIP_TRY(hipGetLastError());
     return 0;
   });
@@ -377,20 +272,12 @@ int launch_readout(const dpa4c_model* m, int64_t n, const int32_t* species, cons
 
 int launch_readout_vjp(const dpa4c_model* m, int64_t n, const float* node, const float* desc,
                        float* node_grad, hipStream_t st) {
+  const int64_t groups = (n + kRowAtoms - 1) / kRowAtoms;
+  const unsigned grid = static_cast<unsigned>(groups < kRowGrid ? groups : kRowGrid);
   return with_profile(m->C0, m->L, m->R, m->F, [&](auto p, auto) {
     using P = decltype(p);
-    constexpr int KP = mlp_width(P::DOUT);
-    if constexpr (P::L <= 3) {
-      const int64_t groups = (n + kRowAtoms - 1) / kRowAtoms;
-      const unsigned grid = static_cast<unsigned>(groups < 1024 ? groups : 1024);
-      hipLaunchKernelGGL((row_vjp_kernel<P, KP>), dim3(grid), dim3(kThreads), 0, st, m->dev(), n,
-                         node, desc, node_grad);
-    } else {
-      const int64_t groups = (n + kAtoms - 1) / kAtoms;
-      const unsigned grid = static_cast<unsigned>(groups < 4096 ? groups : 4096);
-      hipLaunchKernelGGL((readout_vjp_kernel<P, KP>), dim3(grid), dim3(kThreads), 0, st, m->dev(),
-                         n, node, desc, node_grad);
-    }
+    hipLaunchKernelGGL((row_vjp_kernel<P, mlp_width(P::DOUT)>), dim3(grid), dim3(kThreads), 0, st,
+                       m->dev(), n, node, desc, node_grad);
     DPA4C_HIP_TRY(hipGetLastError());
     return 0;
   });

@@ -1,4 +1,4 @@
-// The invariant readout (Eqs. (alignment) .. (descriptor)) and its
+// The invariant readout (Eqs. (alignment) .. (calibration)) and its
 // vector-Jacobian product with sixteen lanes, one DPP row, per atom and the
 // features in registers: lane l holds channel c = l mod C1 of degree one,
 // e = l mod C2 of degree two and probe kappa = e of the half (l / K1) mod 2,
@@ -71,6 +71,11 @@ __device__ __forceinline__ float row_max(float x) {
   return fmaxf(x, ror<8>(x));
 }
 
+// x formed here: without it the compiler moves the last multiply-adds of a
+// sum past later conditional stores, or its first rotations far ahead, and
+// keeps every rotated operand in a register in between
+__device__ __forceinline__ void formed(float& x) { asm volatile("" : "+v"(x)); }
+
 constexpr float kRowSqrt2 = 1.4142135623730951f;
 constexpr float kRowInvSqrt2 = 0.7071067811865476f;
 constexpr float kRowInvSqrt6 = 0.4082482904638631f;
@@ -103,18 +108,30 @@ struct RowLane {
 //   kW1:  W1[c_k][c]      kW2:  W2[e_k][e]     kA1:  A1[c_k][e]   kA2: A2[e_k][eta]
 //   kW1T: W1[c][c_k]      kW2T: W2[e][e_k]     kA1T: A1[c][e_k]
 //   kA2P: A2[e][eta], A2[e][1 - eta]
-//   kCT: C123[o = l][.] (7, l < 15)   kCW: C233[m1][m2 = l][.] (35, l < 7)
-//   kCZ: C123[.][m = l] (15, l < 7); zero elsewhere
+//   kCT: C123[o = l][.] (7, l < 15)   kCW: C233[m1][m2 = l][.] (5 rows of 7, l < 7)
+//   kCZ: C123[.][m = l] (15, l < 7)
+// and at degree four
+//   k134: C134[m1][m3 = l][.] (3 rows of 9, l < 7)    k224: C224[m1][m2 = l][.] (5 of 9, l < 5)
+//   k244: C244[m1][a = l][.] (5 of 9, l < 9)          k334: C334[a = l][b][.] (7 of 9, l < 7)
+//   k444: C444[a = l][b][.] (9 of 9, l < 9)           k134Z: C134[m1][.][m4 = l] (3 of 7, l < 9)
+//   k224Z: C224[m1][.][m4 = l] (5 of 5, l < 9)        k334Z: C334[a][.][m4 = l] (7 of 7, l < 9)
+// zero elsewhere; rows begin a piece of their own
 template <class P>
 struct RowTable {
   static constexpr int C1 = P::C1, C2 = P::C2, K1 = P::K1;
   static constexpr int kW1 = 0, kW2 = kW1 + C1 / 4, kA1 = kW2 + C2 / 4;
   static constexpr int kA2 = kA1 + (P::kHasA1 ? C1 / 4 : 0);
   static constexpr int kCT = kA2 + C2 / 4, kCW = kCT + (P::L >= 3 ? 2 : 0);
-  static constexpr int kFwd = kCW + (P::L >= 3 ? 9 : 0);   // pieces of the forward pass
+  static constexpr bool k4 = P::L >= 4;
+  static constexpr int k134 = kCW + (P::L >= 3 ? 10 : 0), k224 = k134 + (k4 ? 9 : 0);
+  static constexpr int k244 = k224 + (k4 ? 15 : 0), k334 = k244 + (k4 ? 15 : 0);
+  static constexpr int k444 = k334 + (k4 ? 21 : 0);
+  static constexpr int kFwd = k444 + (k4 ? 27 : 0);   // pieces of the forward pass
   static constexpr int kW1T = kFwd, kW2T = kW1T + C1 / 4, kA1T = kW2T + C2 / 4;
   static constexpr int kA2P = kA1T + (P::kHasA1 ? K1 / 4 : 0), kCZ = kA2P + 1;
-  static constexpr int kAll = kCZ + (P::L >= 3 ? 4 : 0);
+  static constexpr int k134Z = kCZ + (P::L >= 3 ? 4 : 0), k224Z = k134Z + (k4 ? 6 : 0);
+  static constexpr int k334Z = k224Z + (k4 ? 10 : 0);
+  static constexpr int kAll = k334Z + (k4 ? 14 : 0);
   static constexpr size_t floats(int pieces) { return size_t(pieces) * kRow * 4; }
 
   // the table, from the parameters on the host (cpl null below degree three)
@@ -144,8 +161,23 @@ struct RowTable {
       if (P::L >= 3) {
         for (int q = 0; q < 7 && l < 15; ++q) put(kCT, l, q, cpl[l * 7 + q]);
         for (int q = 0; q < 35 && l < 7; ++q)
-          put(kCW, l, q, cpl[kC123 + (q / 7 * 7 + l) * 7 + q % 7]);
+          put(kCW + q / 7 * 2, l, q % 7, cpl[kC123 + (q / 7 * 7 + l) * 7 + q % 7]);
         for (int q = 0; q < 15 && l < 7; ++q) put(kCZ, l, q, cpl[q * 7 + l]);
+      }
+      if (P::L >= 4) {
+        const float *c134 = cpl + kO134, *c224 = cpl + kO224, *c244 = cpl + kO244,
+                    *c334 = cpl + kO334, *c444 = cpl + kO444;
+        for (int q = 0; q < 27 && l < 7; ++q)
+          put(k134 + q / 9 * 3, l, q % 9, c134[(q / 9 * 7 + l) * 9 + q % 9]);
+        for (int q = 0; q < 45 && l < 5; ++q)
+          put(k224 + q / 9 * 3, l, q % 9, c224[(q / 9 * 5 + l) * 9 + q % 9]);
+        for (int q = 0; q < 45 && l < 9; ++q)
+          put(k244 + q / 9 * 3, l, q % 9, c244[(q / 9 * 9 + l) * 9 + q % 9]);
+        for (int q = 0; q < 63 && l < 7; ++q) put(k334 + q / 9 * 3, l, q % 9, c334[l * 63 + q]);
+        for (int q = 0; q < 81 && l < 9; ++q) put(k444 + q / 9 * 3, l, q % 9, c444[l * 81 + q]);
+        for (int q = 0; q < 21 && l < 9; ++q) put(k134Z + q / 7 * 2, l, q % 7, c134[q * 9 + l]);
+        for (int q = 0; q < 25 && l < 9; ++q) put(k224Z + q / 5 * 2, l, q % 5, c224[q * 9 + l]);
+        for (int q = 0; q < 49 && l < 9; ++q) put(k334Z + q / 7 * 2, l, q % 7, c334[q * 9 + l]);
       }
     }
   }
@@ -159,9 +191,12 @@ __device__ __forceinline__ void stage_table(float* dst, const float* src, int pi
     reinterpret_cast<row_f4*>(dst)[t] = reinterpret_cast<const row_f4*>(src)[t];
 }
 
-// N floats of a lane from piece ``first`` of the table on
+// N floats of a lane from piece ``first`` of the table on.  Not before what
+// comes ahead of it in the program: hoisted together the tables would fill the
+// registers.
 template <int N>
 __device__ __forceinline__ void table_read(const float* tab, int first, int l, float (&out)[N]) {
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int q = 0; q < (N + 3) / 4; ++q) {
     const row_f4 v = *reinterpret_cast<const row_f4*>(tab + ((first + q) * kRow + l) * 4);
@@ -181,6 +216,8 @@ __device__ __forceinline__ void row_product(float (&acc)[M], const float (&x)[M]
 #pragma unroll
     for (int m = 0; m < M; ++m) acc[m] = fmaf(ror<decltype(j)::value>(x[m]), w[j], acc[m]);
   });
+#pragma unroll
+  for (int m = 0; m < M; ++m) formed(acc[m]);
 }
 
 // the forward intermediates of an atom
@@ -195,6 +232,13 @@ struct RowFwd {
   // T123[o = l], W233[m1][m2 = l], V233[m1] and U123[m1][eta]
   float t123, w233[P::L >= 3 ? 5 : 1], v233[P::L >= 3 ? 5 : 1], u123[P::L >= 3 ? 3 : 1];
   float z3l;                           // degree-three component l (l < 7)
+  // degree four (one channel, Z4 = X~4): all components and component l
+  // (l < 9); by lane R134[m1] = C134[m1][l] : Z4, R244[m1] = C244[m1][l] : Z4,
+  // R334 = C334[l] : Z3 Z4 and R444 = C444[l] : Z4 Z4; in every lane T134[m1],
+  // T244[m1] and V224[m1] = T224[m1] : Z2 of this half's eta
+  static constexpr int n4 = P::L >= 4 ? 1 : 0;
+  float xt4[n4 ? 9 : 1], z4l, r134[n4 ? 3 : 1], r244[n4 ? 5 : 1], r334, r444;
+  float t134[n4 ? 3 : 1], t244[n4 ? 5 : 1], v224[n4 ? 5 : 1];
 };
 
 // y: the features of the lane (degree one, degree two, all of degree three)
@@ -202,7 +246,8 @@ template <class P>
 __device__ __forceinline__ void row_forward(RowFwd<P>& f, const RowLane<P>& k, const float* tab,
                                             float s0, float s1, const float (&y1)[3],
                                             const float (&y2)[5],
-                                            const float (&y3)[P::L >= 3 ? 7 : 1]) {
+                                            const float (&y3)[P::L >= 3 ? 7 : 1],
+                                            const float (&y4)[P::L >= 4 ? 9 : 1]) {
   f.m0 = sqrtf(0.25f + s0);
   f.m1 = sqrtf(0.25f + s1);
   f.i0 = 1.0f / f.m0;
@@ -241,9 +286,8 @@ __device__ __forceinline__ void row_forward(RowFwd<P>& f, const RowLane<P>& k, c
   f.qv[1] = f.q[3] * f.z1[0] + f.q[1] * f.z1[1] + f.q[4] * f.z1[2];
   f.qv[2] = f.q[5] * f.z1[0] + f.q[4] * f.z1[1] + f.q[2] * f.z1[2];
   if constexpr (P::L >= 3) {
-    float ct[7], cw[35];
+    float ct[7];
     table_read(tab, T::kCT, k.l, ct);
-    table_read(tab, T::kCW, k.l, cw);
     f.t123 = 0.0f;
     f.z3l = 0.0f;
 #pragma unroll
@@ -253,11 +297,13 @@ __device__ __forceinline__ void row_forward(RowFwd<P>& f, const RowLane<P>& k, c
     }
 #pragma unroll
     for (int m1 = 0; m1 < 5; ++m1) {
-      float acc = 0.0f;
+      float acc = 0.0f, cw[7];
+      table_read(tab, T::kCW + 2 * m1, k.l, cw);
 #pragma unroll
-      for (int m3 = 0; m3 < 7; ++m3) acc = fmaf(cw[7 * m1 + m3], f.xt3[m3], acc);
+      for (int m3 = 0; m3 < 7; ++m3) acc = fmaf(cw[m3], f.xt3[m3], acc);
       f.w233[m1] = acc;
       f.v233[m1] = row_sum(acc * f.z3l);
+      formed(f.v233[m1]);
     }
     unrolled<3>([&](auto m1) {
       float acc = 0.0f;
@@ -265,7 +311,51 @@ __device__ __forceinline__ void row_forward(RowFwd<P>& f, const RowLane<P>& k, c
         acc = fmaf(bcast<decltype(m1)::value * 5 + decltype(m2)::value>(f.t123), f.z2[m2], acc);
       });
       f.u123[m1] = acc;
+      formed(f.u123[m1]);
     });
+  }
+  if constexpr (P::L >= 4) {
+    f.z4l = 0.0f;
+#pragma unroll
+    for (int m = 0; m < 9; ++m) {
+      f.xt4[m] = y4[m] * f.i1;
+      f.z4l = k.l == m ? f.xt4[m] : f.z4l;
+    }
+    // one row of nine couplings against Z4
+    auto dot4 = [&](int piece) {
+      float c[9], acc = 0.0f;
+      table_read(tab, piece, k.l, c);
+#pragma unroll
+      for (int e = 0; e < 9; ++e) acc = fmaf(c[e], f.xt4[e], acc);
+      return acc;
+    };
+#pragma unroll
+    for (int m1 = 0; m1 < 3; ++m1) {
+      f.r134[m1] = dot4(T::k134 + 3 * m1);
+      f.t134[m1] = row_sum(f.r134[m1] * f.z3l);
+      formed(f.t134[m1]);
+    }
+#pragma unroll
+    for (int m1 = 0; m1 < 5; ++m1) {
+      const float t = dot4(T::k224 + 3 * m1);   // T224[m1][m2 = l]
+      float acc = 0.0f;
+      unrolled<5>([&](auto m2) { acc = fmaf(bcast<decltype(m2)::value>(t), f.z2[m2], acc); });
+      f.v224[m1] = acc;
+      formed(f.v224[m1]);
+    }
+#pragma unroll
+    for (int m1 = 0; m1 < 5; ++m1) {
+      f.r244[m1] = dot4(T::k244 + 3 * m1);
+      f.t244[m1] = row_sum(f.r244[m1] * f.z4l);
+      formed(f.t244[m1]);
+    }
+    f.r334 = f.r444 = 0.0f;
+#pragma unroll
+    for (int b = 0; b < 7; ++b) f.r334 = fmaf(dot4(T::k334 + 3 * b), f.xt3[b], f.r334);
+#pragma unroll
+    for (int b = 0; b < 9; ++b) f.r444 = fmaf(dot4(T::k444 + 3 * b), f.xt4[b], f.r444);
+    formed(f.r334);
+    formed(f.r444);
   }
 }
 
@@ -354,6 +444,27 @@ __device__ __forceinline__ void row_descriptor(const RowFwd<P>& f, const RowLane
     for (int m = 0; m < 5; ++m) v = fmaf(f.z2[m], f.v233[m], v);
     d[P::o233 + k.eta] = v;
   }
+  if constexpr (P::L >= 4) {
+    float g = 0.0f, j134 = 0.0f, own = 0.0f, off = 0.0f, j244 = 0.0f;
+#pragma unroll
+    for (int m = 0; m < 9; ++m) g = fmaf(f.xt4[m], f.xt4[m], g);
+    d[P::oG4] = g;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) j134 = fmaf(f.z1[m], f.t134[m], j134);
+    d[P::o134 + k.e] = j134;
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+      own = fmaf(f.z2[m], f.v224[m], own);
+      off = fmaf(f.z2[m], ror<P::K1>(f.v224[m]), off);
+      j244 = fmaf(f.z2[m], f.t244[m], j244);
+    }
+    // (k1, k2) = (0, 0), (0, 1), (1, 1); the mixed one from the lanes of eta 0
+    d[P::o224 + 2 * k.eta] = own;
+    if (k.eta == 0) d[P::o224 + 1] = off * kRowSqrt2;
+    d[P::o244 + k.eta] = j244;
+    d[P::o334] = row_sum(f.r334 * f.z3l);
+    d[P::o444] = row_sum(f.r444 * f.z4l);
+  }
   d[P::oM0] = f.m0;
   d[P::oM1] = f.m1;
 }
@@ -380,7 +491,8 @@ struct RowVjpPlaces {
 template <class P>
 __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
                                         const RowVjpPlaces<P>& b, const float* tab, const float* d,
-                                        float (&xb1)[3], float (&xb2)[5], float& xb3) {
+                                        float (&xb1)[3], float (&xb2)[5], float& xb3,
+                                        float& xb4) {
   using T = RowTable<P>;
   // s = S z with the (1,1,2) adjoints, this half's eta
   float s[3] = {0.0f, 0.0f, 0.0f};
@@ -390,6 +502,8 @@ __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
 #pragma unroll
     for (int m = 0; m < 3; ++m) s[m] = fmaf(ror<J>(f.z1[m]), w, s[m]);
   });
+#pragma unroll
+  for (int m = 0; m < 3; ++m) formed(s[m]);
   const float pb = d[P::oPi + k.eta * P::K1 + k.e];
   float t[3], r[3];
 #pragma unroll
@@ -441,7 +555,10 @@ __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
     gz2[3] += 2.0f * g[5] * kRowInvSqrt2;
     gz2[4] += (g[0] - g[1]) * kRowInvSqrt2;
   }
+#pragma unroll
+  for (int m = 0; m < 5; ++m) formed(gz2[m]);
   xb3 = 0.0f;
+  xb4 = 0.0f;
   if constexpr (P::L >= 3) {
     const float j123 = d[P::o123 + k.e * P::K2 + k.eta], j233 = d[P::o233 + k.eta];
     float cz[15];
@@ -465,6 +582,7 @@ __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
         float tb = ub[m1] * f.z2[m2];
         tb += ror<P::K1>(tb);
         gz3 = fmaf(tb, cz[5 * m1 + m2], gz3);
+        formed(gz3);
       }
 #pragma unroll
     for (int m1 = 0; m1 < 5; ++m1) gz3 = fmaf(2.0f * vb[m1], f.w233[m1], gz3);
@@ -474,11 +592,70 @@ __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
         acc = fmaf(bcast<decltype(m1)::value * 5 + decltype(m)::value>(f.t123), ub[m1], acc);
       });
       gz2[m] = fmaf(j233, f.v233[m], acc);
+      formed(gz2[m]);
     });
     xb3 = fmaf(2.0f * d[P::oG3], f.z3l, gz3);
   }
 #pragma unroll
   for (int m = 0; m < 3; ++m) gz1[m] += ror<P::K1>(gz1[m]);   // both etas
+  if constexpr (P::L >= 4) {
+    const float j134 = d[P::o134 + k.e], j334 = d[P::o334], j444 = d[P::o444];
+    const float jown = d[P::o224 + 2 * k.eta], joff = d[P::o224 + 1] * kRowSqrt2;
+    const float j244 = d[P::o244 + k.eta];
+    float gz4 = 0.0f, gz3 = 0.0f, z2o[5];
+#pragma unroll
+    for (int m1 = 0; m1 < 3; ++m1) {
+      float c[7], r = 0.0f;
+      table_read(tab, T::k134Z + 2 * m1, k.l, c);
+      const float tb134 = half_row_sum<P::K1>(j134 * f.z1[m1]);
+      gz1[m1] = fmaf(j134, f.t134[m1], gz1[m1]);
+      gz3 = fmaf(tb134, f.r134[m1], gz3);
+#pragma unroll
+      for (int a = 0; a < 7; ++a) r = fmaf(c[a], f.xt3[a], r);
+      gz4 = fmaf(tb134, r, gz4);
+    }
+#pragma unroll
+    for (int m = 0; m < 5; ++m) z2o[m] = ror<P::K1>(f.z2[m]);
+    // the (2,2,4) adjoint of T224 made symmetric: this half's share is
+    // Jbar z z + (Jbar_01 / 2) z z', the halves together the whole
+#pragma unroll
+    for (int m1 = 0; m1 < 5; ++m1) {
+      float c[5];
+      table_read(tab, T::k224Z + 2 * m1, k.l, c);
+#pragma unroll
+      for (int m2 = 0; m2 < 5; ++m2) {
+        float tb = f.z2[m1] * fmaf(jown, f.z2[m2], 0.5f * joff * z2o[m2]);
+        tb += ror<P::K1>(tb);
+        gz4 = fmaf(tb, c[m2], gz4);
+      }
+      formed(gz4);
+    }
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+      gz2[m] = fmaf(2.0f * jown, f.v224[m], gz2[m]);
+      gz2[m] = fmaf(joff, ror<P::K1>(f.v224[m]), gz2[m]);
+      gz2[m] = fmaf(j244, f.t244[m], gz2[m]);
+      float tb = j244 * f.z2[m];
+      tb += ror<P::K1>(tb);
+      gz4 = fmaf(2.0f * tb, f.r244[m], gz4);
+    }
+    {
+      float r = 0.0f;
+#pragma unroll
+      for (int a = 0; a < 7; ++a) {
+        float c[7], q = 0.0f;
+        table_read(tab, T::k334Z + 2 * a, k.l, c);
+#pragma unroll
+        for (int e = 0; e < 7; ++e) q = fmaf(c[e], f.xt3[e], q);
+        r = fmaf(q, f.xt3[a], r);
+      }
+      gz4 = fmaf(j334, r, gz4);
+    }
+    gz3 = fmaf(2.0f * j334, f.r334, gz3);
+    gz4 = fmaf(3.0f * j444, f.r444, gz4);
+    xb3 += gz3;
+    xb4 = fmaf(2.0f * d[P::oG4], f.z4l, gz4);
+  }
   // dE/dX~ from the Gram blocks and the probes
   float gx1[3] = {0.0f, 0.0f, 0.0f}, gx2[5];
   unrolled<P::C1>([&](auto j) {
@@ -487,6 +664,8 @@ __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
 #pragma unroll
     for (int m = 0; m < 3; ++m) gx1[m] = fmaf(ror<J>(f.xt1[m]), w, gx1[m]);
   });
+#pragma unroll
+  for (int m = 0; m < 3; ++m) formed(gx1[m]);
   if constexpr (P::kHasA1) {
     row_product<P::K1>(gx1, gz1, tab, T::kA1T, k.l);
   } else {
@@ -503,6 +682,8 @@ __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
 #pragma unroll
     for (int m = 0; m < 5; ++m) gx2[m] = fmaf(ror<J>(f.xt2[m]), w, gx2[m]);
   });
+#pragma unroll
+  for (int m = 0; m < 5; ++m) formed(gx2[m]);
   // through the alignment (I + W)
 #pragma unroll
   for (int m = 0; m < 3; ++m) xb1[m] = gx1[m];
