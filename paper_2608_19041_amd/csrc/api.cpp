@@ -332,12 +332,11 @@ int dpa4c_model_create(const void* blob, size_t nbytes, int device, dpa4c_model*
     *out = nullptr;
     return DPA4C_ERR_HIP;
   }
-  // folded tables of two species (18 MB at full width), so that a program that
+  // folded tables of two species (20 MB at full width), so that a program that
   // only ever calls the entry point without allocation reads them too: the
   // separable tables take four times the bytes an edge
   if ((*out)->fold_allowed)
-    rc = w.ftab.ensure(4 * size_t(kFoldFirstTypes * kFoldFirstTypes) * (*out)->n_rows *
-                       (*out)->C0 * kFoldWords);
+    rc = w.ftab.ensure(fold_bytes((*out)->n_rows, (*out)->C0, (*out)->C[1], kFoldFirstTypes));
   if (rc == 0) rc = ensure_mlp_rows(*out, kMlpRowsFirst);
   if (rc == 0) rc = noalloc_setup(device);
   if (rc) {

@@ -36,6 +36,13 @@
 // lane that forms a gradient also adds -g_e (x) r_e (float64) to its group's
 // slot in LDS; the slots are summed in group order into the atom's term W_i
 // of the virial of Eq. (forces).
+//
+// What bounds it is the stream of table entries into the CUs, so it reads only
+// what a slope needs (fold.hip): 8 bytes a channel where the forward kernel
+// reads 12.  Backward over 24,000 water atoms (four tables, more than an L2)
+// 251 -> 168 us, 31,250 alloy atoms (25 tables) 435 -> 323 us, a million copper
+// atoms (one table) 5.86 -> 4.97 ms, 7,056 carbon atoms with the virial 89 ->
+// 82 us.
 #include <hip/hip_runtime.h>
 
 #include "../../include/dpa4c.h"
@@ -49,9 +56,9 @@ namespace {
 constexpr int kTeam = 256;
 constexpr int kWaves = kTeam / kWave;
 
-// Four waves per SIMD for the degree-three variants without the virial
-// (measured faster than three, despite a few spilled registers); the virial
-// and degree-four variants would spill more and keep their natural count.
+// Four waves per SIMD for the degree-three variants (121 to 128 registers, none
+// spilled; the virial's get there by themselves); degree four would spill and
+// keeps its natural three.
 template <class P, bool VIR>
 constexpr int backward_min_waves() { return P::L < 4 && !VIR ? 4 : 1; }
 
@@ -148,50 +155,48 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
     const int cnt = ecount[i];
     if (VIR && k == 0)
       for (int c = 0; c < 9; ++c) wv[grp][c] = 0.0;
-    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * (P::C0 * kFoldWords)
+    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * fold_pitch(P::C0, P::CPL)
                                   : md.pair + size_t(ai) * T1 * (P::C0 * P::PW);
 
     // Entry x of the pass (compact slot c0 + x of the row): the edge
     // gradient from its LDS entry and, with folded tables, the lane's table
     // entries ``T`` of that edge.
-    auto edge_work = [&](int x, int c0, const float3* T) {
+    auto edge_work = [&](int x, int c0, const FoldRow<P::CPL, false>& T) {
       const float4 ge = geo[x], ra = rad[x];
       const float x_ = ge.x, y = ge.y, z = ge.z, inv_rho = ge.w;
       const float tau = ra.x, chi = ra.y, dchi = ra.z;
       const bool valid = c0 + x < cnt;
       const float4 sc = scl[x];
-      float a0 = 0.0f, b0 = 0.0f, psi0 = 0.0f, dpsi0 = 0.0f;
+      // sum of dE/dY0 with the amplitudes, with their slopes, and (folded tables)
+      // with the slopes of amplitude times envelope
+      float a0 = 0.0f, b0 = 0.0f, d0 = 0.0f, psi0 = 0.0f, dpsi0 = 0.0f;
       if constexpr (FOLD) {
-        // the quintic of each channel from the table of the pair (a_i, a_j)
-        // (c4 and c5 below float32 resolution, not stored), power form; the
-        // float16 c2, c3 enter through their scaled weights (one
-        // mixed-precision FMA each).  The weighted sums a0 and b0 only
-        // need the lane's coefficients contracted with dE/dY0 first,
-        // A_p = sum_j Ybar0_j c_pj, and then one quintic in tau and its
-        // derivative; d/drho's 1/Delta is applied once to the sums.
+        // the polynomials of the table of the pair (a_i, a_j) (c4 and c5
+        // below float32 resolution, not stored), power form; the float16 c2,
+        // c3 enter through their scaled weights (one mixed-precision FMA
+        // each).  The lane's first channel is an amplitude, whose value the
+        // higher degrees need too; the others hold amplitude times envelope
+        // (fold.hip) and only their slope enters, so their c0 stays in
+        // memory.  Their coefficients are contracted with dE/dY0 first,
+        // A_p = sum_j Ybar0_j c_pj, then one slope in tau; d/drho's 1/Delta
+        // is applied once to the sums.
         const float4 wt = wts[x];
         const float e2 = wt.x, e3 = wt.y, f2 = wt.z, f3 = wt.w;
-        float A[4] = {0.f, 0.f, 0.f, 0.f};
+        psi0 = fmaf(T.c1[0], tau, T.c0[0]);
+        psi0 = fmaf(half_lo(T.w[0]), e2, psi0);
+        psi0 = fmaf(half_hi(T.w[0]), e3, psi0);
+        dpsi0 = fmaf(half_lo(T.w[0]), f2, T.c1[0]);
+        dpsi0 = fmaf(half_hi(T.w[0]), f3, dpsi0) * inv_delta;
+        float A1 = 0.0f, A2 = 0.0f, A3 = 0.0f;
 #pragma unroll
-        for (int jj = 0; jj < P::CPL; ++jj) {
-          const float c0f = T[jj].x, c1 = T[jj].y;
-          const uint32_t h23 = __float_as_uint(T[jj].z);
-          const float h2 = half_lo(h23), h3 = half_hi(h23);
-          if (jj == 0) {   // the amplitude of the lane's first channel itself
-            psi0 = fmaf(c1, tau, c0f);
-            psi0 = fmaf(h2, e2, psi0);
-            psi0 = fmaf(h3, e3, psi0);
-            dpsi0 = fmaf(h2, f2, c1);
-            dpsi0 = fmaf(h3, f3, dpsi0);
-          }
-          A[0] = fmaf(gy0[jj], c0f, A[0]);
-          A[1] = fmaf(gy0[jj], c1, A[1]);
-          A[2] = fmaf(gy0[jj], h2, A[2]);
-          A[3] = fmaf(gy0[jj], h3, A[3]);
+        for (int jj = 1; jj < P::CPL; ++jj) {
+          A1 = fmaf(gy0[jj], T.c1[jj], A1);
+          A2 = fmaf(gy0[jj], half_lo(T.w[jj]), A2);
+          A3 = fmaf(gy0[jj], half_hi(T.w[jj]), A3);
         }
-        a0 = fmaf(A[3], e3, fmaf(A[2], e2, fmaf(A[1], tau, A[0])));
-        b0 = fmaf(A[3], f3, fmaf(A[2], f2, A[1])) * inv_delta;
-        dpsi0 *= inv_delta;
+        a0 = gy0[0] * psi0;
+        b0 = gy0[0] * dpsi0;
+        d0 = fmaf(A3, f3, fmaf(A2, f2, A1)) * inv_delta;
       } else {
         const float t2 = tau * tau, t3 = t2 * tau, t4 = t2 * t2, t5 = t4 * tau;
         const float d1 = 2.0f * tau, d2 = 3.0f * t2, d3 = 4.0f * t3, d4 = 5.0f * t4;
@@ -246,7 +251,7 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
       const float Q = (v1[0] * x_ + v1[1] * y + v1[2] * z) +
                       0.5f * (gq[0] * x_ + gq[1] * y + gq[2] * z) + m0 * sc.w;
       const float chi2 = sc.x, dchi2 = sc.y;
-      float drho = dchi * a0 + chi * b0 + Q * (dchi2 * psi0 + chi2 * dpsi0) + m0 * sc.z;
+      float drho = dchi * a0 + chi * b0 + d0 + Q * (dchi2 * psi0 + chi2 * dpsi0) + m0 * sc.z;
       const float wu = chi2 * psi0;
       float dux = wu * (v1[0] + gq[0] + m0 * cb.x);
       float duy = wu * (v1[1] + gq[1] + m0 * cb.y);
@@ -276,9 +281,8 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
       }
     };
     // the lane's folded table entries of entry x of the pass
-    auto load_rows = [&](int x, float3* T) {
-      load_fold_row<P::LPE, P::CPL>(
-          pair_base + size_t(__float_as_int(rad[x].w)) * (P::C0 * kFoldWords), k, T);
+    auto load_rows = [&](int x, FoldRow<P::CPL, false>& T) {
+      load_fold_row<P::LPE, P::CPL, false>(pair_base, __float_as_uint(rad[x].w), k, T);
     };
 
     // The row in passes of 64 edges: each lane first reads one record and
@@ -302,7 +306,9 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
           const int j = __float_as_int(rec.w);
           const int aj = type_of(j);
           ge = make_float4(g.ux, g.uy, g.uz, g.inv_rho);
-          ra = make_float4(tau, chi, dchi, __int_as_float(FOLD ? aj * md.n_rows + row : row));
+          ra = make_float4(tau, chi, dchi,
+                           FOLD ? __uint_as_float(fold_offset<P::C0, P::CPL>(aj * md.n_rows + row))
+                                : __int_as_float(row));
           id = make_int2(j, aj);
           const float x_ = g.ux, y = g.uy, z = g.uz;
           const float chi2 = chi * chi, dchi2 = 2.0f * chi * dchi;
@@ -346,7 +352,7 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
       if constexpr (FOLD) {
         // the table entries of a group's next edge are requested before its
         // current edge is evaluated (two register sets, used in turn)
-        float3 TA[P::CPL], TB[P::CPL];
+        FoldRow<P::CPL, false> TA, TB;
         load_rows(grp, TA);
         for (int base = 0; base < np; base += 2 * G) {
           if (base + G < np) load_rows(base + G + grp, TB);
@@ -356,7 +362,7 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
           edge_work(base + G + grp, c0, TB);
         }
       } else {
-        for (int base = 0; base < np; base += G) edge_work(base + grp, c0, nullptr);
+        for (int base = 0; base < np; base += G) edge_work(base + grp, c0, {});
       }
       wave_sync();
       // every record of the pass was read before its edges ran

@@ -133,7 +133,7 @@ int with_profile(int C0, int L, int R, int F, Fn&& fn) {
 constexpr int kMaxTypeRows = 128;        // type-table rows (species + padding) a model may have
 constexpr int kMaxFoldTypes = 5;         // species for which pair-folded tables are built
 constexpr int kFoldFirstTypes = 2;       // species whose folded tables have room from the start
-constexpr size_t kMaxFoldBytes = size_t(256) << 20;  // and their largest total size
+constexpr size_t kMaxFoldBytes = size_t(300) << 20;  // and their largest total size
 constexpr int kC123 = 3 * 5 * 7;          // dense (1,2,3) coupling, [m1][m2][m3]
 constexpr int kC233 = 5 * 7 * 7;          // dense (2,3,3) coupling
 constexpr int kCouplings = kC123 + kC233;
@@ -168,7 +168,7 @@ struct ModelDev {
   const float* E_ref;       // [T+1]
   const float* row_tab;     // per-lane tables of the readout (readout_row.h)
   // pair-folded tables (fold.hip), used when fold_n > 0:
-  // [fold_n^2 pairs][n_rows] rows of kFoldWords C0 words in the order of
+  // [fold_n^2 pairs][n_rows] rows of fold_pitch words in the order of
   // load_fold_row, pair (fa, fb) at fa * fold_n + fb; c_inv = the inverse
   // scales of the float16 c2, c3
   const float* ftab;
@@ -177,8 +177,17 @@ struct ModelDev {
 };
 
 // Words per channel of a folded table: c0 and c1 as float32, then (c2, c3)
-// as a scaled float16 pair: one 12-byte load.
+// as a scaled float16 pair.
 constexpr int kFoldWords = 3;
+// words from one row of a folded table to the next: the channels' words and,
+// where a lane owns more than two channels, the line of first c0 (load_fold_row)
+__host__ __device__ constexpr int fold_pitch(int C0, int CPL) {
+  return C0 * kFoldWords + (CPL > 2 ? 32 : 0);
+}
+// bytes of the folded tables of n species
+inline size_t fold_bytes(int rows, int C0, int LPE, int n) {
+  return 4 * size_t(n) * n * rows * fold_pitch(C0, C0 / LPE);
+}
 
 // ---------------------------------------------------------------------------
 // Error handling

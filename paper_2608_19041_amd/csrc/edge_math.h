@@ -298,42 +298,69 @@ __device__ inline float4 group_bcast(float4 v) {
   return v;
 }
 
-// The lane's entries of a folded table row (kFoldWords * C0 words) for its
-// CPL channels c = k + LPE j.  The row holds first the (c0, c1) float32 pairs
-// and then the words of scaled float16 (c2, c3), each permuted so that a
-// lane's values are adjacent: the pairs of its channels j = 2q, 2q + 1 form
-// the 16 bytes at (q LPE + k) * 4, and the words of j = 4q .. 4q + 3 the 16
-// bytes at 2 C0 + (q LPE + k) * 4 (8 bytes at 2 C0 + 2 k when CPL = 2).  A
-// lane thus reads its 12 CPL bytes with 16-byte loads, the group at unit
-// stride.  T[j] = (c0, c1, word) of channel j.
-template <int LPE, int CPL>
-__device__ inline void load_fold_row(const float* __restrict__ row, int k, float3* T) {
-  static_assert(CPL == 2 || CPL % 4 == 0, "folded row layout");
-  float4 a[CPL / 2];
-#pragma unroll
-  for (int q = 0; q < CPL / 2; ++q) a[q] = *reinterpret_cast<const float4*>(row + (q * LPE + k) * 4);
+// A lane's entries of a folded table row for its channels c = k + LPE j: c1 and
+// the word of scaled float16 (c2, c3) of each channel, and c0 of the channels
+// whose value the kernel needs: all of them (VAL), or the first one.  A row
+// holds a plane of C0 words for c0, for c1 and for the (c2, c3), each permuted
+// so that a lane's values are adjacent and a group reads them with 16-byte
+// loads at unit stride.  Where a lane has more than two channels the c0 of the
+// first ones follow once more in a cache line of their own: to read them from
+// their plane would take all of it through the cache, and a split plane took
+// the forward kernel a seventh load (5.95 -> 6.31 ms at a million copper atoms).
+template <int CPL, bool VAL>
+struct FoldRow {
+  float c0[VAL ? CPL : 1], c1[CPL];
   uint32_t w[CPL];
-  const float* wrow = row + 2 * LPE * CPL;
-  if constexpr (CPL == 2) {
-    const uint2 v = *reinterpret_cast<const uint2*>(wrow + 2 * k);
-    w[0] = v.x;
-    w[1] = v.y;
+};
+
+// where channel (k, j) of a plane of LPE x W words lies: pieces of four words
+// of a lane (16 bytes), then a pair
+__host__ __device__ constexpr int fold_at(int LPE, int W, int k, int j) {
+  const int whole = W / 4 * 4;
+  return j < whole ? (j / 4 * LPE + k) * 4 + j % 4 : whole * LPE + k * 2 + j - whole;
+}
+// a row's offset in bytes from its centre type's tables (kMaxFoldBytes fits 32
+// bits, so a load takes the tables' scalar base and one register)
+template <int C0, int CPL>
+__device__ __forceinline__ uint32_t fold_offset(int row) {
+  return static_cast<uint32_t>(row) * (4 * fold_pitch(C0, CPL));
+}
+// one plane of LPE x W words into the lane's v; off = its offset in bytes
+template <int LPE, int W, class T>
+__device__ __forceinline__ void load_fold_plane(const float* __restrict__ base, uint32_t off, int k,
+                                                T* v) {
+  static_assert(W % 2 == 0, "pieces of four words and a pair");
+  const char* p = reinterpret_cast<const char*>(base);
+  const uint32_t o4 = off + 16u * k;
+#pragma unroll
+  for (int j = 0; j + 4 <= W; j += 4) {
+    const float4 a = *reinterpret_cast<const float4*>(p + o4 + 4 * fold_at(LPE, W, 0, j));
+    v[j] = __builtin_bit_cast(T, a.x);
+    v[j + 1] = __builtin_bit_cast(T, a.y);
+    v[j + 2] = __builtin_bit_cast(T, a.z);
+    v[j + 3] = __builtin_bit_cast(T, a.w);
+  }
+  if constexpr (W % 4 != 0) {
+    const float2 a = *reinterpret_cast<const float2*>(p + (off + 8u * k) +
+                                                      4 * fold_at(LPE, W, 0, W - 2));
+    v[W - 2] = __builtin_bit_cast(T, a.x);
+    v[W - 1] = __builtin_bit_cast(T, a.y);
+  }
+}
+template <int LPE, int CPL, bool VAL>
+__device__ __forceinline__ void load_fold_row(const float* __restrict__ base, uint32_t off, int k,
+                                              FoldRow<CPL, VAL>& T) {
+  constexpr int C0 = LPE * CPL;
+  static_assert(LPE <= 32, "the first channels' c0 fill one line");
+  if constexpr (VAL) {
+    load_fold_plane<LPE, CPL>(base, off, k, T.c0);
   } else {
-#pragma unroll
-    for (int q = 0; q < CPL / 4; ++q) {
-      const uint4 v = *reinterpret_cast<const uint4*>(wrow + (q * LPE + k) * 4);
-      w[4 * q] = v.x;
-      w[4 * q + 1] = v.y;
-      w[4 * q + 2] = v.z;
-      w[4 * q + 3] = v.w;
-    }
+    const float* p = CPL > 2 ? base + 3 * C0 : base;
+    T.c0[0] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) +
+                                              (off + (CPL > 2 ? 4u : 8u) * k));
   }
-#pragma unroll
-  for (int j = 0; j < CPL; ++j) {
-    const float4& p = a[j / 2];
-    T[j] = (j & 1) ? make_float3(p.z, p.w, __uint_as_float(w[j]))
-                   : make_float3(p.x, p.y, __uint_as_float(w[j]));
-  }
+  load_fold_plane<LPE, CPL>(base + C0, off, k, T.c1);
+  load_fold_plane<LPE, CPL>(base + 2 * C0, off, k, T.w);
 }
 __device__ inline float half_lo(uint32_t h) {
   return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h & 0xFFFFu)));

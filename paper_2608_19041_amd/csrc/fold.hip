@@ -10,6 +10,13 @@
 // Hermite interpolation of the radial table").  Its normalised coefficients
 // are that same linear combination of the tabulated ones.
 //
+// The channels c >= C1 enter degree zero alone, as chi psi_c, so their tables
+// hold that product: its Taylor coefficients over an interval are those of psi
+// convolved with those of the envelope at the knot.  The forward kernel then
+// adds the interpolant as it is, and the backward kernel, which needs
+// d(chi psi)/drho and no value, leaves c0 of these channels (7 of 8 at full
+// width) in memory and takes 1,088 bytes an edge instead of 1,536.
+//
 // Storage: c0 and c1 in float32, c2 and c3 as float16 scaled by fixed powers
 // of two (one per coefficient, from a bound over every pair: |gamma| < 2 and
 // |U| < 1 by their tanh forms, times the largest tabulated coefficient); c4
@@ -17,9 +24,9 @@
 // coefficients fall by about two orders of magnitude per power at
 // Delta = 0.002 A, so the whole contribution of c4 and c5 together with the
 // 2^-11 relative rounding of c2 and c3 stays below the float32 rounding of
-// the value and below 2^-14 of the slope term (checked per model at set-up;
-// a model that fails the check runs on the separable float32 tables), and a
-// channel takes one 12-byte load instead of 24 bytes.
+// the value and below 2^-14 of the slope term (checked per model at set-up, for
+// psi and for chi psi; a model that fails the check runs on the separable
+// float32 tables), and a channel takes 12 bytes instead of 24.
 //
 // For the few species of an MD system the library keeps one such table per
 // ordered pair present; the edge kernels then read one quintic per channel
@@ -27,7 +34,7 @@
 // with more than kMaxFoldTypes species, or whose folded tables would exceed
 // kMaxFoldBytes, use the separable tables directly.  Five species at full
 // width (128 channels, 3,000 rows at r_c = 6 A and Delta = 0.002 A) fold into
-// 25 tables of 4.6 MB (115 MB, within the last-level cache); on the 5-species
+// 25 tables of 5.0 MB (125 MB, within the last-level cache); on the 5-species
 // alloy the folded tables measured faster than the separable ones (backward
 // 0.94 -> 0.70 ms at 31,250 atoms, when a folded channel still took 16 B),
 // since every edge then reads one 12-byte entry per channel from one table
@@ -61,35 +68,48 @@ struct FoldTypes {
 __global__ void fold_build_kernel(const float* __restrict__ gtab, const float* __restrict__ qtab,
                                   const float* __restrict__ pair, FoldTypes used, int n_used,
                                   int n_types1, int C0, int R, int LPE, int rows,
-                                  const float2 scale, float* __restrict__ ftab) {
+                                  double r_c, double delta, const float2 scale,
+                                  float* __restrict__ ftab) {
   const int s = blockIdx.x, p = blockIdx.y;
+  // the envelope at the row's knot, chi_n = chi^(n) Delta^n / n!:
+  // chi = t^4 (1 + 4x + 10x^2 + 20x^3 + 35x^4), chi' = -280 x^4 t^3 / r_c
+  const double x = s * delta / r_c, t = x < 1.0 ? 1.0 - x : 0.0, h = delta / r_c;
+  const double x2 = x * x, t2 = t * t;
+  const double chi[4] = {
+      t2 * t2 * (1.0 + x * (4.0 + x * (10.0 + x * (20.0 + x * 35.0)))),
+      -280.0 * x2 * x2 * t2 * t * h,
+      -140.0 * x2 * x * t2 * (4.0 * t - 3.0 * x) * h * h,
+      -280.0 * x2 * t * (2.0 * t2 - 4.0 * x * t + x2) * h * h * h};
   const int a = used.t[p / n_used], b = used.t[p % n_used];
   const int PW = 2 + R, CPL = C0 / LPE;
   for (int c = threadIdx.x; c < C0; c += blockDim.x) {
     const int k = c % LPE, j = c / LPE;
     const float* pc = pair + ((size_t(a * n_types1 + b) * CPL + j) * LPE + k) * PW;
     const float* g = gtab + ((size_t(s) * CPL + j) * LPE + k) * 6;
-    // row s of pair p: the (c0, c1) pairs, then the (c2, c3) words, each
-    // permuted so that lane k's values for its channels are adjacent (the
-    // order the edge kernels read, load_fold_row)
-    float* row = ftab + (size_t(p) * rows + s) * C0 * kFoldWords;
-    float* pr = row + ((j / 2) * LPE + k) * 4 + 2 * (j % 2);
-    uint32_t* wd = reinterpret_cast<uint32_t*>(row + 2 * C0) +
-                   (CPL == 2 ? 2 * k + j : ((j / 4) * LPE + k) * 4 + j % 4);
+    // row s of pair p, in the order the edge kernels read (load_fold_row)
+    float* row = ftab + (size_t(p) * rows + s) * fold_pitch(C0, CPL);
+    const int at = fold_at(LPE, CPL, k, j);
     double v[4];
     for (int q = 0; q < 4; ++q) {
       v[q] = double(pc[0]) * double(g[q]) + (q == 0 ? double(pc[1]) : 0.0);
       for (int mu = 0; mu < R; ++mu)
         v[q] += double(pc[2 + mu]) * double(qtab[(size_t(s) * R + mu) * 6 + q]);
     }
+    if (j > 0)   // times the envelope, from the highest power down
+      for (int q = 3; q >= 0; --q) {
+        double f = 0.0;
+        for (int m = 0; m <= q; ++m) f += chi[m] * v[q - m];
+        v[q] = f;
+      }
     const float sc[2] = {scale.x, scale.y};
     uint16_t hb[2];
     for (int q = 0; q < 2; ++q)
       hb[q] = __builtin_bit_cast(uint16_t,
                                  static_cast<_Float16>(static_cast<float>(v[2 + q] * sc[q])));
-    pr[0] = static_cast<float>(v[0]);
-    pr[1] = static_cast<float>(v[1]);
-    *wd = uint32_t(hb[0]) | (uint32_t(hb[1]) << 16);
+    row[at] = static_cast<float>(v[0]);
+    if (CPL > 2 && j == 0) row[3 * C0 + k] = static_cast<float>(v[0]);
+    row[C0 + at] = static_cast<float>(v[1]);
+    reinterpret_cast<uint32_t*>(row)[2 * C0 + at] = uint32_t(hb[0]) | (uint32_t(hb[1]) << 16);
   }
 }
 
@@ -125,8 +145,7 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
         }
         ++n_used;
       }
-    const size_t per_pair = size_t(m->n_rows) * m->C0 * kFoldWords;
-    const size_t need = 4 * per_pair * size_t(n_used) * size_t(n_used);
+    const size_t need = fold_bytes(m->n_rows, m->C0, m->C[1], n_used);
     if (!m->fold_allowed || n_used > kMaxFoldTypes || need > kMaxFoldBytes) {
       std::memcpy(m->fold_types_mask, mask, sizeof(m->fold_types_mask));
       m->fold_n = 0;   // the separable tables are used
@@ -140,7 +159,7 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
       DPA4C_HIP_TRY(hipMemcpyAsync(w.fold_map.p, hmap, 4 * size_t(T1), hipMemcpyHostToDevice, st));
       hipLaunchKernelGGL(fold_build_kernel, dim3(m->n_rows, n_used * n_used),
                          dim3(m->C0 < 256 ? m->C0 : 256), 0, st, m->gtab, m->qtab, m->pair, used,
-                         n_used, T1, m->C0, m->R, m->C[1], m->n_rows,
+                         n_used, T1, m->C0, m->R, m->C[1], m->n_rows, m->r_c, m->delta,
                          make_float2(m->c_scale[0], m->c_scale[1]),
                          w.ftab.as<float>());
       DPA4C_HIP_TRY(hipGetLastError());

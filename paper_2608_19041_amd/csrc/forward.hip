@@ -86,29 +86,29 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
     // accumulates component m = k of each
     float acc3 = 0.0f, acc4 = 0.0f;
     float s0 = 0.0f, s1 = 0.0f;
-    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * (P::C0 * kFoldWords)
+    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * fold_pitch(P::C0, P::CPL)
                                   : md.pair + size_t(ai) * T1 * (P::C0 * P::PW);
 
     // One edge's contribution from its LDS entry and, with folded tables,
     // the lane's table entries ``T`` of that edge.
-    auto edge_work = [&](int x, const float3* T) {
+    auto edge_work = [&](int x, const FoldRow<P::CPL, true>& T) {
       const float4 pr = pre[x];
       const float tau = pr.x, chi = pr.y;
       float psi0 = 0.0f;
       if constexpr (FOLD) {
-        // the quintic of each channel from the table of the pair (a_i, a_j)
+        // the polynomial of each channel from the table of the pair (a_i, a_j)
         // (c4 and c5 below float32 resolution, not stored), power form with
         // the float16 c2, c3 scaled through their weights e_n = tau^n / s_n
-        // (one mixed-precision FMA each)
+        // (one mixed-precision FMA each): the amplitude of the lane's first
+        // channel, the amplitude times the envelope of the others (fold.hip)
         const float t2 = tau * tau, t3 = t2 * tau;
         const float e2 = md.c_inv[0] * t2, e3 = md.c_inv[1] * t3;
 #pragma unroll
         for (int jj = 0; jj < P::CPL; ++jj) {
-          const uint32_t h23 = __float_as_uint(T[jj].z);
-          float psi = fmaf(T[jj].y, tau, T[jj].x);
-          psi = fmaf(half_lo(h23), e2, psi);
-          psi = fmaf(half_hi(h23), e3, psi);
-          acc0[jj] += chi * psi;
+          float psi = fmaf(T.c1[jj], tau, T.c0[jj]);
+          psi = fmaf(half_lo(T.w[jj]), e2, psi);
+          psi = fmaf(half_hi(T.w[jj]), e3, psi);
+          acc0[jj] += (jj == 0 ? chi : pr.w) * psi;   // pr.w: 1, or 0 past the pass
           if (jj == 0) psi0 = psi;
         }
       } else {
@@ -164,9 +164,8 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
       }
     };
     // the lane's folded table entries of entry x of the pass
-    auto load_rows = [&](int x, float3* T) {
-      load_fold_row<P::LPE, P::CPL>(
-          pair_base + size_t(__float_as_int(pre[x].z)) * (P::C0 * kFoldWords), k, T);
+    auto load_rows = [&](int x, FoldRow<P::CPL, true>& T) {
+      load_fold_row<P::LPE, P::CPL, true>(pair_base, __float_as_uint(pre[x].z), k, T);
     };
 
     int kept = 0;
@@ -186,7 +185,7 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
           envelope(g.rho, md.inv_rc, &chi, nullptr);
           const int row = table_row(g.rho, inv_delta, md.n_rows, &tau);
           const int aj = type_of(__float_as_int(rec.w));
-          pr = FOLD ? make_float4(tau, chi, __int_as_float(aj * md.n_rows + row), 0.0f)
+          pr = FOLD ? make_float4(tau, chi, __uint_as_float(fold_offset<P::C0, P::CPL>(aj * md.n_rows + row)), 1.0f)
                     : make_float4(tau, chi, __int_as_float(row), __int_as_float(aj));
           hv[0] = g.ux;
           hv[1] = g.uy;
@@ -209,7 +208,7 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
       if constexpr (FOLD) {
         // the table entries of a group's next edge are requested before its
         // current edge is evaluated (two register sets, used in turn)
-        float3 TA[P::CPL], TB[P::CPL];
+        FoldRow<P::CPL, true> TA, TB;
         if (np > 0) load_rows(grp, TA);
         for (int base = 0; base < np; base += 2 * G) {
           if (base + G < np) load_rows(base + G + grp, TB);
@@ -219,7 +218,7 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
           edge_work(base + G + grp, TB);
         }
       } else {
-        for (int base = 0; base < np; base += G) edge_work(base + grp, nullptr);
+        for (int base = 0; base < np; base += G) edge_work(base + grp, {});
       }
       wave_sync();   // the LDS entries are rewritten by the next pass
     }

@@ -516,16 +516,35 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
     for (size_t e = q; e < qtab.size(); e += 6) qmax = std::max(qmax, double(std::fabs(qtab[e])));
     bnd[q] = 2.0 * gmax + double(R) * qmax;
   }
+  // The channels past C1 hold chi psi, whose coefficients are those of psi
+  // convolved with the envelope's (|chi| <= 1; the derivatives' bounds below
+  // hold for every x in [0, 1]: |x^4 t^3| <= 0.0085, |x^3 t^2 (4t - 3x)| <=
+  // 0.034, |x^2 t (2t^2 - 4xt + x^2)| <= 0.041, the next two at the ends).
+  // |beta| < 1 + 2 max|embedding| enters psi's value alone.
+  const double f16 = std::ldexp(1.0, -11);
+  auto within = [&](double value) {
+    return (bnd[2] + bnd[3]) * f16 + bnd[4] + bnd[5] <= value * std::ldexp(1.0, -24) &&
+           (2.0 * bnd[2] + 3.0 * bnd[3]) * f16 + 4.0 * bnd[4] + 5.0 * bnd[5] <=
+               bnd[1] * std::ldexp(1.0, -14);
+  };
+  m->fold_allowed = within(bnd[0]);   // the channels that hold psi
+  {
+    double beta = 1.0;
+    for (size_t e = 0; e < size_t(T1) * C0; ++e)
+      beta = std::max(beta, 1.0 + 2.0 * std::fabs(double(type_embed[e])));
+    const double h = m->delta / m->r_c;
+    const double chi[6] = {1.0, 280 * 0.0085 * h, 140 * 0.034 * h * h, 280 * 0.041 * std::pow(h, 3),
+                           70 * std::pow(h, 4), 224 * std::pow(h, 5)};
+    for (int q = 5; q >= 1; --q)
+      for (int n = 1; n <= q; ++n) bnd[q] += chi[n] * (n == q ? bnd[0] + beta : bnd[q - n]);
+    m->fold_allowed = m->fold_allowed && within(bnd[0] + beta);   // those that hold chi psi
+  }
   for (int q = 2; q < 6; ++q) {
     int ex = 0;
     if (bnd[q] > 0.0) ex = static_cast<int>(std::floor(std::log2(16384.0 / bnd[q])));
     ex = std::max(-100, std::min(100, ex));
     m->c_scale[q - 2] = static_cast<float>(std::ldexp(1.0, ex));
   }
-  const double f16 = std::ldexp(1.0, -11);
-  const double val_lim = bnd[0] * std::ldexp(1.0, -24), slope_lim = bnd[1] * std::ldexp(1.0, -14);
-  m->fold_allowed = (bnd[2] + bnd[3]) * f16 + bnd[4] + bnd[5] <= val_lim &&
-                    (2.0 * bnd[2] + 3.0 * bnd[3]) * f16 + 4.0 * bnd[4] + 5.0 * bnd[5] <= slope_lim;
 
   // ---- coupling tensors, each symmetrised over the indices of equal degree
   // (the exact integrals are; the quadrature sums are only up to rounding)
