@@ -62,7 +62,9 @@ constexpr int kWaves = kTeam / kWave;
 template <class P, bool VIR>
 constexpr int backward_min_waves() { return P::L < 4 && !VIR ? 4 : 1; }
 
-template <class P, bool FOLD, bool VIR>
+// W = 4 as in the forward kernel: up to kSplitRows centres the four waves of a
+// workgroup share a row.
+template <class P, bool FOLD, bool VIR, int W>
 __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backward_kernel(ModelDev md, int64_t n,
                                                          const int32_t* __restrict__ typ,
                                                          const int64_t* __restrict__ row_ptr,
@@ -103,8 +105,15 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
   // index of every atom
   auto type_of = [&](int64_t a) { return FOLD ? typ[a] : clamp_type(typ[a], T1); };
 
-  for (int64_t blk = xcd_block(blockIdx.x, gridDim.x); blk * kWaves < n; blk += gridDim.x) {
-    const int64_t i = blk * kWaves + wave;
+  constexpr int kRows = kWaves / W;   // centres of a workgroup
+  static_assert(W == 1 || W == kWaves, "a row per wave or per workgroup");
+  // the records of a round are read before its gradients are stored
+  auto round_sync = [] {
+    if constexpr (W == 1) wave_sync();
+    else __syncthreads();
+  };
+  for (int64_t blk = xcd_block(blockIdx.x, gridDim.x); blk * kRows < n; blk += gridDim.x) {
+    const int64_t i = blk * kRows + (W == 1 ? wave : 0);
     if (i >= n) break;
     const int ai = type_of(i);
     const float* gyr = node_grad + size_t(i) * P::NS;
@@ -158,14 +167,14 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
     const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * fold_pitch(P::C0, P::CPL)
                                   : md.pair + size_t(ai) * T1 * (P::C0 * P::PW);
 
-    // Entry x of the pass (compact slot c0 + x of the row): the edge
+    // Entry x of the pass's np (compact slot c0 + x of the row): the edge
     // gradient from its LDS entry and, with folded tables, the lane's table
     // entries ``T`` of that edge.
-    auto edge_work = [&](int x, int c0, const FoldRow<P::CPL, false>& T) {
+    auto edge_work = [&](int x, int np, const FoldRow<P::CPL, false>& T) {
       const float4 ge = geo[x], ra = rad[x];
       const float x_ = ge.x, y = ge.y, z = ge.z, inv_rho = ge.w;
       const float tau = ra.x, chi = ra.y, dchi = ra.z;
-      const bool valid = c0 + x < cnt;
+      const bool valid = x < np;
       const float4 sc = scl[x];
       // sum of dE/dY0 with the amplitudes, with their slopes, and (folded tables)
       // with the slopes of amplitude times envelope
@@ -289,8 +298,12 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
     // forms its edge's geometry, envelope and table row into the wave's LDS
     // slice (entries past the row get chi = 0 and table row 0), then the
     // groups take the pass's edges.
-    for (int c0 = ((cnt - 1) / kWave) * kWave; cnt > 0 && c0 >= 0; c0 -= kWave) {
-      const int np = cnt - c0 < kWave ? cnt - c0 : kWave;
+    const int rounds = (cnt + W * kWave - 1) / (W * kWave);
+    // edges of a wave in a round: 64, or an even share of the row
+    const int share = W == 1 ? kWave : rounds > 0 ? (cnt + W * rounds - 1) / (W * rounds) : 0;
+    for (int rd = rounds - 1; rd >= 0; --rd) {
+      const int c0 = (rd * W + (W == 1 ? 0 : wave)) * share;
+      const int np = cnt - c0 < share ? (cnt > c0 ? cnt - c0 : 0) : share;
       {
         float4 ge = make_float4(0.f, 0.f, 0.f, 1.0f), ra = make_float4(0.f, 0.f, 0.f, 0.f);
         float4 sc = make_float4(0.f, 0.f, 0.f, 0.f), cb = sc, wt = sc;
@@ -348,7 +361,7 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
         cub[lane] = cb;
         if constexpr (FOLD) wts[lane] = wt;
       }
-      wave_sync();
+      round_sync();
       if constexpr (FOLD) {
         // the table entries of a group's next edge are requested before its
         // current edge is evaluated (two register sets, used in turn)
@@ -356,13 +369,13 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
         load_rows(grp, TA);
         for (int base = 0; base < np; base += 2 * G) {
           if (base + G < np) load_rows(base + G + grp, TB);
-          edge_work(base + grp, c0, TA);
+          edge_work(base + grp, np, TA);
           if (base + G >= np) break;
           if (base + 2 * G < np) load_rows(base + 2 * G + grp, TA);
-          edge_work(base + G + grp, c0, TB);
+          edge_work(base + G + grp, np, TB);
         }
       } else {
-        for (int base = 0; base < np; base += G) edge_work(base + grp, c0, {});
+        for (int base = 0; base < np; base += G) edge_work(base + grp, np, {});
       }
       wave_sync();
       // every record of the pass was read before its edges ran
@@ -370,13 +383,13 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
       wave_sync();   // the LDS entries are rewritten by the next pass
     }
     if (VIR) {
-      wave_sync();
-      if (lane < 9) {
+      round_sync();
+      if (lane < 9 && (W == 1 || wave == 0)) {
         double s = 0.0;
-        for (int q = 0; q < G; ++q) s += wv[q][lane];
+        for (int q = 0; q < W * G; ++q) s += W == 1 ? wv[q][lane] : wv_all[q / G][q % G][lane];
         w_atom[9 * i + lane] = s;
       }
-      wave_sync();   // the slots are cleared for the next row
+      round_sync();   // the slots are cleared for the next row
     }
   }
 }
@@ -385,23 +398,25 @@ template <class P>
 int launch(const dpa4c_model* m, int64_t n, const int32_t* species, const int32_t* fidx,
            const int64_t* row_ptr, const int32_t* ecount, float4* edge, const int32_t* cskin,
            const float* node_grad, double* w_atom, hipStream_t st) {
-  int64_t blocks = (n + kWaves - 1) / kWaves;   // a wave per centre
+  const bool split = n <= kSplitRows;   // a workgroup per centre, else a wave
+  int64_t blocks = split ? n : (n + kWaves - 1) / kWaves;
   blocks = blocks < 65536 ? blocks : 65536;
   if (blocks < 1) return 0;
   const int32_t* typ = fidx ? fidx : species;
-  const dim3 grid(static_cast<unsigned>(blocks)), block(kTeam);
-  if (fidx && w_atom)
-    hipLaunchKernelGGL((backward_kernel<P, true, true>), grid, block, 0, st, m->dev(), n, typ,
-                       row_ptr, ecount, edge, cskin, node_grad, w_atom);
-  else if (fidx)
-    hipLaunchKernelGGL((backward_kernel<P, true, false>), grid, block, 0, st, m->dev(), n, typ,
-                       row_ptr, ecount, edge, cskin, node_grad, w_atom);
-  else if (w_atom)
-    hipLaunchKernelGGL((backward_kernel<P, false, true>), grid, block, 0, st, m->dev(), n, typ,
-                       row_ptr, ecount, edge, cskin, node_grad, w_atom);
-  else
-    hipLaunchKernelGGL((backward_kernel<P, false, false>), grid, block, 0, st, m->dev(), n, typ,
-                       row_ptr, ecount, edge, cskin, node_grad, w_atom);
+  auto go = [&](auto fold, auto vir) {
+    constexpr bool F = decltype(fold)::value, V = decltype(vir)::value;
+    const dim3 grid(static_cast<unsigned>(blocks)), block(kTeam);
+    if (split)
+      hipLaunchKernelGGL((backward_kernel<P, F, V, kWaves>), grid, block, 0, st, m->dev(), n, typ,
+                         row_ptr, ecount, edge, cskin, node_grad, w_atom);
+    else
+      hipLaunchKernelGGL((backward_kernel<P, F, V, 1>), grid, block, 0, st, m->dev(), n, typ,
+                         row_ptr, ecount, edge, cskin, node_grad, w_atom);
+  };
+  if (fidx && w_atom) go(std::true_type{}, std::true_type{});
+  else if (fidx) go(std::true_type{}, std::false_type{});
+  else if (w_atom) go(std::false_type{}, std::true_type{});
+  else go(std::false_type{}, std::false_type{});
   DPA4C_HIP_TRY(hipGetLastError());
   return 0;
 }

@@ -63,15 +63,18 @@ __device__ inline CentreQ centre_q(const CompactArgs& a, int64_t i) {
 
 // One pass of a wavefront over the skin entries [s0, s0 + 64) of the row
 // [b, e) of centre ``ci``: lane l tests entry s0 + l with the exact predicate,
-// and the entries inside r_c keep canonical order.  ``kept`` edges of the row
-// precede the pass.  A kept lane writes its record r_ij = (r_j + sum_b n_b
-// h_b) - r_i (float64 difference stored as float32) to compact slot kept +
-// *at of the row, and the position of its skin entry in the row to the same
+// and the entries inside r_c keep canonical order.  first(m), called by every
+// lane with the number m that the pass keeps, tells how many edges of the row
+// precede them.  A kept lane writes its record r_ij = (r_j + sum_b n_b
+// h_b) - r_i (float64 difference stored as float32) to compact slot first
+// + *at of the row, and the position of its skin entry in the row to the same
 // slot of cskin; it returns the record in *rec and its rank within the pass
 // in *at (-1 for lanes that keep nothing).  Returns the number kept
 // by the pass (the same in every lane).
+template <class First>
 __device__ inline int compact_pass(const CompactArgs& a, int64_t n, int64_t b, int64_t s0,
-                                   int64_t e, int kept, const CentreQ& ci, float4* rec, int* at) {
+                                   int64_t e, const CentreQ& ci, float4* rec, int* at,
+                                   First&& first) {
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t s = s0 + lane;
   bool pred = false;
@@ -103,6 +106,7 @@ __device__ inline int compact_pass(const CompactArgs& a, int64_t n, int64_t b, i
   }
   const uint64_t m = __ballot(pred);
   const int pre = __popcll(m & ((uint64_t(1) << lane) - 1));
+  const int kept = first(__popcll(m));
   *at = -1;
   if (s < e) {
     if (pred) {

@@ -40,7 +40,11 @@ constexpr int kWaves = kTeam / kWave;
 template <class P>
 constexpr int forward_min_waves() { return P::L >= 4 ? 1 : 4; }
 
-template <class P, bool FOLD>
+// Up to kSplitRows centres a row is taken by the four waves of a workgroup
+// (W = 4), a quarter of its entries each, else by one wave: with few centres
+// the chip is mostly idle and a row's passes and edges are one chain of
+// latencies.
+template <class P, bool FOLD, int W>
 __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(ModelDev md, int64_t n,
                                                         const int32_t* __restrict__ typ,
                                                         const int64_t* __restrict__ row_ptr,
@@ -52,6 +56,8 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
   static_assert(P::L < 3 || P::LPE >= (P::L >= 4 ? 9 : 7), "a lane per degree-3/4 component");
   __shared__ float4 pre_all[kWaves][kWave];          // per edge: tau, chi, table row (and pair)
   __shared__ float4 harm_all[kWaves][kWave][kNH / 4];
+  __shared__ float part_all[W > 1 ? W : 1][W > 1 ? P::NS : 1];   // the waves' node states
+  __shared__ int kept_all[kWaves];                               // and edges kept in a round
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int grp = lane / P::LPE;
@@ -69,8 +75,10 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
   const float w4mask = k < 9 ? 1.0f : 0.0f;
   const int m3 = k < 7 ? k : 0, m4 = k < 9 ? k : 0;
 
-  for (int64_t blk = xcd_block(blockIdx.x, gridDim.x); blk * kWaves < n; blk += gridDim.x) {
-    const int64_t i = blk * kWaves + wave;
+  constexpr int kRows = kWaves / W;   // centres of a workgroup
+  static_assert(W == 1 || W == kWaves, "a row per wave or per workgroup");
+  for (int64_t blk = xcd_block(blockIdx.x, gridDim.x); blk * kRows < n; blk += gridDim.x) {
+    const int64_t i = blk * kRows + (W == 1 ? wave : 0);
     if (i >= n) break;
     const int ai = type_of(i);
     const int64_t b = row_ptr[i];
@@ -169,11 +177,30 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
     };
 
     int kept = 0;
-    for (int64_t s0r = b; s0r < e; s0r += kWave) {
+    // entries of a wave in a round: all 64, or an even share of the row
+    const int64_t rounds = (e - b + W * kWave - 1) / (W * kWave);
+    const int64_t share = W == 1 ? kWave : rounds > 0 ? (e - b + W * rounds - 1) / (W * rounds) : 0;
+    for (int64_t rd = b; rd < e; rd += W * share) {
       float4 rec;
       int at;
-      const int np = compact_pass(ca, n, b, s0r, e, kept, ci, &rec, &at);
-      kept += np;
+      const int64_t s0r = rd + (W == 1 ? 0 : wave * share);
+      const int64_t end = W == 1 || s0r + share > e ? e : s0r + share;
+      const int np = compact_pass(ca, n, b, s0r, end, ci, &rec, &at, [&](int m) {
+        int before = kept;
+        if constexpr (W == 1) {
+          kept += m;
+        } else {
+          if (lane == 0) kept_all[wave] = m;
+          __syncthreads();
+          for (int q = 0; q < W; ++q) {
+            const int mq = kept_all[q];
+            if (q < wave) before += mq;
+            kept += mq;
+          }
+          __syncthreads();   // the counts are read before the next round's
+        }
+        return before;
+      });
       // per-edge quantities of the pass's kept edges, in their order; the
       // entries past np get chi = 0, table offset 0 and zero harmonics
       {
@@ -222,7 +249,7 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
       }
       wave_sync();   // the LDS entries are rewritten by the next pass
     }
-    if (lane == 0) ca.ecount[i] = kept;
+    if (lane == 0 && (W == 1 || wave == 0)) ca.ecount[i] = kept;
 
     // combine the groups (fixed xor butterfly over the group index)
 #pragma unroll
@@ -239,7 +266,7 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
       s1 += __shfl_xor(s1, off);
     }
     if (lane < P::LPE) {
-      float* nrow = node + size_t(i) * P::NS;
+      float* nrow = W == 1 ? node + size_t(i) * P::NS : part_all[W == 1 ? 0 : wave];
 #pragma unroll
       for (int j = 0; j < P::CPL; ++j) nrow[P::Y0 + j * P::LPE + k] = acc0[j];
 #pragma unroll
@@ -259,21 +286,39 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
         nrow[1] = s1;
       }
     }
+    if constexpr (W > 1) {   // the waves' sums in their order
+      __syncthreads();
+      for (int t = threadIdx.x; t < P::NS; t += kTeam) {
+        float v = part_all[0][t];
+        for (int q = 1; q < W; ++q) v += part_all[q][t];
+        node[size_t(i) * P::NS + t] = v;
+      }
+      __syncthreads();   // read before the next row's are written
+    }
   }
 }
 
 template <class P>
 int launch(const dpa4c_model* m, int64_t n, const int32_t* species, const int32_t* fidx,
            const int64_t* row_ptr, const CompactArgs& ca, float* node, hipStream_t st) {
-  int64_t blocks = (n + kWaves - 1) / kWaves;   // a wave per centre
+  const bool split = n <= kSplitRows;   // a workgroup per centre, else a wave
+  int64_t blocks = split ? n : (n + kWaves - 1) / kWaves;
   blocks = blocks < 65536 ? blocks : 65536;
   if (blocks < 1) return 0;
-  if (fidx)
-    hipLaunchKernelGGL((forward_kernel<P, true>), dim3(blocks), dim3(kTeam), 0, st, m->dev(), n,
-                       fidx, row_ptr, ca, node);
+  const dim3 grid(static_cast<unsigned>(blocks)), block(kTeam);
+  const int32_t* typ = fidx ? fidx : species;
+  if (fidx && split)
+    hipLaunchKernelGGL((forward_kernel<P, true, kWaves>), grid, block, 0, st, m->dev(), n, typ,
+                       row_ptr, ca, node);
+  else if (fidx)
+    hipLaunchKernelGGL((forward_kernel<P, true, 1>), grid, block, 0, st, m->dev(), n, typ, row_ptr,
+                       ca, node);
+  else if (split)
+    hipLaunchKernelGGL((forward_kernel<P, false, kWaves>), grid, block, 0, st, m->dev(), n, typ,
+                       row_ptr, ca, node);
   else
-    hipLaunchKernelGGL((forward_kernel<P, false>), dim3(blocks), dim3(kTeam), 0, st, m->dev(), n,
-                       species, row_ptr, ca, node);
+    hipLaunchKernelGGL((forward_kernel<P, false, 1>), grid, block, 0, st, m->dev(), n, typ, row_ptr,
+                       ca, node);
   DPA4C_HIP_TRY(hipGetLastError());
   return 0;
 }

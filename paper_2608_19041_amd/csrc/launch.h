@@ -6,6 +6,15 @@
 
 namespace dpa4c {
 
+// Centres up to which a workgroup, not a wave, takes a row of edges: as many as
+// the chip has SIMDs, so that a wave per centre would leave SIMDs idle.
+// Forward and backward of the full model in us, a wave against a workgroup:
+// 108 atoms 16.7 + 14.2 against 9.5 + 6.5, 500 16.2 + 14.0 against 11.0 + 7.8,
+// 864 16.4 + 14.4 against 14.0 + 10.3, 1,372 18.3 + 17.1 against 18.6 + 14.2,
+// 2,048 19.1 + 17.8 against 22.3 + 17.4 (the small model at 1,372 11.4 + 10.0
+// against 12.8 + 9.2).
+constexpr int64_t kSplitRows = 1024;
+
 // host-only checks of a weight blob's header (no device is touched)
 int check_blob_header(const void* blob, size_t nbytes);
 int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out);

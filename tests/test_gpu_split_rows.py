@@ -1,0 +1,49 @@
+"""Rows shared by the waves of a workgroup (few centres) and rows of one wave
+(many), against the float64 oracle and each other, where a row takes several
+rounds: skin rows of more than 256 entries, and more than 256 edges inside the
+cutoff.  The dense cells lie outside the models' calibration, so the repository's
+1e-5 eV and 1e-4 eV/A hold relative to the largest energy and force; between the
+two mappings only the order of float32 sums differs, held to the same.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import model as om
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name,scale,r_list", [("mini", 1.0, 6.0), ("plus", 1.0, 9.5),
+                                               ("plus", 0.62, 7.0), ("plus_l4", 0.62, 6.0)])
+def test_rows_of_several_rounds(name, scale, r_list):
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_2608_19041_amd as dp
+    spec, w = synth.model_weights(name)
+    s = synth.fcc_copper(3, 0.06, seed=5)
+    cell, pos = s.cell * scale, s.pos * scale
+    model = dp.Model(synth.pack_blob(spec, w))
+
+    def run(reps):
+        shifts = np.array([(a, b, c) for a in range(reps[0]) for b in range(reps[1])
+                           for c in range(reps[2])]) @ cell
+        p = torch.tensor((pos[None] + shifts[:, None]).reshape(-1, 3), device="cuda")
+        sp = torch.tensor(np.tile(s.species, len(shifts)), dtype=torch.int32, device="cuda")
+        big = cell * np.array(reps)[:, None]
+        rows = dp.build_neighbors(p, big, s.pbc, r_list)
+        e, f, _, v = model.compute_energy_forces_virial(p, sp, big, s.pbc, 6.0, *rows)[:4]
+        e2, f2, _ = model.compute_energy_forces(p, sp, big, s.pbc, 6.0, *rows)
+        assert torch.equal(e, e2) and torch.equal(f, f2)
+        return e.cpu().numpy(), f.cpu().numpy(), v.cpu().numpy() / len(shifts)
+
+    ref_e, ref_f = om.Oracle(spec, w).energy_forces(pos, s.species, cell, s.pbc)
+    se, sf = max(1.0, np.abs(ref_e).max()), max(1.0, np.abs(ref_f).max())
+    few, many = run((1, 1, 1)), run((2, 3, 4))     # 108 and 2,592 atoms
+    for e, f, _ in (few, many):
+        n = len(e) // len(ref_e)
+        assert np.abs(e - np.tile(ref_e, n)).max() < 1e-5 * se
+        assert np.abs(f - np.tile(ref_f, (n, 1))).max() < 1e-4 * sf
+    # a virial sums 108 x 78 or more products of a force and a vector of up to 6 A
+    assert np.abs(few[2] - many[2]).max() < 1e-4 * sf * 6.0

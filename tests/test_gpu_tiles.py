@@ -4,7 +4,11 @@ The stage takes 16, 32, 48 or 64 atoms a workgroup, whichever leaves the
 fewest rounds, in stretches of at most 65,536 atoms; an atom's E_i and dE/dD
 do not depend on which tile, lane or stretch it falls into.  So
 
-* open clusters of every size around the tile edges equal the oracle, and
+* open clusters of every size around the tile edges equal the oracle, to the
+  repository's 1e-5 eV and 1e-4 eV/A where |E_i| is of the size of 1 eV; their
+  surface atoms lie outside the models' calibration, up to 10 eV, where E_i
+  inherits the relative error that the descriptor is allowed, 15 times the
+  1.8e-7 of the published check, so that is added in units of max |E_i|; and
 * a crystal tiled from one jittered 108-atom cell, at sizes that take every
   workgroup shape and more than one stretch, has the E_i and forces of that
   cell in every copy.  The copies' positions are the cell's plus whole cell
@@ -52,7 +56,8 @@ def test_open_clusters_around_the_tile_edges(dp, name):
         pos, species = s.pos[:n], s.species[:n]
         e, f = evaluate(dp, model, pos, species, s.cell, pbc)
         ref_e, ref_f = oracle.energy_forces(pos, species, s.cell, pbc)
-        assert np.abs(e - ref_e).max() < 1e-5 and np.abs(f - ref_f).max() < 1e-4, n
+        assert np.abs(e - ref_e).max() < 1e-5 + 15 * 1.8e-7 * np.abs(ref_e).max(), n
+        assert np.abs(f - ref_f).max() < 1e-4, n
 
 
 @pytest.mark.parametrize("name,reps", [
