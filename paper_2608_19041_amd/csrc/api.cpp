@@ -235,7 +235,7 @@ struct NvtConfig {
 };
 
 // Everything after the skin list: forward (with the compaction of the skin
-// rows), per-atom kernel, backward, forces and the energy sum, on the
+// rows), readout and MLP, backward, forces and the energy sum, on the
 // buffers ``B``; ``fidx`` is the folded index of every atom (null: the
 // separable tables).  ``record``: the buffers are the model's workspace, so
 // the stages may be timed and the inputs are kept for dpa4c_debug_stages.

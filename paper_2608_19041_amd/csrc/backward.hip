@@ -4,7 +4,7 @@
 //
 // One wavefront per centre (four per 256-thread workgroup, never waiting for
 // each other).  For centre i the wave reads the node-state gradient
-// [dE/dS0, dE/dS1, dE/dY] (from the per-atom kernel), revisits the edges of
+// [dE/dS0, dE/dS1, dE/dY] (from the readout VJP), revisits the edges of
 // row i, recomputes the tabulated radial maps (value and derivative), the
 // pair coefficients and the envelope, and writes
 //     dE/dr_ij = (dE/drho) u + (I - u u^T)(dE/du) / rho,
@@ -56,16 +56,17 @@ namespace {
 constexpr int kTeam = 256;
 constexpr int kWaves = kTeam / kWave;
 
-// Four waves per SIMD for the degree-three variants (121 to 128 registers, none
-// spilled; the virial's get there by themselves); degree four would spill and
-// keeps its natural three.
-template <class P, bool VIR>
-constexpr int backward_min_waves() { return P::L < 4 && !VIR ? 4 : 1; }
+// Four waves per SIMD for the degree-three variants on folded tables (121 to 128
+// registers, none spilled; the virial's get there by themselves), three with the
+// pair coefficients of the separable tables; degree four would spill and keeps
+// its natural three.
+template <class P, bool FOLD, bool VIR>
+constexpr int backward_min_waves() { return P::L < 4 && !VIR ? (FOLD ? 4 : 3) : 1; }
 
 // W = 4 as in the forward kernel: up to kSplitRows centres the four waves of a
 // workgroup share a row.
 template <class P, bool FOLD, bool VIR, int W>
-__global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backward_kernel(ModelDev md, int64_t n,
+__global__ void __launch_bounds__(kTeam, (backward_min_waves<P, FOLD, VIR>())) backward_kernel(ModelDev md, int64_t n,
                                                          const int32_t* __restrict__ typ,
                                                          const int64_t* __restrict__ row_ptr,
                                                          const int32_t* __restrict__ ecount,
@@ -167,6 +168,16 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
     const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * fold_pitch(P::C0, P::CPL)
                                   : md.pair + size_t(ai) * T1 * (P::C0 * P::PW);
 
+    // Separable tables: the coefficients of the lane's channels for the pair of
+    // a_i and the type of the group's last edge.  The edges of a pass are taken
+    // by type, so they are read once for a run of edges: 3 KB of the 6 KB that
+    // an edge streams at full width (13,718 atoms of eight species 328 -> 280
+    // us).  The forward kernel, with less work to cover the loads, gained nothing
+    // from it (287 -> 303 us, three waves on a SIMD instead of five) and reads
+    // them for every edge.
+    float pp[FOLD ? 1 : P::CPL][FOLD ? 1 : P::PW];
+    int pp_of = -1;
+
     // Entry x of the pass's np (compact slot c0 + x of the row): the edge
     // gradient from its LDS entry and, with folded tables, the lane's table
     // entries ``T`` of that edge.
@@ -222,7 +233,19 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
             dq[mu] = __shfl(dqk, mu, P::LPE);
           }
         }
-        const float* pc = pair_base + size_t(aj) * (P::C0 * P::PW);
+        if (aj != pp_of) {
+          const float* pc = pair_base + size_t(aj) * (P::C0 * P::PW);
+#pragma unroll
+          for (int jj = 0; jj < P::CPL; ++jj)
+#pragma unroll
+            for (int v = 0; v < P::PW; v += 2) {
+              const float2 a =
+                  *reinterpret_cast<const float2*>(pc + (jj * P::LPE + k) * P::PW + v);
+              pp[jj][v] = a.x;
+              pp[jj][v + 1] = a.y;
+            }
+          pp_of = aj;
+        }
         const float* gt = md.gtab + size_t(row) * (P::C0 * 6);
 #pragma unroll
         for (int jj = 0; jj < P::CPL; ++jj) {
@@ -230,15 +253,11 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
           load6(gt + (jj * P::LPE + k) * 6, c);
           const float gv = c[0] + c[1] * tau + c[2] * t2 + c[3] * t3 + c[4] * t4 + c[5] * t5;
           const float gd = (c[1] + c[2] * d1 + c[3] * d2 + c[4] * d3 + c[5] * d4) * inv_delta;
-          const float* pp = pc + (jj * P::LPE + k) * P::PW;
-          const float2 gb = *reinterpret_cast<const float2*>(pp);
-          float psi = gb.x * gv + gb.y;
-          float dpsi = gb.x * gd;
+          float psi = pp[jj][0] * gv + pp[jj][1];
+          float dpsi = pp[jj][0] * gd;
           if constexpr (P::R > 0) {
-            const float2 u01 = *reinterpret_cast<const float2*>(pp + 2);
-            const float2 u23 = *reinterpret_cast<const float2*>(pp + 4);
-            psi += u01.x * q[0] + u01.y * q[1] + u23.x * q[2] + u23.y * q[3];
-            dpsi += u01.x * dq[0] + u01.y * dq[1] + u23.x * dq[2] + u23.y * dq[3];
+            psi += pp[jj][2] * q[0] + pp[jj][3] * q[1] + pp[jj][4] * q[2] + pp[jj][5] * q[3];
+            dpsi += pp[jj][2] * dq[0] + pp[jj][3] * dq[1] + pp[jj][4] * dq[2] + pp[jj][5] * dq[3];
           }
           a0 += gy0[jj] * psi;
           b0 += gy0[jj] * dpsi;
@@ -354,12 +373,17 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
                              md.c_inv[1] * (3.0f * t2));
           }
         }
-        geo[lane] = ge;
-        rad[lane] = ra;
-        ids[lane] = id;
-        scl[lane] = sc;
-        cub[lane] = cb;
-        if constexpr (FOLD) wts[lane] = wt;
+        int at = lane;
+        if constexpr (!FOLD) {   // by type, then the entries past the pass
+          const int rank = type_rank(lane < np, id.y);
+          at = lane < np ? rank : lane;
+        }
+        geo[at] = ge;
+        rad[at] = ra;
+        ids[at] = id;
+        scl[at] = sc;
+        cub[at] = cb;
+        if constexpr (FOLD) wts[at] = wt;
       }
       round_sync();
       if constexpr (FOLD) {
@@ -375,7 +399,9 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, VIR>())) backwar
           edge_work(base + G + grp, np, TB);
         }
       } else {
-        for (int base = 0; base < np; base += G) edge_work(base + grp, np, {});
+        // an even share of the pass for every group, one run of types each
+        const int per = (np + G - 1) / G;
+        for (int x = 0; x < per; ++x) edge_work(grp * per + x, np, {});
       }
       wave_sync();
       // every record of the pass was read before its edges ran

@@ -288,6 +288,22 @@ __device__ inline void load6(const float* __restrict__ p, float* c) {
   c[0] = a.x; c[1] = a.y; c[2] = b.x; c[3] = b.y; c[4] = d.x; c[5] = d.y;
 }
 
+// The rank of this lane among the lanes with ``on``, in order of type and then
+// of lane (undefined without).
+__device__ inline int type_rank(bool on, int type) {
+  const uint64_t below = (uint64_t(1) << lane_of()) - 1;
+  uint64_t todo = __ballot(on);
+  int rank = 0, before = 0;
+  while (todo) {
+    const int t = __builtin_amdgcn_readlane(type, __builtin_ctzll(todo));
+    const uint64_t m = __ballot(on && type == t);
+    if (type == t) rank = before + __popcll(m & below);
+    before += __popcll(m);
+    todo &= ~m;
+  }
+  return rank;
+}
+
 // lane 0 of every group of W lanes to all lanes of its group
 template <int W>
 __device__ inline float4 group_bcast(float4 v) {

@@ -8,7 +8,7 @@
 // the harmonics are formed in registers and accumulated into the node state
 // [sum chi^2, sum chi^4, Y_lmc].  Apart from the compacted edge records and
 // their skin positions, no per-edge quantity is written to memory.
-// The readout runs in the per-atom kernel.
+// The readout follows in kernels of its own (readout.hip).
 //
 // Mapping: one wavefront per centre (four centres per 256-thread
 // workgroup; the waves never wait for each other).  The wave takes the skin

@@ -1,6 +1,6 @@
 // Plain fp32 GEMM on the matrix cores (v_mfma_f32_16x16x4_f32) with an
 // optional fused epilogue (bias + SiLU + residual, or residual + product).
-// The energy path uses the per-atom kernel; this one backs the exported
+// The energy path uses mlp_chain.hip; this one backs the exported
 // dpa4c_debug_gemm entry used to check the MFMA operand layout.
 #include <hip/hip_runtime.h>
 
