@@ -54,7 +54,7 @@ struct ListCheck {
   const int32_t* species;
   int n_types1;
   // device scratch for partial pair counts and masks: 8 bytes for each block of
-  // the search (four atoms, at most 4,096 blocks), and from 32 KB on 4 KB more
+  // the search (one atom or four, at most 4,096 blocks), and from 32 KB on 4 KB more
   // when n is above 8,192; the node state, which comes later, has the room
   void* scratch;
   uint32_t* host;   // pinned: uint32 mask[4], int64 row_ptr[n], int64 pairs

@@ -45,6 +45,11 @@ constexpr int kMaxRow = 512;           // longest row the fill kernel ranks in L
 constexpr int kRankBlock = 8;          // keys compared per step of the bucketed rank
 constexpr int kMaxSeg = kWave;         // stencil runs a wave holds at once
 constexpr int64_t kFlagCapacity = 1, kFlagRowTooLong = 2, kFlagShift = 4, kFlagNonFinite = 8;
+// Atoms up to which the four waves of a workgroup search a row: a row's
+// searches are two rounds of a chain of eight loads for one wave.  A wave
+// against a workgroup in us: 108 atoms 11.7, 5.9; 500 11.5, 6.4; 1,372 12.7, 8.9;
+// 2,916 14.0, 15.5; 4,000 15.4, 20.2.
+constexpr int64_t kSplitSearch = 2048;
 constexpr int64_t kPresenceOne = 8192; // atoms whose species one block looks through
 constexpr int kFlagMaxRow = 3;         // flags[3]: the longest row of the last count
 
@@ -994,7 +999,8 @@ __device__ inline bool reverse_search(int64_t n, int32_t i, int64_t s, int32_t j
 // other (13,718 atoms: 176 us of search, 20 without).  With ``order`` (the
 // neighbour build's atom records in bin order) the rows are taken in that
 // spatial order, so that centres searched close in time share their rows j
-// in L2; the results do not depend on the order.
+// in L2; the results do not depend on the order.  With ``parts`` > 1 a row is
+// taken by that many waves, 64 entries each in turn.
 template <bool VEC>
 __global__ void __launch_bounds__(kBlock) skin_rev_kernel(int64_t n, const int64_t* __restrict__ row_ptr,
                                                           const int32_t* __restrict__ nbr_j,
@@ -1003,7 +1009,8 @@ __global__ void __launch_bounds__(kBlock) skin_rev_kernel(int64_t n, const int64
                                                           const int32_t* __restrict__ jsamp,
                                                           int64_t* __restrict__ rev,
                                                           unsigned long long* __restrict__ paired,
-                                                          const CellRec* __restrict__ order) {
+                                                          const CellRec* __restrict__ order,
+                                                          int parts) {
   __shared__ int64_t qs_all[kWavesPerBlock][2 * kWave];
   __shared__ int32_t qi_all[kWavesPerBlock][2 * kWave];
   __shared__ int32_t qj_all[kWavesPerBlock][2 * kWave];   // (j, n) of each queued entry
@@ -1043,11 +1050,13 @@ __global__ void __launch_bounds__(kBlock) skin_rev_kernel(int64_t n, const int64
     wave_local_sync();
     qn = rest;
   };
-  for (int64_t r = xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + w; r < n; r += nwaves) {
+  for (int64_t rp = xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + w; rp < n * parts;
+       rp += nwaves) {
+    const int64_t r = parts == 1 ? rp : rp / parts;
     const int64_t i = order ? order[r].j : r;
     const int64_t b = row_ptr[i], e = row_ptr[i + 1];
     if (!row_ok(b, e, cap)) continue;
-    for (int64_t s0 = b; s0 < e; s0 += kWave) {
+    for (int64_t s0 = b + (rp - r * parts) * kWave; s0 < e; s0 += parts * kWave) {
       const int64_t s = s0 + lane;
       bool canon = false;
       int32_t j = 0, sh = 0;
@@ -1334,15 +1343,17 @@ int launch_skin_rev(const int64_t* row_ptr, const int32_t* nbr_j, const int32_t*
   // the block compare reads 16-byte groups of nbr_j: a list that is not
   // 16-byte aligned takes one load per entry
   const bool vec = (reinterpret_cast<uintptr_t>(nbr_j) & 15) == 0;
+  const int parts = n <= kSplitSearch ? kWavesPerBlock : 1;
+  const int grid = waves_grid(n * parts);
   if (vec)
-    hipLaunchKernelGGL(skin_rev_kernel<true>, dim3(waves_grid(n)), dim3(kBlock), 0, st, n, row_ptr,
-                       nbr_j, nbr_shift, cap, jsamp, skin_rev, pairs, order);
+    hipLaunchKernelGGL(skin_rev_kernel<true>, dim3(grid), dim3(kBlock), 0, st, n, row_ptr, nbr_j,
+                       nbr_shift, cap, jsamp, skin_rev, pairs, order, parts);
   else
-    hipLaunchKernelGGL(skin_rev_kernel<false>, dim3(waves_grid(n)), dim3(kBlock), 0, st, n, row_ptr,
-                       nbr_j, nbr_shift, cap, jsamp, skin_rev, pairs, order);
+    hipLaunchKernelGGL(skin_rev_kernel<false>, dim3(grid), dim3(kBlock), 0, st, n, row_ptr, nbr_j,
+                       nbr_shift, cap, jsamp, skin_rev, pairs, order, parts);
   if (check)
     hipLaunchKernelGGL(list_finish_kernel, dim3(1), dim3(kBlock), 0, st, masks, nmask,
-                       check->species, n, check->n_types1, pairs, waves_grid(n), row_ptr + n,
+                       check->species, n, check->n_types1, pairs, grid, row_ptr + n,
                        check->host);
   DPA4C_HIP_TRY(hipGetLastError());
   return 0;
