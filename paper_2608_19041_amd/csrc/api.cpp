@@ -326,6 +326,7 @@ int dpa4c_model_create(const void* blob, size_t nbytes, int device, dpa4c_model*
   const size_t T1 = size_t((*out)->n_types) + 1;
   if (w.fold_map.ensure(4 * T1) != 0 ||
       hipHostMalloc((void**)&w.fold_host, 64 + 4 * T1, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
     w.fold_host = nullptr;
     set_error("dpa4c_model_create: allocation of the species buffers failed");
     dpa4c_model_destroy(*out);

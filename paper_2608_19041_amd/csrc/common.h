@@ -195,11 +195,13 @@ inline size_t fold_bytes(int rows, int C0, int LPE, int n) {
 void set_error(const std::string& msg);
 
 // a failed HIP call returns DPA4C_ERR_OOM when the device (or pinned host)
-// memory is exhausted, DPA4C_ERR_HIP otherwise
+// memory is exhausted, DPA4C_ERR_HIP otherwise; the runtime's own record of the
+// error is taken with it, or the launch check of the next call would find it
 #define DPA4C_HIP_TRY(expr)                                                      \
   do {                                                                           \
     hipError_t _e = (expr);                                                      \
     if (_e != hipSuccess) {                                                      \
+      (void)hipGetLastError();                                                   \
       ::dpa4c::set_error(std::string(#expr) + ": " + hipGetErrorString(_e));     \
       return _e == hipErrorOutOfMemory ? DPA4C_ERR_OOM : DPA4C_ERR_HIP;          \
     }                                                                            \

@@ -36,6 +36,7 @@ int DevBuf::ensure(size_t want) {
   }
   hipError_t e = hipMalloc(&p, b);
   if (e != hipSuccess) {
+    (void)hipGetLastError();   // reported here, not by the next launch check
     p = nullptr;
     set_error(std::string("hipMalloc of ") + std::to_string(b) + " bytes: " + hipGetErrorString(e));
     return e == hipErrorOutOfMemory ? DPA4C_ERR_OOM : DPA4C_ERR_HIP;

@@ -1,0 +1,119 @@
+"""The library's host code against a stand-in HIP runtime (fake_hip.cpp): which
+buffers reach the kernels after a refused allocation, what is still queued when
+a call returns, and which memory a call works in.  No GPU: the scenarios run in
+a process of their own, where the stand-in takes the place of libamdhip64.
+"""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+OK, OOM = 0, -7   # DPA4C_ERR_OOM
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    from paper_2608_19041_amd import build
+    out = str(tmp_path_factory.mktemp("hip") / "fake_hip.so")
+    subprocess.run([build.HIPCC, "-x", "hip", "--offload-host-only", f"--offload-arch={build.ARCH}",
+                    "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"),
+                    "-o", out], check=True)
+    return out
+
+
+class Host:
+    """The library on the stand-in runtime, called with plain addresses."""
+
+    def __init__(self, runtime):
+        self.rt = ctypes.CDLL(runtime, mode=ctypes.RTLD_GLOBAL)
+        self.lib = ctypes.CDLL(os.path.join(ROOT, "paper_2608_19041_amd", "libdpa4c.so"))
+        self.rt.fake_log.restype = ctypes.c_char_p
+        self.lib.dpa4c_last_error.restype = ctypes.c_char_p
+
+    def log(self):
+        return self.rt.fake_log().decode().splitlines()
+
+    def refuse_from(self, nbytes):
+        self.rt.fake_refuse_from(ctypes.c_size_t(nbytes))
+
+    def device(self, values):
+        """Device memory with these values."""
+        a = np.ascontiguousarray(values)
+        p = ctypes.c_void_p()
+        assert self.rt.hipMalloc(ctypes.byref(p), ctypes.c_size_t(max(a.nbytes, 1))) == 0
+        ctypes.memmove(p, a.ctypes.data, a.nbytes)
+        return p
+
+    def create(self, name, **change):
+        import dataclasses
+        import synth
+        spec, weights = synth.model_weights(name)
+        blob = synth.pack_blob(dataclasses.replace(spec, **change), weights)
+        h = ctypes.c_void_p()
+        rc = self.lib.dpa4c_model_create(blob, ctypes.c_size_t(len(blob)), 0, ctypes.byref(h))
+        return rc, h
+
+    def system(self, species, pairs=None):
+        n = len(species)
+        pairs = 2 * n if pairs is None else pairs
+        s = {"n": n, "pairs": pairs,
+             "pos": self.device(np.zeros((n, 3))), "species": self.device(np.int32(species)),
+             "rows": self.device(np.linspace(0, pairs, n + 1).astype(np.int64)),
+             "j": self.device(np.zeros(pairs, np.int32)),
+             "shift": self.device(np.zeros(pairs, np.int32)),
+             "vel": self.device(np.zeros((n, 3))), "force": self.device(np.zeros((n, 3))),
+             "e": self.device(np.zeros(n)), "etot": self.device(np.zeros(1)),
+             "chain": self.device(np.zeros(6)), "out": self.device(np.zeros((64, 9))),
+             "cell": (ctypes.c_double * 9)(30, 0, 0, 0, 30, 0, 0, 0, 30),
+             "pbc": (ctypes.c_int * 3)(1, 1, 1)}
+        return s
+
+    def energy(self, model, s, call="compute_energy_forces"):
+        return getattr(self.lib, call)(
+            model, s["pos"], s["species"], ctypes.c_int64(s["n"]), s["cell"], s["pbc"],
+            ctypes.c_double(6.0), s["rows"], s["j"], s["shift"], ctypes.c_int64(s["pairs"]), s["e"],
+            s["force"], s["etot"], None)
+
+    def md(self, model, s, steps, nvt=False):
+        mass = (ctypes.c_double * 128)(*([10.0] * 128))
+        d, i64 = ctypes.c_double, ctypes.c_int64
+        rebuilds = i64()
+        head = (model, s["pos"], s["vel"], s["species"], mass, i64(s["n"]), s["cell"], s["pbc"],
+                d(6.0), d(1.0), d(1.0), steps, 0)
+        if nvt:
+            return self.lib.nvt_step(*head, d(300.0), d(100.0), 3, s["chain"], s["out"], s["out"],
+                                     s["out"], s["out"], s["force"], ctypes.byref(rebuilds), None)
+        return self.lib.verlet_step(*head, s["out"], s["out"], s["force"], ctypes.byref(rebuilds),
+                                    None)
+
+
+def refused_allocation_fails_one_call(h):
+    """A call that ran out of memory is refused; the next one is not."""
+    rc, m = h.create("full")
+    assert rc == OK
+    two, five = h.system([28, 12] * 20), h.system([28, 12, 26, 21, 77] * 8)
+    assert h.energy(m, two) == OK
+    h.refuse_from(100 << 20)
+    assert h.energy(m, five) == OOM
+    h.refuse_from(0)
+    assert h.energy(m, two) == OK, h.lib.dpa4c_last_error()
+
+
+SCENARIOS = [refused_allocation_fails_one_call]
+
+
+@pytest.mark.parametrize("name", [f.__name__ for f in SCENARIOS])
+def test_host_path(runtime, name):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), runtime, name],
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    sys.path.insert(0, ROOT)
+    globals()[sys.argv[2]](Host(sys.argv[1]))
