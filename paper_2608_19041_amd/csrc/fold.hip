@@ -152,8 +152,10 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
     } else if (!may_alloc && need > w.ftab.bytes) {
       return 0;        // this call only: separable tables, the folded state kept
     } else {
+      // no set has tables until these are built: a refused allocation has
+      // already given the old ones back
+      m->fold_n = -1;
       DPA4C_TRY(w.ftab.ensure(need));
-      std::memcpy(m->fold_types_mask, mask, sizeof(m->fold_types_mask));
       int32_t* hmap = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(w.fold_host) + 64);
       std::memcpy(hmap, map.data(), 4 * size_t(T1));
       DPA4C_HIP_TRY(hipMemcpyAsync(w.fold_map.p, hmap, 4 * size_t(T1), hipMemcpyHostToDevice, st));
@@ -163,6 +165,7 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
                          make_float2(m->c_scale[0], m->c_scale[1]),
                          w.ftab.as<float>());
       DPA4C_HIP_TRY(hipGetLastError());
+      std::memcpy(m->fold_types_mask, mask, sizeof(m->fold_types_mask));
       m->fold_n = n_used;
     }
   }

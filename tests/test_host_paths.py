@@ -104,7 +104,22 @@ def refused_allocation_fails_one_call(h):
     assert h.energy(m, two) == OK, h.lib.dpa4c_last_error()
 
 
-SCENARIOS = [refused_allocation_fails_one_call]
+def tables_after_a_refused_allocation(h):
+    """Five species' tables do not fit; the two species of before still run."""
+    rc, m = h.create("full")
+    assert rc == OK
+    two, five = h.system([28, 12] * 20), h.system([28, 12, 26, 21, 77] * 8)
+    assert h.energy(m, two) == OK
+    h.refuse_from(100 << 20)
+    assert h.energy(m, five) == OOM
+    h.refuse_from(0)
+    assert h.energy(m, two) == OK
+    log = h.log()
+    assert any("15backward_kernel" in x and x.endswith(" folded") for x in log), "not folded"
+    assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
+
+
+SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation]
 
 
 @pytest.mark.parametrize("name", [f.__name__ for f in SCENARIOS])
