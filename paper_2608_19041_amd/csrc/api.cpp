@@ -177,6 +177,9 @@ void collect_timing(dpa4c_model* m) {
 int ensure_workspace(dpa4c_model* m, int64_t n, int64_t cap) {
   Workspace& w = m->ws;
   const int64_t nn = n < 1 ? 1 : n, cc = cap < 1 ? 1 : cap;
+  // a refused allocation has given a buffer up, and with it the last evaluation
+  const int64_t last = m->last_n;
+  m->last_n = -1;
   DPA4C_TRY(w.ecount.ensure(4 * nn));
   DPA4C_TRY(w.edge.ensure(16 * cc));
   DPA4C_TRY(w.cskin.ensure(4 * cc));
@@ -187,7 +190,9 @@ int ensure_workspace(dpa4c_model* m, int64_t n, int64_t cap) {
   DPA4C_TRY(w.flags.ensure(8 * 8));
   DPA4C_TRY(w.eatom.ensure(8 * nn));
   DPA4C_TRY(w.fidx.ensure(4 * nn));
-  return ensure_mlp_rows(m, nn);
+  DPA4C_TRY(ensure_mlp_rows(m, nn));
+  m->last_n = last;
+  return 0;
 }
 
 // the model workspace as the buffers of an evaluation
@@ -498,6 +503,7 @@ int energy_forces_core(const dpa4c_model* m, const double* pos, const int32_t* s
   if (rc) return rc;
   const bool own = bufs == nullptr;
   if (own) {
+    w.list_valid = false;   // the reverse index will describe the caller's list, or be given up
     rc = ensure_workspace(mm, N, n_pairs);
     if (rc) return rc;
   }
@@ -507,7 +513,6 @@ int energy_forces_core(const dpa4c_model* m, const double* pos, const int32_t* s
     if (rc == 0 && virial) rc = launch_zero_i64(reinterpret_cast<int64_t*>(virial), 9, st);
     return rc;
   }
-  if (own) w.list_valid = false;   // the reverse index now describes the caller's list
   {
     StageScope t(m, kStSkinRev, st, own);
     // the reverse search's samples live in the edge records and the partial
@@ -631,6 +636,10 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
   rc = make_grids();
   if (rc) return rc;
 
+  if (w.list_n != N) {   // growing the list's arrays gives their contents up
+    w.list_valid = false;
+    mm->last_n = -1;
+  }
   // masses on the device
   const int np_tail = tail_partial_count(N);
   DPA4C_TRY(w.flags.ensure(64));
@@ -714,6 +723,7 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
       // 1/8 headroom over the need (plus 16 per atom) before the next
       // reallocation; the per-edge workspace is sized with it
       const int64_t cap = need + need / 8 + 16 * N;
+      w.cap = 0;   // until both arrays are there
       DPA4C_TRY(w.skin_j.ensure(4 * size_t(cap)));
       DPA4C_TRY(w.skin_shift.ensure(4 * size_t(cap)));
       w.cap = cap;

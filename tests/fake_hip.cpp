@@ -26,7 +26,7 @@ std::map<const void*, std::string> g_name;       // kernels
 std::ostringstream g_log;
 std::string g_log_text;
 size_t g_refuse_from = SIZE_MAX, g_free = size_t(200) << 30;
-int g_bad = 0;
+int g_refuse_after = 0, g_bad = 0;
 hipError_t g_last = hipSuccess;
 struct { dim3 grid, block; size_t shm; hipStream_t st; } g_cfg;
 
@@ -57,7 +57,11 @@ bool folded(const std::string& name) { return name[name.find("Lb") + 2] == '1'; 
 
 extern "C" {
 
-void fake_refuse_from(size_t bytes) { g_refuse_from = bytes ? bytes : SIZE_MAX; }
+// refuses requests of ``bytes`` or more (0: none) once ``after`` of them were granted
+void fake_refuse_from(size_t bytes, int after) {
+  g_refuse_from = bytes ? bytes : SIZE_MAX;
+  g_refuse_after = after;
+}
 void fake_free_bytes(size_t bytes) { g_free = bytes; }
 int fake_bad() { return g_bad; }
 const char* fake_log() {
@@ -67,7 +71,7 @@ const char* fake_log() {
 }
 
 hipError_t hipMalloc(void** p, size_t n) {
-  if (n >= g_refuse_from) {
+  if (n >= g_refuse_from && g_refuse_after-- <= 0) {
     g_log << "refused " << n << "\n";
     return g_last = hipErrorOutOfMemory;
   }

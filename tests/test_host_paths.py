@@ -38,8 +38,8 @@ class Host:
     def log(self):
         return self.rt.fake_log().decode().splitlines()
 
-    def refuse_from(self, nbytes):
-        self.rt.fake_refuse_from(ctypes.c_size_t(nbytes))
+    def refuse_from(self, nbytes, after=0):
+        self.rt.fake_refuse_from(ctypes.c_size_t(nbytes), after)
 
     def device(self, values):
         """Device memory with these values."""
@@ -119,7 +119,52 @@ def tables_after_a_refused_allocation(h):
     assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
 
 
-SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation]
+def list_after_a_refused_workspace(h):
+    """The list of the last dynamics call lost its buffers to a larger evaluation."""
+    rc, m = h.create("small")
+    s, large = h.system([28] * 40), h.system([28] * 40, pairs=400000)
+    assert rc == OK and h.md(m, s, 3) == OK
+    h.refuse_from(4 << 20)
+    assert h.energy(m, large) == OOM
+    h.refuse_from(0)
+    h.log()
+    assert h.lib.dpa4c_debug_stages(m, ctypes.c_int64(40), None, None, None, None) != OK
+    assert h.md(m, s, 3) == OK
+    log = h.log()
+    assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
+    assert any("12count_kernel" in x for x in log), "the list was not built again"
+
+
+def list_after_a_refused_larger_system(h):
+    """The rows of the list went to a larger system, which was refused."""
+    rc, m = h.create("small")
+    s, large = h.system([28] * 40), h.system([28] * 200000)
+    assert rc == OK and h.md(m, s, 3) == OK
+    h.refuse_from(1 << 20)
+    assert h.md(m, large, 3) == OOM
+    h.refuse_from(0)
+    h.log()
+    assert h.md(m, s, 3) == OK
+    assert any("12count_kernel" in x for x in h.log()), "the list was not built again"
+
+
+def list_after_a_half_refused_list(h):
+    """Of the two arrays of a larger list the second was refused."""
+    rc, m = h.create("small")
+    s, large = h.system([28] * 1000), h.system([28] * 10000)
+    assert rc == OK and h.md(m, s, 3) == OK
+    entries = 20000 + 20000 // 8 + 16 * 10000   # with the list's head room
+    h.refuse_from(4 * entries, after=1)
+    assert h.md(m, large, 3) == OOM
+    h.refuse_from(0)
+    assert h.md(m, s, 3) == OK
+    log = h.log()
+    assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
+
+
+SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation,
+             list_after_a_refused_workspace, list_after_a_refused_larger_system,
+             list_after_a_half_refused_list]
 
 
 @pytest.mark.parametrize("name", [f.__name__ for f in SCENARIOS])
