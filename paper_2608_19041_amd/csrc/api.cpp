@@ -340,9 +340,10 @@ int dpa4c_model_create(const void* blob, size_t nbytes, int device, dpa4c_model*
   }
   // folded tables of two species (20 MB at full width), so that a program that
   // only ever calls the entry point without allocation reads them too: the
-  // separable tables take four times the bytes an edge
-  if ((*out)->fold_allowed)
-    rc = w.ftab.ensure(fold_bytes((*out)->n_rows, (*out)->C0, (*out)->C[1], kFoldFirstTypes));
+  // separable tables take four times the bytes an edge.  Where they would be
+  // above the limit or there is no memory for them, the model does without.
+  const size_t first = fold_bytes((*out)->n_rows, (*out)->C0, (*out)->C[1], kFoldFirstTypes);
+  if ((*out)->fold_allowed && first <= kMaxFoldBytes) (void)w.ftab.ensure(first);
   if (rc == 0) rc = ensure_mlp_rows(*out, kMlpRowsFirst);
   if (rc == 0) rc = noalloc_setup(device);
   if (rc) {

@@ -162,9 +162,33 @@ def list_after_a_half_refused_list(h):
     assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
 
 
+def creation_without_room_for_tables(h):
+    """A model whose folded tables have no room yet runs on the separable ones."""
+    tables = 4 * 4 * 3000 * (3 * 128 + 32)   # two species at full width
+    h.refuse_from(tables, after=1)           # the parameter block is as large
+    rc, m = h.create("full")
+    assert rc == OK, h.lib.dpa4c_last_error()
+    s = h.system([28, 12] * 20)
+    assert h.energy(m, s, "compute_energy_forces_noalloc") == OK
+    h.refuse_from(0)
+    assert any("backward_kernel" in x and x.endswith(" separable") for x in h.log())
+    assert h.energy(m, s) == OK
+    assert any("backward_kernel" in x and x.endswith(" folded") for x in h.log())
+    assert h.rt.fake_bad() == 0
+
+
+def creation_reserves_only_tables_it_would_use(h):
+    """At this spacing two species' tables are above the limit for any use."""
+    rc, m = h.create("full", delta=1.2e-4)
+    assert rc == OK
+    tables = 4 * 4 * 50000 * (3 * 128 + 32)
+    assert not any(x.startswith("malloc") and int(x.split()[1]) >= tables for x in h.log())
+
+
 SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation,
              list_after_a_refused_workspace, list_after_a_refused_larger_system,
-             list_after_a_half_refused_list]
+             list_after_a_half_refused_list,
+             creation_without_room_for_tables, creation_reserves_only_tables_it_would_use]
 
 
 @pytest.mark.parametrize("name", [f.__name__ for f in SCENARIOS])
