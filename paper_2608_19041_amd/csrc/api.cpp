@@ -954,10 +954,9 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
   if (nvt)
     DPA4C_HIP_TRY(hipMemcpyAsync(nvt->chain, nvt_state, 16 * size_t(nvt->length),
                                  hipMemcpyDeviceToDevice, st));
-  if (!read) {
-    DPA4C_HIP_TRY(hipMemcpyAsync(w.host_flags, flags, 64, hipMemcpyDeviceToHost, st));
-    DPA4C_HIP_TRY(hipStreamSynchronize(st));
-  }
+  if (!read) DPA4C_HIP_TRY(hipMemcpyAsync(w.host_flags, flags, 64, hipMemcpyDeviceToHost, st));
+  // nothing is left queued: the chain state is the caller's when the call returns
+  if (nvt || !read) DPA4C_HIP_TRY(hipStreamSynchronize(st));
   if (n_rebuilds) *n_rebuilds = rebuilds;
   if (nsteps > 0) w.list_steps_since_build = nsteps - 1 - last_build;
   return flags_to_error(w.host_flags[0]);

@@ -185,10 +185,23 @@ def creation_reserves_only_tables_it_would_use(h):
     assert not any(x.startswith("malloc") and int(x.split()[1]) >= tables for x in h.log())
 
 
+def nothing_is_queued_after_the_last_wait(h):
+    """A dynamics call has waited for all it queued, however it ended."""
+    for nvt in (False, True):
+        for steps in (0, 1, 2, 5, 30):
+            rc, m = h.create("small")
+            s = h.system([28] * 40)
+            assert rc == OK and h.md(m, s, steps, nvt) == OK
+            assert h.md(m, s, steps, nvt) == OK      # with the list carried over
+            log = h.log()
+            assert log[-1] == "sync", (nvt, steps, log[-2:])
+
+
 SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation,
              list_after_a_refused_workspace, list_after_a_refused_larger_system,
              list_after_a_half_refused_list,
-             creation_without_room_for_tables, creation_reserves_only_tables_it_would_use]
+             creation_without_room_for_tables, creation_reserves_only_tables_it_would_use,
+             nothing_is_queued_after_the_last_wait]
 
 
 @pytest.mark.parametrize("name", [f.__name__ for f in SCENARIOS])
