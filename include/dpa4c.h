@@ -200,23 +200,23 @@ int compute_energy_forces_virial(const dpa4c_model* model, const double* pos,
  * hipMalloc, hipFree or allocating routine and records no memset.
  *
  * The per-call buffers live in a fixed 64 MiB device array (one per device,
- * held until the process ends) instead of the model's workspace.  They take
+ * held until the process ends) instead of the model's workspace, and the rows
+ * between readout and MLP in one of 32 MiB.  The buffers of the first take
  * 28 bytes per list entry (n_pairs), 8 (S+2) + 8 bytes per atom and about
  * 1 KB more (each array rounded up to 256 bytes): about 12,000 atoms of a
  * dense metal at the full width with a 1 A skin.  A larger input returns
  * DPA4C_ERR_INVALID_ARG before any device work.  Every call on a device
- * shares that device's array, so calls that overlap on one device (other
+ * shares that device's arrays, so calls that overlap on one device (other
  * streams, other threads, other models) race; calls on one stream do not.
  *
  * The pair-folded radial tables are built only inside the allocation the
- * model holds: two species from its creation, more once another call needed
- * them.  With a species set whose tables do not fit it, this call reads the
- * separable tables (the same model, results equal to float32 rounding).  One
- * compute_energy_forces call with the same species beforehand gives this
- * entry point the folded tables.  The model's
- * own workspace, and so the list that verlet_step carries between calls, is
- * untouched (but for the rows its readout and MLP pass between each other,
- * which no call leaves anything in).  Synchronises ``stream`` once (the species present).
+ * model holds: two species from its creation where there was room, more once
+ * another call needed them.  With a species set whose tables do not fit it,
+ * this call reads the separable tables (the same model, results equal to
+ * float32 rounding).  One compute_energy_forces call with the same species
+ * beforehand gives this entry point the folded tables.  The model's own
+ * workspace, and so the list that verlet_step carries between calls, is
+ * untouched.  Synchronises ``stream`` once (the species present).
  */
 int compute_energy_forces_noalloc(const dpa4c_model* model, const double* pos,
                                   const int32_t* species, int64_t N, const double cell[9],

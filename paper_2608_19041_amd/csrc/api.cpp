@@ -206,6 +206,7 @@ EvalBufs ws_bufs(Workspace& w) {
   b.node_grad = w.node_grad.as<float>();
   b.epart = w.epart.as<double>();
   b.fidx = w.fidx.as<int32_t>();
+  b.mid = {w.mlp_buf.as<float>(), w.mlp_rows};
   return b;
 }
 
@@ -265,7 +266,7 @@ int run_model(const dpa4c_model* mc, const double* pos, const int32_t* species, 
   }
   {
     StageScope t(m, kStAtoms, st, record);
-    rc = launch_atoms(m, n, species, B.node, B.node_grad, e_atom, nullptr, st);
+    rc = launch_atoms(m, n, species, B.node, B.node_grad, e_atom, nullptr, B.mid, st);
     if (rc) return rc;
   }
   {
@@ -344,8 +345,7 @@ int dpa4c_model_create(const void* blob, size_t nbytes, int device, dpa4c_model*
   // above the limit or there is no memory for them, the model does without.
   const size_t first = fold_bytes((*out)->n_rows, (*out)->C0, (*out)->C[1], kFoldFirstTypes);
   if ((*out)->fold_allowed && first <= kMaxFoldBytes) (void)w.ftab.ensure(first);
-  if (rc == 0) rc = ensure_mlp_rows(*out, kMlpRowsFirst);
-  if (rc == 0) rc = noalloc_setup(device);
+  rc = noalloc_setup(device);
   if (rc) {
     dpa4c_model_destroy(*out);
     *out = nullptr;
@@ -1013,7 +1013,7 @@ int dpa4c_debug_stages(const dpa4c_model* m, int64_t N, float* node_state, float
   DPA4C_TRY(w.desc.ensure(size_t(4) * N * m->D_out));
   DPA4C_TRY(w.eatom.ensure(size_t(8) * N));
   rc = launch_atoms(m, N, w.last_species, w.node.as<float>(), w.node_grad.as<float>(),
-                    w.eatom.as<double>(), w.desc.as<float>(), st);
+                    w.eatom.as<double>(), w.desc.as<float>(), ws_bufs(w).mid, st);
   if (rc) return rc;
   if (node_state)
     DPA4C_HIP_TRY(hipMemcpyAsync(node_state, w.node.p, 4 * N * (m->S + 2), hipMemcpyDeviceToDevice, st));

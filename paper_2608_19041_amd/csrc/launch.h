@@ -81,11 +81,19 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
 // compaction of every skin row (compact.h) and the forward pass
 int launch_forward(const dpa4c_model* m, int64_t n, const int32_t* species, const int32_t* fidx,
                    const int64_t* row_ptr, const CompactArgs& ca, float* node, hipStream_t st);
+// The rows between the readout and the MLP: ``rows`` atoms, each a row of
+// mlp_width(D_out) floats, then each a float2; ``at`` is 128-byte aligned.
+struct MlpRows {
+  float* at = nullptr;
+  int64_t rows = 0;
+};
+constexpr size_t mlp_row_bytes(int dout) { return 4 * size_t(mlp_width(dout)) + sizeof(float2); }
 // readout, MLP with head and input gradient, readout VJP, in stretches of
-// the atoms that the model's rows hold (Workspace::mlp_rows); desc_out (float
-// [N][D_out]) receives D when not null
+// the atoms that the rows hold; desc_out (float [N][D_out]) receives D when
+// not null
 int launch_atoms(const dpa4c_model* m, int64_t n, const int32_t* species, const float* node,
-                 float* node_grad, double* e_atom, float* desc_out, hipStream_t st);
+                 float* node_grad, double* e_atom, float* desc_out, const MlpRows& mid,
+                 hipStream_t st);
 // the stages of launch_atoms on atoms [0, n) (readout.hip, mlp_chain.hip):
 // rows of mlp_width(D_out) floats and one float2 per atom between them
 int launch_readout(const dpa4c_model* m, int64_t n, const int32_t* species, const float* node,
@@ -106,10 +114,10 @@ int launch_split_weights(const float* w, int K, int N, int sk, int sn, int block
 // kMlpRows goes through them in stretches: 65,536 rows of the full width are
 // 143 MB, which the 256 MB last-level cache holds between the three kernels
 // (1 M copper atoms: 16,384 rows at a time 14.5 ms, 65,536 13.5, 131,072
-// 13.3), and four full rounds of 64-atom workgroups.  kMlpRowsFirst come with the model.
-constexpr int64_t kMlpRows = 65536, kMlpRowsFirst = 4096;
-// grows the rows to what ``n`` atoms can use; where that would leave less
-// than 8 GiB of device memory free the rows stay as they are (more, shorter
+// 13.3), and four full rounds of 64-atom workgroups.
+constexpr int64_t kMlpRows = 65536, kMlpRowsLeast = 4096;
+// grows the model's rows to what ``n`` atoms can use; where that would leave
+// less than 8 GiB of device memory free, to kMlpRowsLeast (more, shorter
 // stretches, the same results), so that the largest systems keep the memory
 int ensure_mlp_rows(dpa4c_model* m, int64_t n);
 // the gradient dE/dr_ij of compact slot c of row i goes to the skin position
@@ -234,6 +242,7 @@ struct EvalBufs {
   float* node_grad;     // float [N][S+2]
   double* epart;        // double [partial_count(N) + 8]
   int32_t* fidx;        // int32 [N]
+  MlpRows mid;          // sized by its owner, not by eval_buf_sizes
 };
 // bytes of each EvalBufs array for N atoms, a list of cap entries and a node
 // state of ns floats per atom, each rounded up to 256 (in struct order)

@@ -507,17 +507,17 @@ int launch_chain(const dpa4c_model* m, int64_t n, const int32_t* species, float*
 
 int ensure_mlp_rows(dpa4c_model* m, int64_t n) {
   Workspace& w = m->ws;
+  const size_t each = mlp_row_bytes(m->D_out);
   int64_t rows = n < kMlpRows ? (n + 63) / 64 * 64 : kMlpRows;
-  if (rows < kMlpRowsFirst) rows = kMlpRowsFirst;
   if (rows <= w.mlp_rows) return 0;
-  const size_t bytes = size_t(rows) * (4 * mlp_width(m->D_out) + sizeof(float2));
-  if (w.mlp_rows > 0) {
+  if (rows > kMlpRowsLeast) {
     size_t free_b = 0, total_b = 0;
     DPA4C_HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-    if (free_b < bytes + (size_t(8) << 30)) return 0;
+    if (free_b < rows * each + (size_t(8) << 30)) rows = kMlpRowsLeast;
+    if (rows <= w.mlp_rows) return 0;
   }
   DevBuf grown;
-  const int rc = grown.ensure(bytes);
+  const int rc = grown.ensure(rows * each);
   if (rc) return w.mlp_rows > 0 ? 0 : rc;
   w.mlp_buf.release();
   w.mlp_buf = grown;
@@ -526,20 +526,20 @@ int ensure_mlp_rows(dpa4c_model* m, int64_t n) {
 }
 
 int launch_atoms(const dpa4c_model* m, int64_t n, const int32_t* species, const float* node,
-                 float* node_grad, double* e_atom, float* desc_out, hipStream_t st) {
+                 float* node_grad, double* e_atom, float* desc_out, const MlpRows& mid,
+                 hipStream_t st) {
   if (n <= 0) return 0;
   if (m->n_layers != 3 || !m->wsplit[0]) {
     set_error("the per-atom kernels need three hidden layers");
     return DPA4C_ERR_UNSUPPORTED;
   }
-  const Workspace& w = m->ws;
-  const int64_t rows = w.mlp_rows;
+  const int64_t rows = mid.rows;
   if (rows <= 0) {
     set_error("no rows between the readout and the MLP");
     return DPA4C_ERR_OOM;
   }
   const int64_t ns = m->S + 2;
-  float* desc = w.mlp_buf.as<float>();
+  float* desc = mid.at;
   float2* meta = reinterpret_cast<float2*>(desc + rows * mlp_width(m->D_out));
   for (int64_t c = 0; c < n; c += rows) {
     const int64_t k = n - c < rows ? n - c : rows;

@@ -77,10 +77,7 @@ struct Workspace {
   // per-atom state
   DevBuf node;          // float [N][NS]
   DevBuf node_grad;     // float [N][NS]: dE/d(node state)
-  // rows between the readout and the MLP: mlp_rows atoms, each a row of
-  // mlp_width(D_out) floats, then each a float2 (kMlpRowsFirst of them from
-  // the model's creation on, so that an evaluation without allocation has
-  // some; grown by ensure_mlp_rows)
+  // rows between the readout and the MLP (MlpRows), grown by ensure_mlp_rows
   DevBuf mlp_buf;
   int64_t mlp_rows = 0;
   DevBuf desc;          // float [N][D_out]: D, written only for stage checks

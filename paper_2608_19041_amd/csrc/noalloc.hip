@@ -5,14 +5,16 @@
 // per-call buffers of an evaluation (compaction maps, edge records, reverse
 // index, node state and its gradient, energy partials, folded species index)
 // live in one file-scope device array of kNoAllocScratchBytes instead of the
-// model's grow-only workspace.  Each device holds its own copy of the array
-// until the process ends.  Its device address is looked up once per device,
-// when the first model is created there, and only that address reaches the
-// kernels.
+// model's grow-only workspace, and the rows that the readout and the MLP pass
+// between each other in a second one (kNoAllocRowBytes: 15,000 atoms at full
+// width, more than fit the first array with their edges; any more go in
+// stretches).  Each device holds its own copy of the arrays until the process
+// ends.  Their device addresses are looked up once per device, when the first
+// model is created there, and only those addresses reach the kernels.
 //
-// Every call on a device shares that device's array and leaves the last
-// call's contents in it; nothing in it needs to start at zero.  Calls
-// that overlap on one device race on the array.
+// Every call on a device shares that device's arrays and leaves the last
+// call's contents in them; nothing in them needs to start at zero.  Calls
+// that overlap on one device race on the arrays.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -26,17 +28,23 @@ namespace dpa4c {
 namespace {
 
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
+constexpr size_t kNoAllocRowBytes = size_t(32) << 20;
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+__device__ __align__(256) unsigned char mlp_scratch[kNoAllocRowBytes];
 
+struct Scratch {
+  void* base = nullptr;
+  void* rows = nullptr;
+};
 std::mutex g_scratch_lock;
-void* g_scratch_ptr[kMaxDevices] = {};
+Scratch g_scratch[kMaxDevices];
 
-void* scratch_of(int device) {
-  if (device < 0 || device >= kMaxDevices) return nullptr;
+Scratch scratch_of(int device) {
+  if (device < 0 || device >= kMaxDevices) return {};
   std::lock_guard<std::mutex> lock(g_scratch_lock);
-  return g_scratch_ptr[device];
+  return g_scratch[device];
 }
 
 }  // namespace
@@ -47,15 +55,16 @@ int noalloc_setup(int device) {
     return DPA4C_ERR_UNSUPPORTED;
   }
   std::lock_guard<std::mutex> lock(g_scratch_lock);
-  if (g_scratch_ptr[device]) return 0;
-  void* p = nullptr;
-  const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-  if (e != hipSuccess || !p) {
+  if (g_scratch[device].base) return 0;
+  Scratch s;
+  hipError_t e = hipGetSymbolAddress(&s.base, HIP_SYMBOL(scratch));
+  if (e == hipSuccess) e = hipGetSymbolAddress(&s.rows, HIP_SYMBOL(mlp_scratch));
+  if (e != hipSuccess || !s.base || !s.rows) {
     set_error(std::string("hipGetSymbolAddress of the no-allocation scratch: ") +
               hipGetErrorString(e));
     return DPA4C_ERR_HIP;
   }
-  g_scratch_ptr[device] = p;
+  g_scratch[device] = s;
   return 0;
 }
 
@@ -74,7 +83,8 @@ extern "C" int compute_energy_forces_noalloc(const dpa4c_model* m, const double*
     set_error("compute_energy_forces_noalloc: bad pointer or size");
     return DPA4C_ERR_INVALID_ARG;
   }
-  unsigned char* base = static_cast<unsigned char*>(scratch_of(m->device));
+  const Scratch s = scratch_of(m->device);
+  unsigned char* base = static_cast<unsigned char*>(s.base);
   if (!base) {
     set_error("compute_energy_forces_noalloc: no scratch on the model's device");
     return DPA4C_ERR_INVALID_ARG;
@@ -105,6 +115,7 @@ extern "C" int compute_energy_forces_noalloc(const dpa4c_model* m, const double*
   b.node_grad = reinterpret_cast<float*>(take(5));
   b.epart = reinterpret_cast<double*>(take(6));
   b.fidx = reinterpret_cast<int32_t*>(take(7));
+  b.mid = {static_cast<float*>(s.rows), int64_t(kNoAllocRowBytes / mlp_row_bytes(m->D_out))};
   return energy_forces_core(m, pos, species, N, cell, pbc, r_c, row_ptr, nbr_j, nbr_shift, n_pairs,
                             e_atom, forces, e_total, nullptr, nullptr, &b, stream);
 }

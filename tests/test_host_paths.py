@@ -197,11 +197,25 @@ def nothing_is_queued_after_the_last_wait(h):
             assert log[-1] == "sync", (nvt, steps, log[-2:])
 
 
+def noalloc_works_outside_the_workspace(h):
+    """The no-allocation call's rows are the device's own, and hold its atoms at once."""
+    rc, m = h.create("full")
+    s, many = h.system([28, 12] * 20), h.system([28, 12] * 6000)
+    assert rc == OK and h.energy(m, s) == OK
+    rows = lambda log: [x.split(" rows ")[1] for x in log if " rows " in x]  # noqa: E731
+    assert rows(h.log()) == ["MM atoms 40", "MM", "M"]
+    for x in (s, many):
+        assert h.energy(m, x, "compute_energy_forces_noalloc") == OK, h.lib.dpa4c_last_error()
+        log = h.log()
+        assert rows(log) == [f"VV atoms {x['n']}", "VV", "V"], rows(log)
+        assert not any(y.startswith(("malloc", "free", "memset")) for y in log)
+
+
 SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation,
              list_after_a_refused_workspace, list_after_a_refused_larger_system,
              list_after_a_half_refused_list,
              creation_without_room_for_tables, creation_reserves_only_tables_it_would_use,
-             nothing_is_queued_after_the_last_wait]
+             nothing_is_queued_after_the_last_wait, noalloc_works_outside_the_workspace]
 
 
 @pytest.mark.parametrize("name", [f.__name__ for f in SCENARIOS])
