@@ -254,19 +254,20 @@ __device__ __forceinline__ void row_forward(RowFwd<P>& f, const RowLane<P>& k, c
   f.i1 = 1.0f / f.m1;
   using T = RowTable<P>;
 #pragma unroll
-  for (int m = 0; m < 3; ++m) f.xt1[m] = y1[m];
+  for (int m = 0; m < 3; ++m) f.xt1[m] = 0.0f;
 #pragma unroll
-  for (int m = 0; m < 5; ++m) f.xt2[m] = y2[m];
+  for (int m = 0; m < 5; ++m) f.xt2[m] = 0.0f;
   row_product<P::C1>(f.xt1, y1, tab, T::kW1, k.l);
   row_product<P::C2>(f.xt2, y2, tab, T::kW2, k.l);
+  // (I + W) y as y + (W y): the small sum rounds at its own size
 #pragma unroll
   for (int m = 0; m < 3; ++m) {
-    f.xt1[m] *= f.i1;
+    f.xt1[m] = (y1[m] + f.xt1[m]) * f.i1;
     f.z1[m] = P::kHasA1 ? 0.0f : f.xt1[m];
   }
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    f.xt2[m] *= f.i1;
+    f.xt2[m] = (y2[m] + f.xt2[m]) * f.i1;
     f.z2[m] = 0.0f;
   }
   if constexpr (P::L >= 3) {
@@ -684,13 +685,17 @@ __device__ __forceinline__ void row_vjp(const RowFwd<P>& f, const RowLane<P>& k,
   });
 #pragma unroll
   for (int m = 0; m < 5; ++m) formed(gx2[m]);
-  // through the alignment (I + W)
+  // through the alignment (I + W), W's share summed by itself
 #pragma unroll
-  for (int m = 0; m < 3; ++m) xb1[m] = gx1[m];
+  for (int m = 0; m < 3; ++m) xb1[m] = 0.0f;
 #pragma unroll
-  for (int m = 0; m < 5; ++m) xb2[m] = gx2[m];
+  for (int m = 0; m < 5; ++m) xb2[m] = 0.0f;
   row_product<P::C1>(xb1, gx1, tab, T::kW1T, k.l);
   row_product<P::C2>(xb2, gx2, tab, T::kW2T, k.l);
+#pragma unroll
+  for (int m = 0; m < 3; ++m) xb1[m] += gx1[m];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) xb2[m] += gx2[m];
 }
 
 }  // namespace dpa4c

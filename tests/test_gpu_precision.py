@@ -1,0 +1,79 @@
+"""What the stages of an evaluation lose against 64 bits, each from its own
+float32 inputs, so that no stage hides behind another: the readout from the node
+state, the MLP from the descriptor.  Errors are 2-norms over all atoms of eight
+jittered systems; the bounds are what plain float32 kernels (a sum over lanes in
+order for the readout, v_mfma_f32_16x16x4_f32 for the MLP) reach on the same
+systems, with a few percent for another order of sums: the eight seeds' own
+spread is 2 to 4 percent.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import model as om
+
+pytestmark = pytest.mark.gpu
+F64 = torch.float64
+
+
+def system(kind, seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    lattice, a, reps = {"cluster": ("fcc", 3.615, (5, 7, 5)), "fcc": ("fcc", 3.615, (6, 6, 6)),
+                        "bcc": ("bcc", 2.87, (6, 7, 7))}[kind]
+    pos, cell = synth.lattice(lattice, a, reps)
+    pos = pos + rng.normal(0.0, 0.07, pos.shape)
+    types = np.array([28, 12, 26] if kind == "bcc" else [28], np.int32)
+    species = types[rng.integers(0, len(types), len(pos))].astype(np.int32)
+    pbc = np.zeros(3, np.int32) if kind == "cluster" else np.ones(3, np.int32)
+    return pos, species, cell, pbc
+
+
+def stage_errors(dp, name, kind, seeds=range(1, 9)):
+    """(relative error of D from the node state, rms error of E_i from D in eV)"""
+    spec, w = synth.model_weights(name)
+    oracle = om.Oracle(spec, w)
+    model = dp.Model(synth.pack_blob(spec, w))
+    d2 = ref2 = e2 = n = 0.0
+    for seed in seeds:
+        pos, species, cell, pbc = system(kind, seed)
+        p = torch.tensor(pos, dtype=F64, device="cuda")
+        s = torch.tensor(species, dtype=torch.int32, device="cuda")
+        e, _, _ = model.compute_energy_forces(p, s, cell, pbc, 6.0,
+                                              *dp.build_neighbors(p, cell, pbc, 6.0))
+        node, desc, _ = model.debug_stages(len(pos))
+        torch.cuda.synchronize()
+        node, desc = node.cpu().double(), desc.cpu().double()
+        M0, M1 = torch.sqrt(0.25 + node[:, 0]), torch.sqrt(0.25 + node[:, 1])
+        X, at = [], 2
+        for l, c in enumerate(oracle.C[: spec.L + 1]):
+            k = (2 * l + 1) * c
+            X.append(node[:, at: at + k].reshape(len(pos), 2 * l + 1, c)
+                     / (M0 if l == 0 else M1)[:, None, None])
+            at += k
+        D = oracle.descriptor({"X": X, "M0": M0, "M1": M1}, species)[1]
+        E = oracle.mlp_energy(desc, species)
+        d2 += float(((desc - D) ** 2).sum())
+        ref2 += float((D ** 2).sum())
+        e2 += float(((e.cpu() - E) ** 2).sum())
+        n += len(pos)
+    return (d2 / ref2) ** 0.5, (e2 / n) ** 0.5
+
+
+@pytest.fixture(scope="module")
+def dp():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_2608_19041_amd as m
+    m.library()
+    return m
+
+
+@pytest.mark.parametrize("name,kind,bound", [
+    ("small", "cluster", 1.985e-7), ("nano", "cluster", 1.039e-7), ("mini", "bcc", 0.785e-7),
+    ("neo", "cluster", 1.283e-7), ("air", "cluster", 1.748e-7), ("full", "bcc", 1.469e-7),
+    ("plus_l4", "cluster", 2.236e-7)])
+def test_readout_from_the_node_state(dp, name, kind, bound):
+    error = stage_errors(dp, name, kind)[0]
+    print(f"{name} {kind}: {error:.3e} of |D|", flush=True)
+    assert error <= 1.05 * bound
