@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(64 * NW, 2)
   constexpr int DT = KP / 16;                 // feature tiles of dE/dD
   constexpr int KBD = KP / 32, KBF = F / 32;
   __shared__ __align__(16) _Float16 act[2 * PL];
-  __shared__ float epart[NW][R];
+  __shared__ double epart[NW][R];
   __shared__ __align__(16) float vec[4][F];   // b1, b2, b3, w
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
@@ -318,24 +318,26 @@ __global__ void __launch_bounds__(64 * NW, 2)
       }
     }
     if (layer == 2) {
-      // head: fixed-order sums over this wave's features
+      // head: fixed-order sums over this wave's features; from the lanes' shares
+      // on in 64 bits, since those sums are of the size of E itself
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        part[r] += __shfl_xor(part[r], 16);
-        part[r] += __shfl_xor(part[r], 32);
-        if (grp == 0) epart[wave][r * 16 + col] = part[r];
+        double sum = part[r];
+        sum += __shfl_xor(sum, 16);
+        sum += __shfl_xor(sum, 32);
+        if (grp == 0) epart[wave][r * 16 + col] = sum;
       }
     }
     __syncthreads();
   }
   for (int i = threadIdx.x; i < R; i += 64 * NW) {
     if (row0 + i < n) {
-      float e = epart[0][i];
+      double e = epart[0][i];
 #pragma unroll
       for (int w = 1; w < NW; ++w) e += epart[w][i];
       int a = species[row0 + i];
       a = static_cast<unsigned>(a) < static_cast<unsigned>(p.n_types1) ? a : p.n_types1 - 1;
-      e_atom[row0 + i] = double(e) + double(p.b_head) + double(p.E_ref[a]);
+      e_atom[row0 + i] = e + double(p.b_head) + double(p.E_ref[a]);
     }
   }
   // dE/dD: ND whole feature tiles for each wave, and what is left of them in

@@ -77,3 +77,14 @@ def test_readout_from_the_node_state(dp, name, kind, bound):
     error = stage_errors(dp, name, kind)[0]
     print(f"{name} {kind}: {error:.3e} of |D|", flush=True)
     assert error <= 1.05 * bound
+
+
+@pytest.mark.parametrize("name,kind,bound", [
+    ("small", "cluster", 9.42e-8), ("nano", "bcc", 6.80e-9), ("mini", "cluster", 4.08e-8),
+    ("neo", "bcc", 1.911e-8), ("air", "fcc", 7.02e-9), ("air", "cluster", 8.11e-8),
+    ("full", "fcc", 8.21e-9), ("full", "bcc", 2.284e-8), ("full", "cluster", 1.115e-7),
+    ("plus_l4", "fcc", 8.84e-9), ("plus_l4", "cluster", 1.066e-7)])
+def test_mlp_from_the_descriptor(dp, name, kind, bound):
+    error = stage_errors(dp, name, kind)[1]
+    print(f"{name} {kind}: {error:.3e} eV", flush=True)
+    assert error <= 1.03 * bound
