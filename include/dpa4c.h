@@ -319,6 +319,13 @@ int dpa4c_debug_stages(const dpa4c_model* model, int64_t N, float* node_state,
                        float* descriptor, int32_t* edge_count, void* stream);
 
 /*
+ * The MLP's input gradient dE_i/dD of the same evaluation, likewise for
+ * stage-by-stage checks: gradient float32 [N][D_out].  Synchronous on
+ * ``stream``.
+ */
+int dpa4c_debug_gradient(const dpa4c_model* model, int64_t N, float* gradient, void* stream);
+
+/*
  * Per-stage timing.  For every stage s whose bit (1 << s) is set in
  * ``stage_mask`` (0: none, -1: all), the library records HIP events around
  * the kernels of that stage on the caller's stream and accumulates their

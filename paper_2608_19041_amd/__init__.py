@@ -60,6 +60,7 @@ def library():
             "nvt_step": (i32, [vp, vp, vp, vp, vp, i64, vp, vp, dbl, dbl, dbl, i32, i32, dbl, dbl,
                                i32, vp, vp, vp, vp, vp, vp, ctypes.POINTER(i64), vp]),
             "dpa4c_debug_stages": (i32, [vp, i64, vp, vp, vp, vp]),
+            "dpa4c_debug_gradient": (i32, [vp, i64, vp, vp]),
             "dpa4c_set_timing": (i32, [vp, i64]),
             "dpa4c_get_timings": (i32, [vp, vp, vp, i32]),
             "dpa4c_stage_name": (ctypes.c_char_p, [i32]),
@@ -78,7 +79,7 @@ def exported_symbols() -> list[str]:
     return ["dpa4c_model_create", "dpa4c_model_destroy", "dpa4c_model_info", "build_neighbors",
             "compute_energy_forces", "compute_energy_forces_virial",
             "compute_energy_forces_noalloc", "verlet_step", "nvt_step",
-            "dpa4c_debug_stages", "dpa4c_set_timing",
+            "dpa4c_debug_stages", "dpa4c_debug_gradient", "dpa4c_set_timing",
             "dpa4c_get_timings", "dpa4c_stage_name", "dpa4c_debug_gemm", "dpa4c_last_error"]
 
 
@@ -351,6 +352,13 @@ class Model:
         _check(library().dpa4c_debug_stages(self._h, n, _ptr(node), _ptr(desc), _ptr(cnt),
                                             _stream(stream)))
         return node, desc, cnt
+
+    def debug_gradient(self, n, stream=None):
+        import torch
+        grad = torch.empty(n, self.info["D_out"], dtype=torch.float32,
+                           device=torch.device("cuda", self.device))
+        _check(library().dpa4c_debug_gradient(self._h, n, _ptr(grad), _stream(stream)))
+        return grad
 
     def set_timing(self, on=True):
         """True: time every stage; False: none; a list of stage names: those."""

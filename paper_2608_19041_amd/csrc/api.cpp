@@ -1,6 +1,7 @@
 // C-ABI entry points of the DPA4C library (declared in include/dpa4c.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -962,6 +963,54 @@ int dynamics(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
   return flags_to_error(w.host_flags[0]);
 }
 
+// the stages of the last evaluation, recomputed for checks
+int debug_stages(const dpa4c_model* m, int64_t N, float* node_state, float* descriptor,
+                 int32_t* edge_count, float* gradient, void* stream) {
+  if (!m || N < 0 || N != m->last_n || !m->ws.last_species) {
+    set_error("dpa4c_debug_stages: N must match the last evaluation on this model");
+    return DPA4C_ERR_INVALID_ARG;
+  }
+  DeviceGuard guard(m->device);
+  dpa4c_model* mm = const_cast<dpa4c_model*>(m);
+  std::lock_guard<std::mutex> lock(mm->mu_lock);
+  Workspace& w = mm->ws;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (N == 0) return 0;
+  // recompute node state and descriptor from the stored compacted edges
+  const CompactArgs ca = compact_args(w.last_grid, w.last_pos, w.skin_j_used, w.skin_shift_used,
+                                      qfix_host(m->r_c), w.cap_used, ws_bufs(w));
+  int rc = launch_forward(m, N, w.last_species, w.last_fidx, w.skin_row_used, ca,
+                          w.node.as<float>(), st);
+  if (rc) return rc;
+  DPA4C_TRY(w.desc.ensure(size_t(4) * N * m->D_out));
+  DPA4C_TRY(w.eatom.ensure(size_t(8) * N));
+  rc = launch_atoms(m, N, w.last_species, w.node.as<float>(), w.node_grad.as<float>(),
+                    w.eatom.as<double>(), w.desc.as<float>(), ws_bufs(w).mid, st);
+  if (rc) return rc;
+  if (gradient) {   // the rows hold dE/dD between the MLP and the readout's VJP
+    const MlpRows mid = ws_bufs(w).mid;
+    const size_t pitch = 4 * size_t(mlp_width(m->D_out)), width = 4 * size_t(m->D_out);
+    float2* meta = reinterpret_cast<float2*>(mid.at + mid.rows * mlp_width(m->D_out));
+    for (int64_t c = 0; c < N; c += mid.rows) {
+      const int64_t k = std::min(N - c, mid.rows);
+      DPA4C_TRY(launch_readout(m, k, w.last_species + c, w.node.as<float>() + c * (m->S + 2), mid.at,
+                               meta, nullptr, st));
+      DPA4C_TRY(launch_chain(m, k, w.last_species + c, mid.at, meta, w.eatom.as<double>() + c, st));
+      DPA4C_HIP_TRY(hipMemcpy2DAsync(gradient + c * m->D_out, width, mid.at, pitch, width, size_t(k),
+                                     hipMemcpyDeviceToDevice, st));
+    }
+  }
+  if (node_state)
+    DPA4C_HIP_TRY(hipMemcpyAsync(node_state, w.node.p, 4 * N * (m->S + 2), hipMemcpyDeviceToDevice, st));
+  if (descriptor)
+    DPA4C_HIP_TRY(hipMemcpyAsync(descriptor, w.desc.p, size_t(4) * N * m->D_out,
+                                 hipMemcpyDeviceToDevice, st));
+  if (edge_count)
+    DPA4C_HIP_TRY(hipMemcpyAsync(edge_count, w.ecount.p, 4 * N, hipMemcpyDeviceToDevice, st));
+  DPA4C_HIP_TRY(hipStreamSynchronize(st));
+  return 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -994,36 +1043,11 @@ int nvt_step(const dpa4c_model* m, double* pos, double* vel, const int32_t* spec
 
 int dpa4c_debug_stages(const dpa4c_model* m, int64_t N, float* node_state, float* descriptor,
                        int32_t* edge_count, void* stream) {
-  if (!m || N < 0 || N != m->last_n || !m->ws.last_species) {
-    set_error("dpa4c_debug_stages: N must match the last evaluation on this model");
-    return DPA4C_ERR_INVALID_ARG;
-  }
-  DeviceGuard guard(m->device);
-  dpa4c_model* mm = const_cast<dpa4c_model*>(m);
-  std::lock_guard<std::mutex> lock(mm->mu_lock);
-  Workspace& w = mm->ws;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (N == 0) return 0;
-  // recompute node state and descriptor from the stored compacted edges
-  const CompactArgs ca = compact_args(w.last_grid, w.last_pos, w.skin_j_used, w.skin_shift_used,
-                                      qfix_host(m->r_c), w.cap_used, ws_bufs(w));
-  int rc = launch_forward(m, N, w.last_species, w.last_fidx, w.skin_row_used, ca,
-                          w.node.as<float>(), st);
-  if (rc) return rc;
-  DPA4C_TRY(w.desc.ensure(size_t(4) * N * m->D_out));
-  DPA4C_TRY(w.eatom.ensure(size_t(8) * N));
-  rc = launch_atoms(m, N, w.last_species, w.node.as<float>(), w.node_grad.as<float>(),
-                    w.eatom.as<double>(), w.desc.as<float>(), ws_bufs(w).mid, st);
-  if (rc) return rc;
-  if (node_state)
-    DPA4C_HIP_TRY(hipMemcpyAsync(node_state, w.node.p, 4 * N * (m->S + 2), hipMemcpyDeviceToDevice, st));
-  if (descriptor)
-    DPA4C_HIP_TRY(hipMemcpyAsync(descriptor, w.desc.p, size_t(4) * N * m->D_out,
-                                 hipMemcpyDeviceToDevice, st));
-  if (edge_count)
-    DPA4C_HIP_TRY(hipMemcpyAsync(edge_count, w.ecount.p, 4 * N, hipMemcpyDeviceToDevice, st));
-  DPA4C_HIP_TRY(hipStreamSynchronize(st));
-  return 0;
+  return debug_stages(m, N, node_state, descriptor, edge_count, nullptr, stream);
+}
+
+int dpa4c_debug_gradient(const dpa4c_model* m, int64_t N, float* gradient, void* stream) {
+  return debug_stages(m, N, nullptr, nullptr, nullptr, gradient, stream);
 }
 
 int dpa4c_set_timing(dpa4c_model* m, int64_t stage_mask) {

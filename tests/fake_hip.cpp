@@ -100,6 +100,10 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
   g_log << "copy " << n << "\n";
   return hipSuccess;
 }
+hipError_t hipMemcpy2DAsync(void*, size_t, const void*, size_t, size_t, size_t, hipMemcpyKind,
+                            hipStream_t) {
+  return hipSuccess;   // of the stage checks only
+}
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
   memset(d, v, n);
   g_log << "memset " << n << "\n";

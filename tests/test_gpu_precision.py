@@ -39,8 +39,8 @@ def stage_errors(dp, name, kind, seeds=range(1, 9)):
         pos, species, cell, pbc = system(kind, seed)
         p = torch.tensor(pos, dtype=F64, device="cuda")
         s = torch.tensor(species, dtype=torch.int32, device="cuda")
-        e, _, _ = model.compute_energy_forces(p, s, cell, pbc, 6.0,
-                                              *dp.build_neighbors(p, cell, pbc, 6.0))
+        rows = dp.build_neighbors(p, cell, pbc, 6.0)   # the stages read them again
+        e, _, _ = model.compute_energy_forces(p, s, cell, pbc, 6.0, *rows)
         node, desc, _ = model.debug_stages(len(pos))
         torch.cuda.synchronize()
         node, desc = node.cpu().double(), desc.cpu().double()
@@ -88,3 +88,52 @@ def test_mlp_from_the_descriptor(dp, name, kind, bound):
     error = stage_errors(dp, name, kind)[1]
     print(f"{name} {kind}: {error:.3e} eV", flush=True)
     assert error <= 1.03 * bound
+
+
+def gradient_errors(dp, name, kind, seeds=(1, 2, 3)):
+    """Relative errors of dE/dD from the descriptor: this library's, plain float32's."""
+    spec, w = synth.model_weights(name)
+    oracle = om.Oracle(spec, w)
+    model = dp.Model(synth.pack_blob(spec, w))
+
+    def plain(D, dtype):   # the MLP and its adjoint with torch's products
+        th = {k: torch.tensor(v, dtype=dtype, device="cuda") for k, v in w.items()
+              if k.startswith(("Theta", "b1", "b2", "b3", "w_head"))}
+        h, pre = D.to(dtype), []
+        for t in (1, 2, 3):
+            pre.append(h @ th[f"Theta{t}"] + th[f"b{t}"])
+            out = torch.nn.functional.silu(pre[-1])
+            h = out + h if t > 1 else out
+        g = th["w_head"].reshape(1, -1).expand(len(D), -1)
+        for t in (3, 2, 1):
+            s = torch.sigmoid(pre[t - 1])
+            p = (g * s * (1 + pre[t - 1] * (1 - s))) @ th[f"Theta{t}"].T
+            g = g + p if t > 1 else p
+        return g
+
+    ours = theirs = ref2 = 0.0
+    for seed in seeds:
+        pos, species, cell, pbc = system(kind, seed)
+        p = torch.tensor(pos, dtype=F64, device="cuda")
+        s = torch.tensor(species, dtype=torch.int32, device="cuda")
+        rows = dp.build_neighbors(p, cell, pbc, 6.0)
+        model.compute_energy_forces(p, s, cell, pbc, 6.0, *rows)
+        desc = model.debug_stages(len(pos))[1]
+        ref = plain(desc, F64)
+        if seed == seeds[0]:   # the reference itself against the oracle
+            d = desc[:5].cpu().double().requires_grad_()
+            oracle.mlp_energy(d, species[:5]).sum().backward()
+            assert torch.allclose(d.grad, ref[:5].cpu(), rtol=1e-10, atol=1e-12)
+        ours += float(((model.debug_gradient(len(pos)) - ref) ** 2).sum())
+        theirs += float(((plain(desc, torch.float32) - ref) ** 2).sum())
+        ref2 += float((ref ** 2).sum())
+    return (ours / ref2) ** 0.5, (theirs / ref2) ** 0.5
+
+
+@pytest.mark.parametrize("name", ["small", "nano", "mini", "neo", "air", "full", "plus_l4"])
+@pytest.mark.parametrize("kind", ["fcc", "cluster"])
+def test_mlp_gradient_from_the_descriptor(dp, name, kind):
+    """The split float16 products of the input gradient against torch's float32 ones."""
+    ours, theirs = gradient_errors(dp, name, kind)
+    print(f"{name} {kind}: {ours:.3e} of |dE/dD|, plain float32 {theirs:.3e}", flush=True)
+    assert ours <= theirs
