@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, FOLD, VIR>())) b
     const int cnt = ecount[i];
     if (VIR && k == 0)
       for (int c = 0; c < 9; ++c) wv[grp][c] = 0.0;
-    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * fold_pitch(P::C0, P::CPL)
+    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * (md.n_rows + 1) * fold_pitch(P::C0, P::CPL)
                                   : md.pair + size_t(ai) * T1 * (P::C0 * P::PW);
 
     // Separable tables: the coefficients of the lane's channels for the pair of
@@ -334,12 +334,12 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, FOLD, VIR>())) b
           const EdgeGeom g = edge_geom(rec.x, rec.y, rec.z);
           float chi, dchi, tau;
           envelope(g.rho, md.inv_rc, &chi, &dchi);
-          const int row = table_row(g.rho, inv_delta, md.n_rows, &tau);
+          const int row = table_row<FOLD>(g.rho, inv_delta, md.n_rows, &tau);
           const int j = __float_as_int(rec.w);
           const int aj = type_of(j);
           ge = make_float4(g.ux, g.uy, g.uz, g.inv_rho);
           ra = make_float4(tau, chi, dchi,
-                           FOLD ? __uint_as_float(fold_offset<P::C0, P::CPL>(aj * md.n_rows + row))
+                           FOLD ? __uint_as_float(fold_offset<P::C0, P::CPL>(aj * (md.n_rows + 1) + row))
                                 : __int_as_float(row));
           id = make_int2(j, aj);
           const float x_ = g.ux, y = g.uy, z = g.uz;

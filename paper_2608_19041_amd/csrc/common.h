@@ -148,7 +148,8 @@ constexpr int kCouplings4 = kO444 + kC444;
 constexpr int couplings_for(int L) { return L >= 4 ? kCouplings4 : (L >= 3 ? kCouplings : 0); }
 
 struct ModelDev {
-  // radial table: g rows [n_rows][CPL][LPE][6], q rows [n_rows][R][6]
+  // radial table, a quintic for each of n_rows intervals: g rows
+  // [n_rows][CPL][LPE][6], q rows [n_rows][R][6]
   const float* gtab;
   const float* qtab;
   int n_rows;
@@ -168,7 +169,7 @@ struct ModelDev {
   const float* E_ref;       // [T+1]
   const float* row_tab;     // per-lane tables of the readout (readout_row.h)
   // pair-folded tables (fold.hip), used when fold_n > 0:
-  // [fold_n^2 pairs][n_rows] rows of fold_pitch words in the order of
+  // [fold_n^2 pairs][n_rows + 1] rows of fold_pitch words in the order of
   // load_fold_row, pair (fa, fb) at fa * fold_n + fb; c_inv = the inverse
   // scales of the float16 c2, c3
   const float* ftab;
@@ -184,9 +185,10 @@ constexpr int kFoldWords = 3;
 __host__ __device__ constexpr int fold_pitch(int C0, int CPL) {
   return C0 * kFoldWords + (CPL > 2 ? 32 : 0);
 }
-// bytes of the folded tables of n species
-inline size_t fold_bytes(int rows, int C0, int LPE, int n) {
-  return 4 * size_t(n) * n * rows * fold_pitch(C0, C0 / LPE);
+// bytes of the folded tables of n species: a row at every knot, one more than
+// there are intervals
+inline size_t fold_bytes(int intervals, int C0, int LPE, int n) {
+  return 4 * size_t(n) * n * (intervals + 1) * fold_pitch(C0, C0 / LPE);
 }
 
 // ---------------------------------------------------------------------------

@@ -99,15 +99,19 @@ __device__ inline void harm3_grad(float x, float y, float z, float (*g)[3]) {
   g[6][0] = 3.0f * a * (x * x - y * y);  g[6][1] = -6.0f * a * x * y;          g[6][2] = 0.0f;
 }
 
-// Table interval and local coordinate tau in [0, 1) for rho.
+// Row of rho in a radial table and the coordinate tau in units of Delta from the
+// row's knot: a separable quintic runs from its knot to the next (tau in
+// [0, 1)), a folded row reaches half way to the knots on either side (tau in
+// [-1/2, 1/2]; one row more).
 // The row index is clamped to the table (a NaN rho maps to row 0 and gives
-// a NaN tau, never an out-of-range read); beyond the last knot the last
-// polynomial is extrapolated, where the envelope is already zero.
+// a NaN tau, never an out-of-range read); beyond the last row its polynomial
+// is extrapolated, where the envelope is already zero.
+template <bool FOLD>
 __device__ inline int table_row(float rho, float inv_delta, int n_rows, float* tau) {
-  float s = rho * inv_delta;
-  float sc = fminf(fmaxf(s, 0.0f), static_cast<float>(n_rows - 1));
-  int r = static_cast<int>(sc);
-  *tau = s - static_cast<float>(r);
+  const float s = fmaf(rho, inv_delta, FOLD ? 0.5f : 0.0f);
+  const float sc = fminf(fmaxf(s, 0.0f), static_cast<float>(FOLD ? n_rows : n_rows - 1));
+  const int r = static_cast<int>(sc);
+  *tau = fmaf(rho, inv_delta, -static_cast<float>(r));
   return r;
 }
 

@@ -17,6 +17,16 @@
 // d(chi psi)/drho and no value, leaves c0 of these channels (7 of 8 at full
 // width) in memory and takes 1,088 bytes an edge instead of 1,536.
 //
+// A row belongs to a knot and reaches half an interval to either side, since what
+// a dropped or rounded coefficient c_n does to the value and the slope goes with
+// |tau|^n and n |tau|^(n-1): |tau| <= 1/2 instead of tau < 1 halves the slope's
+// error of c2 and takes that of c3 to a quarter, for the same bytes and
+// operations.  Value, slope and curvature at a knot are those of the quintics on
+// both sides; the cubic coefficient is the mean of theirs, which differ by c4.
+// Forces of isolated pairs against 64 bits: 0.85 - 1.1 A 3.1 to 6.8e-6 of their
+// norm before (rows from knot to knot, three models), 1.8 to 2.5e-6 now; 1.3 -
+// 2 A 2.9 to 3.8e-6 before, 1.8 to 1.9e-6 now.
+//
 // Storage: c0 and c1 in float32, c2 and c3 as float16 scaled by fixed powers
 // of two (one per coefficient, from a bound over every pair: |gamma| < 2 and
 // |U| < 1 by their tanh forms, times the largest tabulated coefficient); c4
@@ -67,13 +77,14 @@ struct FoldTypes {
 // one block per (table row, folded pair); thread = channel c
 __global__ void fold_build_kernel(const float* __restrict__ gtab, const float* __restrict__ qtab,
                                   const float* __restrict__ pair, FoldTypes used, int n_used,
-                                  int n_types1, int C0, int R, int LPE, int rows,
+                                  int n_types1, int C0, int R, int LPE, int intervals,
                                   double r_c, double delta, const float2 scale,
                                   float* __restrict__ ftab) {
   const int s = blockIdx.x, p = blockIdx.y;
   // the envelope at the row's knot, chi_n = chi^(n) Delta^n / n!:
   // chi = t^4 (1 + 4x + 10x^2 + 20x^3 + 35x^4), chi' = -280 x^4 t^3 / r_c
-  const double x = s * delta / r_c, t = x < 1.0 ? 1.0 - x : 0.0, h = delta / r_c;
+  // (a last knot past r_c, where no edge is: the same polynomials)
+  const double h = delta / r_c, x = s * h, t = 1.0 - x;
   const double x2 = x * x, t2 = t * t;
   const double chi[4] = {
       t2 * t2 * (1.0 + x * (4.0 + x * (10.0 + x * (20.0 + x * 35.0)))),
@@ -85,15 +96,33 @@ __global__ void fold_build_kernel(const float* __restrict__ gtab, const float* _
   for (int c = threadIdx.x; c < C0; c += blockDim.x) {
     const int k = c % LPE, j = c / LPE;
     const float* pc = pair + ((size_t(a * n_types1 + b) * CPL + j) * LPE + k) * PW;
-    const float* g = gtab + ((size_t(s) * CPL + j) * LPE + k) * 6;
     // row s of pair p, in the order the edge kernels read (load_fold_row)
-    float* row = ftab + (size_t(p) * rows + s) * fold_pitch(C0, CPL);
+    float* row = ftab + (size_t(p) * (intervals + 1) + s) * fold_pitch(C0, CPL);
     const int at = fold_at(LPE, CPL, k, j);
-    double v[4];
-    for (int q = 0; q < 4; ++q) {
-      v[q] = double(pc[0]) * double(g[q]) + (q == 0 ? double(pc[1]) : 0.0);
-      for (int mu = 0; mu < R; ++mu)
-        v[q] += double(pc[2 + mu]) * double(qtab[(size_t(s) * R + mu) * 6 + q]);
+    // the pair's quintic of an interval
+    auto quintic = [&](int interval, double (&v)[6]) {
+      const float* g = gtab + ((size_t(interval) * CPL + j) * LPE + k) * 6;
+      for (int q = 0; q < 6; ++q) {
+        v[q] = double(pc[0]) * double(g[q]) + (q == 0 ? double(pc[1]) : 0.0);
+        for (int mu = 0; mu < R; ++mu)
+          v[q] += double(pc[2 + mu]) * double(qtab[(size_t(interval) * R + mu) * 6 + q]);
+      }
+    };
+    // around the knot: value, slope and curvature are those of both intervals,
+    // the cubic coefficient is the mean of theirs (at either end of the table
+    // that of the one there is; from the end of an interval by a Taylor shift)
+    double v[6];
+    if (s < intervals) {
+      quintic(s, v);
+      if (s > 0) {
+        double u[6];
+        quintic(s - 1, u);
+        v[3] = 0.5 * (v[3] + u[3] + 4.0 * u[4] + 10.0 * u[5]);
+      }
+    } else {
+      quintic(s - 1, v);
+      for (int n = 0; n < 4; ++n)
+        for (int q = 4; q >= n; --q) v[q] += v[q + 1];
     }
     if (j > 0)   // times the envelope, from the highest power down
       for (int q = 3; q >= 0; --q) {
@@ -159,7 +188,7 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
       int32_t* hmap = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(w.fold_host) + 64);
       std::memcpy(hmap, map.data(), 4 * size_t(T1));
       DPA4C_HIP_TRY(hipMemcpyAsync(w.fold_map.p, hmap, 4 * size_t(T1), hipMemcpyHostToDevice, st));
-      hipLaunchKernelGGL(fold_build_kernel, dim3(m->n_rows, n_used * n_used),
+      hipLaunchKernelGGL(fold_build_kernel, dim3(m->n_rows + 1, n_used * n_used),
                          dim3(m->C0 < 256 ? m->C0 : 256), 0, st, m->gtab, m->qtab, m->pair, used,
                          n_used, T1, m->C0, m->R, m->C[1], m->n_rows, m->r_c, m->delta,
                          make_float2(m->c_scale[0], m->c_scale[1]),

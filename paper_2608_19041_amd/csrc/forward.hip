@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
     // accumulates component m = k of each
     float acc3 = 0.0f, acc4 = 0.0f;
     float s0 = 0.0f, s1 = 0.0f;
-    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * md.n_rows * fold_pitch(P::C0, P::CPL)
+    const float* pair_base = FOLD ? md.ftab + size_t(ai) * nf * (md.n_rows + 1) * fold_pitch(P::C0, P::CPL)
                                   : md.pair + size_t(ai) * T1 * (P::C0 * P::PW);
 
     // One edge's contribution from its LDS entry and, with folded tables,
@@ -210,9 +210,9 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
           const EdgeGeom g = edge_geom(rec.x, rec.y, rec.z);
           float chi, tau;
           envelope(g.rho, md.inv_rc, &chi, nullptr);
-          const int row = table_row(g.rho, inv_delta, md.n_rows, &tau);
+          const int row = table_row<FOLD>(g.rho, inv_delta, md.n_rows, &tau);
           const int aj = type_of(__float_as_int(rec.w));
-          pr = FOLD ? make_float4(tau, chi, __uint_as_float(fold_offset<P::C0, P::CPL>(aj * md.n_rows + row)), 1.0f)
+          pr = FOLD ? make_float4(tau, chi, __uint_as_float(fold_offset<P::C0, P::CPL>(aj * (md.n_rows + 1) + row)), 1.0f)
                     : make_float4(tau, chi, __int_as_float(row), __int_as_float(aj));
           hv[0] = g.ux;
           hv[1] = g.uy;

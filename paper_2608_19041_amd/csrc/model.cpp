@@ -504,12 +504,12 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
   // float16 scales of the folded tables' c2, c3 (and of c4, c5, for the
   // bound): a power of two that maps the bound 2 max|g_n| + R max|q_n|
   // (gamma = 1 + tanh < 2, |U| = |tanh| < 1) to at most 2^14, half of the
-  // float16 range.  The rounding of c2, c3 (at most 2^-11 of each bound)
-  // enters the value with weight 1 and d/dtau with weights 2, 3; c4 and c5
-  // are dropped, so their whole bounds enter with weights 1 and 4, 5.  The
-  // tables are folded only while the value error stays below the float32
-  // rounding of the value term c0 and the slope error below 2^-14 of the
-  // slope term c1, else the separable float32 tables are used.
+  // float16 range.  The tables are folded only while the rounding of c2, c3
+  // (at most 2^-11 of each bound) and the dropped c4, c5 change the value by
+  // less than the float32 rounding of its term c0 and the slope by less than
+  // 2^-14 of its term c1, else the separable float32 tables are used.  For
+  // the channels that hold psi every power of |tau| <= 1/2 is taken as 1, for
+  // those that hold chi psi as what it is.
   double bnd[6] = {};
   for (int q = 0; q < 6; ++q) {
     double gmax = 0.0, qmax = 0.0;
@@ -523,12 +523,17 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
   // 0.034, |x^2 t (2t^2 - 4xt + x^2)| <= 0.041, the next two at the ends).
   // |beta| < 1 + 2 max|embedding| enters psi's value alone.
   const double f16 = std::ldexp(1.0, -11);
-  auto within = [&](double value) {
-    return (bnd[2] + bnd[3]) * f16 + bnd[4] + bnd[5] <= value * std::ldexp(1.0, -24) &&
-           (2.0 * bnd[2] + 3.0 * bnd[3]) * f16 + 4.0 * bnd[4] + 5.0 * bnd[5] <=
+  auto within = [&](double value, double tau) {
+    // c3 is a mean over the knot's two intervals, up to 2 c4 + 5 c5 from either
+    const double jump = tau < 1.0 ? 2.0 * bnd[4] + 5.0 * bnd[5] : 0.0;
+    const double t2 = tau * tau, t3 = t2 * tau, t4 = t2 * t2;
+    return (t2 * bnd[2] + t3 * (bnd[3] + jump)) * f16 + t3 * jump + t4 * bnd[4] + t4 * tau * bnd[5] <=
+               value * std::ldexp(1.0, -24) &&
+           (2.0 * tau * bnd[2] + 3.0 * t2 * (bnd[3] + jump)) * f16 + 3.0 * t2 * jump +
+                   4.0 * t3 * bnd[4] + 5.0 * t4 * bnd[5] <=
                bnd[1] * std::ldexp(1.0, -14);
   };
-  m->fold_allowed = within(bnd[0]);   // the channels that hold psi
+  m->fold_allowed = within(bnd[0], 1.0);   // the channels that hold psi
   {
     double beta = 1.0;
     for (size_t e = 0; e < size_t(T1) * C0; ++e)
@@ -538,8 +543,9 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
                            70 * std::pow(h, 4), 224 * std::pow(h, 5)};
     for (int q = 5; q >= 1; --q)
       for (int n = 1; n <= q; ++n) bnd[q] += chi[n] * (n == q ? bnd[0] + beta : bnd[q - n]);
-    m->fold_allowed = m->fold_allowed && within(bnd[0] + beta);   // those that hold chi psi
+    m->fold_allowed = m->fold_allowed && within(bnd[0] + beta, 0.5);   // those that hold chi psi
   }
+  bnd[3] += 2.0 * bnd[4] + 5.0 * bnd[5];   // of the mean
   for (int q = 2; q < 6; ++q) {
     int ex = 0;
     if (bnd[q] > 0.0) ex = static_cast<int>(std::floor(std::log2(16384.0 / bnd[q])));

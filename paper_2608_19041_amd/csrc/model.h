@@ -93,7 +93,7 @@ struct Workspace {
   std::vector<double> host_mass;   // the masses that inv_mass and mass were formed from
   int64_t* host_flags = nullptr;          // pinned [8]
   // pair-folded tables of the species present (fold.hip)
-  DevBuf ftab;          // float [fold_n^2][n_rows][fold_pitch]
+  DevBuf ftab;          // float [fold_n^2][n_rows + 1][fold_pitch]
   DevBuf fold_map;      // int32 [T+1]: type -> folded index, or -1
   DevBuf fold_mask;     // uint32 [256][4]: partial masks of the species present
   DevBuf fidx;          // int32 [N]: folded index of every atom

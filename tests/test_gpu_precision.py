@@ -1,6 +1,7 @@
 """What the stages of an evaluation lose against 64 bits, each from its own
 float32 inputs, so that no stage hides behind another: the readout from the node
-state, the MLP from the descriptor.  Errors are 2-norms over all atoms of eight
+state, the MLP from the descriptor; and whole energies and forces of isolated
+pairs, where nothing averages the radial tables' errors.  Errors are 2-norms over all atoms of eight
 jittered systems; the bounds are what plain float32 kernels (a sum over lanes in
 order for the readout, v_mfma_f32_16x16x4_f32 for the MLP) reach on the same
 systems, with a few percent for another order of sums: the eight seeds' own
@@ -137,3 +138,35 @@ def test_mlp_gradient_from_the_descriptor(dp, name, kind):
     ours, theirs = gradient_errors(dp, name, kind)
     print(f"{name} {kind}: {ours:.3e} of |dE/dD|, plain float32 {theirs:.3e}", flush=True)
     assert ours <= theirs
+
+
+def pair_errors(dp, name, lo, hi, n=400):
+    """(rms error of E_i in eV, relative error of F) of pairs lo to hi apart."""
+    spec, w = synth.model_weights(name)
+    model = dp.Model(synth.pack_blob(spec, w))
+    rng = np.random.default_rng(5)
+    u = rng.normal(size=(n, 3))
+    u *= (rng.uniform(lo, hi, n) / np.linalg.norm(u, axis=1))[:, None]
+    centre = np.stack(np.meshgrid(*[np.arange(8) * 20.0 + 10.0] * 3), -1).reshape(-1, 3)[:n]
+    pos = np.stack([centre, centre + u], 1).reshape(-1, 3)
+    species = np.tile(np.array([7, 0], np.int32), n)
+    cell, pbc = np.eye(3) * 200.0, np.zeros(3, np.int32)
+    p, s = torch.tensor(pos, device="cuda"), torch.tensor(species, device="cuda")
+    rows = dp.build_neighbors(p, cell, pbc, 6.0)
+    e, f, _ = model.compute_energy_forces(p, s, cell, pbc, 6.0, *rows)
+    ref_e, ref_f = om.Oracle(spec, w).energy_forces(pos, species, cell, pbc)
+    return (float(np.sqrt(((e.cpu().numpy() - ref_e) ** 2).mean())),
+            float(np.linalg.norm(f.cpu().numpy() - ref_f) / np.linalg.norm(ref_f)))
+
+
+@pytest.mark.parametrize("name,lo,hi,bound", [
+    ("mini", 0.85, 1.1, 3.54e-6), ("mini", 1.3, 2.0, 2.92e-6), ("mini", 2.3, 3.0, 2.95e-6),
+    ("air", 0.85, 1.1, 3.17e-6), ("air", 1.3, 2.0, 3.17e-6), ("air", 2.3, 3.0, 2.23e-6),
+    ("full", 0.85, 1.1, 6.70e-6), ("full", 1.3, 2.0, 3.87e-6), ("full", 2.3, 3.0, 1.318e-6)])
+def test_forces_of_pairs(dp, name, lo, hi, bound):
+    """On the folded tables.  The bounds are errors with c2, c3 rounded to float16
+    on rows that run from knot to knot, where the slope feels them twice as much as
+    on rows around a knot; next to them stand the float32 roundings of the edge."""
+    error = pair_errors(dp, name, lo, hi)[1]
+    print(f"{name} {lo}-{hi} A: {error:.3e} of |F|", flush=True)
+    assert error <= 0.8 * bound
