@@ -333,7 +333,7 @@ __global__ void __launch_bounds__(kTeam, (backward_min_waves<P, FOLD, VIR>())) b
           sk = cskin[b + c0 + lane];
           const EdgeGeom g = edge_geom(rec.x, rec.y, rec.z);
           float chi, dchi, tau;
-          envelope(g.rho, md.inv_rc, &chi, &dchi);
+          envelope(g.rho, md.r_c, md.inv_rc, &chi, &dchi);
           const int row = table_row<FOLD>(g.rho, inv_delta, md.n_rows, &tau);
           const int j = __float_as_int(rec.w);
           const int aj = type_of(j);

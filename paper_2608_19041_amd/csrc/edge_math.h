@@ -43,15 +43,19 @@ __device__ inline EdgeGeom edge_geom(float rx, float ry, float rz) {
 }
 
 // Eq. (envelope): chi = t^4 (1 + 4x + 10x^2 + 20x^3 + 35x^4), x = rho/r_c,
-// t = 1 - x, clipped; d chi / d rho = -280 x^4 t^3 / r_c.
-__device__ inline void envelope(float rho, float inv_rc, float* chi, float* dchi) {
-  float x = fminf(rho * inv_rc, 1.0f);
-  float t = 1.0f - x;
-  float t2 = t * t;
-  float p = 1.0f + x * (4.0f + x * (10.0f + x * (20.0f + x * 35.0f)));
+// t = 1 - x, clipped; d chi / d rho = -280 x^4 t^3 / r_c.  t comes from
+// r_c - rho, which is exact past r_c / 2, with the quotient corrected by its
+// residual, so that chi keeps its relative accuracy where it goes to zero
+// (1 - rho / r_c is off by 6e-8, however small t is); and x is one minus that
+// t, so that the factors' roundings cancel where chi is near one.
+__device__ inline void envelope(float rho, float r_c, float inv_rc, float* chi, float* dchi) {
+  const float d = r_c - rho, q = d * inv_rc;
+  const float t = fmaxf(fmaf(fmaf(-q, r_c, d), inv_rc, q), 0.0f), x = 1.0f - t;
+  const float t2 = t * t;
+  const float p = 1.0f + x * (4.0f + x * (10.0f + x * (20.0f + x * 35.0f)));
   *chi = t2 * t2 * p;
   if (dchi) {
-    float x2 = x * x;
+    const float x2 = x * x;
     *dchi = -280.0f * x2 * x2 * t2 * t * inv_rc;
   }
 }

@@ -209,7 +209,7 @@ __global__ void __launch_bounds__(kTeam, forward_min_waves<P>()) forward_kernel(
           float hv[kNH];
           const EdgeGeom g = edge_geom(rec.x, rec.y, rec.z);
           float chi, tau;
-          envelope(g.rho, md.inv_rc, &chi, nullptr);
+          envelope(g.rho, md.r_c, md.inv_rc, &chi, nullptr);
           const int row = table_row<FOLD>(g.rho, inv_delta, md.n_rows, &tau);
           const int aj = type_of(__float_as_int(rec.w));
           pr = FOLD ? make_float4(tau, chi, __uint_as_float(fold_offset<P::C0, P::CPL>(aj * (md.n_rows + 1) + row)), 1.0f)

@@ -170,3 +170,32 @@ def test_forces_of_pairs(dp, name, lo, hi, bound):
     error = pair_errors(dp, name, lo, hi)[1]
     print(f"{name} {lo}-{hi} A: {error:.3e} of |F|", flush=True)
     assert error <= 0.8 * bound
+
+
+def envelope_errors(dp, name, kind, seed=1):
+    """Relative rms errors of sum chi^2 and sum chi^4 from the positions."""
+    model = dp.Model(synth.pack_blob(*synth.model_weights(name)))
+    pos, species, cell, pbc = system(kind, seed)
+    n = len(pos)
+    p, s = torch.tensor(pos, device="cuda"), torch.tensor(species, device="cuda")
+    rows = dp.build_neighbors(p, cell, pbc, 6.0)
+    model.compute_energy_forces(p, s, cell, pbc, 6.0, *rows)
+    node = model.debug_stages(n)[0].cpu().numpy()
+    i = np.repeat(np.arange(n), np.diff(rows[0].cpu().numpy()))
+    j, shift = rows[1].cpu().numpy()[:len(i)], dp.unpack_shift(rows[2].cpu().numpy()[:len(i)])
+    x = np.linalg.norm(pos[j] + shift @ cell - pos[i], axis=1) / 6.0
+    chi = (1 - x) ** 4 * (1 + 4 * x + 10 * x ** 2 + 20 * x ** 3 + 35 * x ** 4)
+    ref = np.stack([np.bincount(i, chi ** k, n) for k in (2, 4)], 1)
+    return np.sqrt(((node[:, :2] / ref - 1) ** 2).mean(0))
+
+
+@pytest.mark.parametrize("kind", ["fcc", "cluster", "bcc"])
+@pytest.mark.parametrize("name", ["small", "full"])
+def test_envelope_sums(dp, name, kind):
+    """chi = t^4 p(1 - t) with t to half a unit of 2^-24: four times that, the
+    polynomial's roundings and those of rho make about 2^-23.5 of chi at worst, twice
+    that of chi^2; over the edges of an atom they average.  With t = 1 - rho / r_c
+    from a rounded product it was 2.0e-7 and 3.7e-7."""
+    s0, s1 = envelope_errors(dp, name, kind)
+    print(f"{name} {kind}: {s0:.3e} of sum chi^2, {s1:.3e} of sum chi^4", flush=True)
+    assert s0 <= 2.0**-23 and s1 <= 1.5 * 2.0**-23
