@@ -131,6 +131,7 @@ int with_profile(int C0, int L, int R, int F, Fn&& fn) {
 // Device-side view of a model, passed to kernels by value.
 // ---------------------------------------------------------------------------
 constexpr int kMaxTypeRows = 128;        // type-table rows (species + padding) a model may have
+constexpr int kMaxModes = 4;             // rank R of a compiled profile
 constexpr int kMaxFoldTypes = 5;         // species for which pair-folded tables are built
 constexpr int kFoldFirstTypes = 2;       // species whose folded tables have room from the start
 constexpr size_t kMaxFoldBytes = size_t(300) << 20;  // and their largest total size

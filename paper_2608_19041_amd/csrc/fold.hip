@@ -91,6 +91,31 @@ __global__ void fold_build_kernel(const float* __restrict__ gtab, const float* _
       -280.0 * x2 * x2 * t2 * t * h,
       -140.0 * x2 * x * t2 * (4.0 * t - 3.0 * x) * h * h,
       -280.0 * x2 * t * (2.0 * t2 - 4.0 * x * t + x2) * h * h * h};
+  // Around the knot the coefficients up to the third of one tabulated function
+  // (coef(interval, power)): value, slope and curvature are those of both
+  // intervals, the cubic coefficient is the mean of theirs; at either end of the
+  // table those of the one interval there is (a Taylor shift from its end).
+  auto around = [&](auto&& coef, double (&v)[4]) {
+    if (s < intervals) {
+      for (int q = 0; q < 4; ++q) v[q] = coef(s, q);
+      if (s > 0)
+        v[3] = 0.5 * (v[3] + coef(s - 1, 3) + 4.0 * coef(s - 1, 4) + 10.0 * coef(s - 1, 5));
+    } else {
+      double u[6];
+      for (int q = 0; q < 6; ++q) u[q] = coef(s - 1, q);
+      v[0] = u[0] + u[1] + u[2] + u[3] + u[4] + u[5];
+      v[1] = u[1] + 2.0 * u[2] + 3.0 * u[3] + 4.0 * u[4] + 5.0 * u[5];
+      v[2] = u[2] + 3.0 * u[3] + 6.0 * u[4] + 10.0 * u[5];
+      v[3] = u[3] + 4.0 * u[4] + 10.0 * u[5];
+    }
+  };
+  __shared__ double mode[kMaxModes][4];   // of the q functions, for all channels
+  if (threadIdx.x < R) {
+    double v[4];
+    around([&](int i, int q) { return double(qtab[(size_t(i) * R + threadIdx.x) * 6 + q]); }, v);
+    for (int q = 0; q < 4; ++q) mode[threadIdx.x][q] = v[q];
+  }
+  __syncthreads();
   const int a = used.t[p / n_used], b = used.t[p % n_used];
   const int PW = 2 + R, CPL = C0 / LPE;
   for (int c = threadIdx.x; c < C0; c += blockDim.x) {
@@ -99,30 +124,11 @@ __global__ void fold_build_kernel(const float* __restrict__ gtab, const float* _
     // row s of pair p, in the order the edge kernels read (load_fold_row)
     float* row = ftab + (size_t(p) * (intervals + 1) + s) * fold_pitch(C0, CPL);
     const int at = fold_at(LPE, CPL, k, j);
-    // the pair's quintic of an interval
-    auto quintic = [&](int interval, double (&v)[6]) {
-      const float* g = gtab + ((size_t(interval) * CPL + j) * LPE + k) * 6;
-      for (int q = 0; q < 6; ++q) {
-        v[q] = double(pc[0]) * double(g[q]) + (q == 0 ? double(pc[1]) : 0.0);
-        for (int mu = 0; mu < R; ++mu)
-          v[q] += double(pc[2 + mu]) * double(qtab[(size_t(interval) * R + mu) * 6 + q]);
-      }
-    };
-    // around the knot: value, slope and curvature are those of both intervals,
-    // the cubic coefficient is the mean of theirs (at either end of the table
-    // that of the one there is; from the end of an interval by a Taylor shift)
-    double v[6];
-    if (s < intervals) {
-      quintic(s, v);
-      if (s > 0) {
-        double u[6];
-        quintic(s - 1, u);
-        v[3] = 0.5 * (v[3] + u[3] + 4.0 * u[4] + 10.0 * u[5]);
-      }
-    } else {
-      quintic(s - 1, v);
-      for (int n = 0; n < 4; ++n)
-        for (int q = 4; q >= n; --q) v[q] += v[q + 1];
+    double v[4];
+    around([&](int i, int q) { return double(gtab[((size_t(i) * CPL + j) * LPE + k) * 6 + q]); }, v);
+    for (int q = 0; q < 4; ++q) {
+      v[q] = double(pc[0]) * v[q] + (q == 0 ? double(pc[1]) : 0.0);
+      for (int mu = 0; mu < R; ++mu) v[q] += double(pc[2 + mu]) * mode[mu][q];
     }
     if (j > 0)   // times the envelope, from the highest power down
       for (int q = 3; q >= 0; --q) {
