@@ -342,8 +342,9 @@ const char* dpa4c_stage_name(int stage);
 
 /*
  * C = A B for row-major float32 A [M][K], B [K][N], C [M][N] (device), with
- * K a multiple of 16 and N a multiple of 4: the fp32 matrix-core GEMM of the
- * MLP stage, exported so that tests can check it against a reference.
+ * K a multiple of 16 and N a multiple of 4, on the fp32 matrix instructions.
+ * The MLP stage's own products are checked through dpa4c_debug_stages and
+ * dpa4c_debug_gradient.
  */
 int dpa4c_debug_gemm(const float* A, const float* B, float* C, int M, int N, int K,
                      void* stream);

@@ -76,7 +76,6 @@ struct Profile {
   static constexpr int o244 = o233 + n233, o334 = o244 + n244, o444 = o334 + n334;
   static constexpr int oPi = o444 + n444;
   static constexpr int DOUT = oPi + nPi;
-  static constexpr int DSTR = (DOUT + 15) / 16 * 16;   // row stride of descriptor arrays
   static_assert(C0 % LPE == 0, "channel split");
   static_assert(R == 0 || R == 4, "the edge kernels handle 0 or 4 radial modes");
   static_assert(L >= 2 && L <= 4, "degrees 2 to 4");
@@ -160,13 +159,8 @@ struct ModelDev {
   int n_types1;             // T + 1
   const float* pair;        // [(T+1)^2][CPL][LPE][PW]
   const float* type_embed;  // [T+1][C0]
-  const float* W1;          // [C1][C1] alignment, degree 1 (I + W applied in-kernel)
-  const float* W2;          // [C2][C2]
-  const float* A1;          // [C1][K1] or null (identity)
-  const float* A2;          // [C2][K2]
   const float* mu;          // [D_out]
   const float* inv_sigma;   // [D_out]
-  const float* cpl;         // [kCouplings]: C123 then C233 (symmetric in m2, m3), or null
   const float* E_ref;       // [T+1]
   const float* row_tab;     // per-lane tables of the readout (readout_row.h)
   // pair-folded tables (fold.hip), used when fold_n > 0:

@@ -60,49 +60,6 @@ __device__ inline void envelope(float rho, float r_c, float inv_rc, float* chi, 
   }
 }
 
-// Real Cartesian harmonics with |u|^2 set to one (Methods "Fidelity of the
-// compressed model"; the error is O(eps^2/rho^2)).
-__device__ inline void harm2(float x, float y, float z, float* b) {
-  const float r3 = 1.7320508075688772f;
-  b[0] = r3 * x * y;
-  b[1] = r3 * y * z;
-  b[2] = 0.5f * (3.0f * z * z - 1.0f);
-  b[3] = r3 * x * z;
-  b[4] = 0.5f * r3 * (x * x - y * y);
-}
-__device__ inline void harm3(float x, float y, float z, float* b) {
-  const float a = 0.7905694150420949f;   // sqrt(5/8)
-  const float r15 = 3.872983346207417f;  // sqrt(15)
-  const float c = 0.6123724356957945f;   // sqrt(3/8)
-  b[0] = a * y * (3.0f * x * x - y * y);
-  b[1] = r15 * x * y * z;
-  b[2] = c * y * (5.0f * z * z - 1.0f);
-  b[3] = 0.5f * z * (5.0f * z * z - 3.0f);
-  b[4] = c * x * (5.0f * z * z - 1.0f);
-  b[5] = 0.5f * r15 * z * (x * x - y * y);
-  b[6] = a * x * (x * x - 3.0f * y * y);
-}
-// gradients d B / d u (with |u|^2 = 1 held constant): g[m][3]
-__device__ inline void harm2_grad(float x, float y, float z, float (*g)[3]) {
-  const float r3 = 1.7320508075688772f;
-  g[0][0] = r3 * y; g[0][1] = r3 * x; g[0][2] = 0.0f;
-  g[1][0] = 0.0f;   g[1][1] = r3 * z; g[1][2] = r3 * y;
-  g[2][0] = 0.0f;   g[2][1] = 0.0f;   g[2][2] = 3.0f * z;
-  g[3][0] = r3 * z; g[3][1] = 0.0f;   g[3][2] = r3 * x;
-  g[4][0] = r3 * x; g[4][1] = -r3 * y; g[4][2] = 0.0f;
-}
-__device__ inline void harm3_grad(float x, float y, float z, float (*g)[3]) {
-  const float a = 0.7905694150420949f, r15 = 3.872983346207417f, c = 0.6123724356957945f;
-  const float d = 0.5f * r15;
-  g[0][0] = 6.0f * a * x * y;            g[0][1] = 3.0f * a * (x * x - y * y); g[0][2] = 0.0f;
-  g[1][0] = r15 * y * z;                 g[1][1] = r15 * x * z;                g[1][2] = r15 * x * y;
-  g[2][0] = 0.0f;                        g[2][1] = c * (5.0f * z * z - 1.0f);  g[2][2] = 10.0f * c * y * z;
-  g[3][0] = 0.0f;                        g[3][1] = 0.0f;                       g[3][2] = 7.5f * z * z - 1.5f;
-  g[4][0] = c * (5.0f * z * z - 1.0f);   g[4][1] = 0.0f;                       g[4][2] = 10.0f * c * x * z;
-  g[5][0] = 2.0f * d * x * z;            g[5][1] = -2.0f * d * y * z;          g[5][2] = d * (x * x - y * y);
-  g[6][0] = 3.0f * a * (x * x - y * y);  g[6][1] = -6.0f * a * x * y;          g[6][2] = 0.0f;
-}
-
 // Row of rho in a radial table and the coordinate tau in units of Delta from the
 // row's knot: a separable quintic runs from its knot to the next (tau in
 // [0, 1)), a folded row reaches half way to the knots on either side (tau in
@@ -271,7 +228,6 @@ __device__ inline void cubic_monomials(float x, float y, float z, float* m) {
   m[5] = x * z2; m[6] = y2 * y; m[7] = y2 * z; m[8] = y * z2; m[9] = z2 * z;
 }
 
-// species index clamped into the type table (the padding type for bad input)
 // The exponent e of an operand of the MLP whose entries are at most b: the
 // largest that keeps b 2^e below 2^15 (half of the float16 range), no more
 // than 2^100 so that 2^e and what it is undone by stay finite.
@@ -280,6 +236,7 @@ __device__ inline int operand_exponent(float b) {
   return e < 100 ? e : 100;
 }
 
+// species index clamped into the type table (the padding type for bad input)
 __device__ inline int clamp_type(int a, int n_types1) {
   return static_cast<unsigned>(a) < static_cast<unsigned>(n_types1) ? a : n_types1 - 1;
 }
@@ -310,16 +267,6 @@ __device__ inline int type_rank(bool on, int type) {
     todo &= ~m;
   }
   return rank;
-}
-
-// lane 0 of every group of W lanes to all lanes of its group
-template <int W>
-__device__ inline float4 group_bcast(float4 v) {
-  v.x = __shfl(v.x, 0, W);
-  v.y = __shfl(v.y, 0, W);
-  v.z = __shfl(v.z, 0, W);
-  v.w = __shfl(v.w, 0, W);
-  return v;
 }
 
 // A lane's entries of a folded table row for its channels c = k + LPE j: c1 and

@@ -1,7 +1,6 @@
-// Plain fp32 GEMM on the matrix cores (v_mfma_f32_16x16x4_f32) with an
-// optional fused epilogue (bias + SiLU + residual, or residual + product).
-// The energy path uses mlp_chain.hip; this one backs the exported
-// dpa4c_debug_gemm entry used to check the MFMA operand layout.
+// Plain fp32 GEMM on the matrix cores (v_mfma_f32_16x16x4_f32) behind the
+// exported dpa4c_debug_gemm.  The energy path has no use for it: its products are
+// those of mlp_chain.hip, on other operands in another layout.
 #include <hip/hip_runtime.h>
 
 #include "../../include/dpa4c.h"
@@ -16,25 +15,12 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int BM = 64, BN = 64, BK = 16;
 constexpr int kThreads = 256;
 
-__device__ inline float sigmoidf(float z) { return 1.0f / (1.0f + __expf(-z)); }
-
-struct Epilogue {
-  int mode;                 // 0: forward activation, 1: backward product
-  const float* bias;        // [N]           (mode 0)
-  const float* res_vec;     // [N] or null   (mode 1)
-  const float* res_mat;     // [M][ldr] or null (mode 0 and 1)
-  int ldr;
-  float* aux;               // mode 0: SiLU'(pre) [M][ldc]
-  const float* mul;         // mode 1: multiply after the residual, [M][ldc], or null
-  float* out_h;             // mode 1: store of the value before ``mul`` or null
-};
-
-// C[M][N] (row stride ldc) = A[M][K] (stride lda) * B[K][N] (stride ldb) + epilogue.
+// C[M][N] (row stride ldc) = A[M][K] (stride lda) * B[K][N] (stride ldb).
 // K is a multiple of BK; M and N are bounds-checked.
 __global__ void __launch_bounds__(kThreads) gemm_kernel(const float* __restrict__ A, int lda,
                                                         const float* __restrict__ B, int ldb,
-                                                        float* C, int ldc, int M, int N, int K,
-                                                        Epilogue ep) {
+                                                        float* __restrict__ C, int ldc, int M,
+                                                        int N, int K) {
   __shared__ float As[BM][BK + 1];
   __shared__ float Bs[BK][BN + 4];
   const int tid = threadIdx.x;
@@ -89,7 +75,7 @@ __global__ void __launch_bounds__(kThreads) gemm_kernel(const float* __restrict_
     }
     __syncthreads();
   }
-  // epilogue: tile (ti, tj), register r -> row 4*(lane/16) + r, column lane%16
+  // tile (ti, tj), register r -> row 4*(lane/16) + r, column lane%16
 #pragma unroll
   for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -99,45 +85,23 @@ __global__ void __launch_bounds__(kThreads) gemm_kernel(const float* __restrict_
         const int row = row0 + wm * 32 + ti * 16 + 4 * (lane >> 4) + r;
         const int col = col0 + wn * 32 + tj * 16 + (lane & 15);
         if (row >= M || col >= N) continue;
-        float v = acc[ti][tj][r];
-        const size_t o = size_t(row) * ldc + col;
-        if (ep.mode == 0) {
-          float pre = v + (ep.bias ? ep.bias[col] : 0.0f);
-          float sg = sigmoidf(pre);
-          float h = pre * sg;
-          if (ep.res_mat) h += ep.res_mat[size_t(row) * ep.ldr + col];
-          C[o] = h;
-          if (ep.aux) ep.aux[o] = sg * (1.0f + pre * (1.0f - sg));
-        } else {
-          if (ep.res_vec) v += ep.res_vec[col];
-          if (ep.res_mat) v += ep.res_mat[size_t(row) * ep.ldr + col];
-          if (ep.out_h) ep.out_h[o] = v;
-          if (ep.mul) v *= ep.mul[o];
-          C[o] = v;
-        }
+        C[size_t(row) * ldc + col] = acc[ti][tj][r];
       }
-}
-
-int gemm(const float* A, int lda, const float* B, int ldb, float* C, int ldc, int M, int N, int K,
-         const Epilogue& ep, hipStream_t st) {
-  if (K % BK || lda % 4 || ldb % 4 || M < 0) {
-    set_error("gemm: K and leading dimensions must be multiples of 16 / 4");
-    return DPA4C_ERR_INVALID_ARG;
-  }
-  if (M == 0) return 0;
-  dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM);
-  hipLaunchKernelGGL(gemm_kernel, grid, dim3(kThreads), 0, st, A, lda, B, ldb, C, ldc, M, N, K, ep);
-  DPA4C_HIP_TRY(hipGetLastError());
-  return 0;
 }
 
 }  // namespace
 
 int launch_gemm_test(const float* A, const float* B, float* C, int M, int N, int K,
                      hipStream_t st) {
-  Epilogue ep{};
-  ep.mode = 1;
-  return gemm(A, K, B, N, C, N, M, N, K, ep, st);
+  if (K % BK || N % 4 || M < 0) {
+    set_error("gemm: K and N must be multiples of 16 and 4");
+    return DPA4C_ERR_INVALID_ARG;
+  }
+  if (M == 0) return 0;
+  const dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM);
+  hipLaunchKernelGGL(gemm_kernel, grid, dim3(kThreads), 0, st, A, K, B, N, C, N, M, N, K);
+  DPA4C_HIP_TRY(hipGetLastError());
+  return 0;
 }
 
 }  // namespace dpa4c

@@ -556,8 +556,6 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
   // ---- coupling tensors, each symmetrised over the indices of equal degree
   // (the exact integrals are; the quadrature sums are only up to rounding)
   std::vector<float> cpl;
-  m->gaunt[0] = coupling(1, 1, 2);
-  m->gaunt[2] = coupling(2, 2, 2);
   auto push = [&](int l1, int l2, int l3) {
     const std::vector<double> g = coupling(l1, l2, l3);
     const int n1 = 2 * l1 + 1, n2 = 2 * l2 + 1, n3 = 2 * l3 + 1;
@@ -605,17 +603,12 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
   add((void**)&m->gtab, gtab.data(), gtab.size() * 4);
   add((void**)&m->qtab, qtab.data(), qtab.size() * 4);
   add((void**)&m->type_embed, type_embed, size_t(T1) * C0 * 4);
-  add((void**)&m->W1, Wa1, size_t(C1) * C1 * 4);
-  add((void**)&m->W2, Wa2, size_t(C2) * C2 * 4);
-  if (A1) add((void**)&m->A1, A1, size_t(C1) * K1 * 4);
-  add((void**)&m->A2, A2, size_t(C2) * K2 * 4);
   add((void**)&m->mu, mu_pad.data(), mu_pad.size() * 4);
   add((void**)&m->inv_sigma, inv_sigma.data(), inv_sigma.size() * 4);
   add((void**)&m->E_ref, E_ref, size_t(T1) * 4);
   for (int t = 0; t < m->n_layers; ++t) add((void**)&m->bias[t], bias[t], size_t(F) * 4);
   add((void**)&m->w_head, w_head, size_t(F) * 4);
   m->b_head = b_head[0];
-  if (!cpl.empty()) add((void**)&m->cpl, cpl.data(), cpl.size() * 4);
   std::vector<float> row_tab(row_table_floats(m.get()));
   build_row_table(m.get(), Wa1, Wa2, A1, A2, cpl.data(), row_tab.data());
   if (!row_tab.empty()) add((void**)&m->row_tab, row_tab.data(), row_tab.size() * 4);
@@ -667,13 +660,8 @@ dpa4c::ModelDev dpa4c_model::dev() const {
   d.n_types1 = n_types + 1;
   d.pair = pair;
   d.type_embed = type_embed;
-  d.W1 = W1;
-  d.W2 = W2;
-  d.A1 = A1;
-  d.A2 = A2;
   d.mu = mu;
   d.inv_sigma = inv_sigma;
-  d.cpl = cpl;
   d.E_ref = E_ref;
   d.row_tab = row_tab;
   d.ftab = ws.ftab.as<float>();

@@ -143,10 +143,6 @@ struct dpa4c_model {
   float* qtab = nullptr;
   float* pair = nullptr;
   float* type_embed = nullptr;
-  float* W1 = nullptr;
-  float* W2 = nullptr;
-  float* A1 = nullptr;
-  float* A2 = nullptr;
   float* mu = nullptr;
   float* inv_sigma = nullptr;
   float* E_ref = nullptr;
@@ -158,9 +154,7 @@ struct dpa4c_model {
   float* row_tab = nullptr;         // per-lane tables of the readout (readout_row.h)
   float* w_head = nullptr;
   float b_head = 0;
-  float* cpl = nullptr;             // dense (1,2,3) and (2,3,3) couplings (degree three only)
   // host copies kept for tests of the host logic
-  std::vector<double> gaunt[4];     // (1,1,2), (1,2,3), (2,2,2), (2,3,3) normalised couplings
   dpa4c::Workspace ws;
   dpa4c::Timing timing;
   std::mutex mu_lock;
