@@ -424,7 +424,14 @@ int create_model(const void* blob, size_t nbytes, int device, dpa4c_model** out)
     set_error("dpa4c_model_create: null blob/out or blob shorter than its header");
     return DPA4C_ERR_INVALID_ARG;
   }
-  std::unique_ptr<dpa4c_model> m(new dpa4c_model());
+  struct Discard {   // a model whose creation fails gives its memory back
+    void operator()(dpa4c_model* p) const {
+      p->params.release();
+      p->wsplit_buf.release();
+      delete p;
+    }
+  };
+  std::unique_ptr<dpa4c_model, Discard> m(new dpa4c_model());
   m->device = device;
   int widths[2] = {0, 0};   // S, D_out of the compiled profile
   if (int rc = read_header(blob, nbytes, m.get(), widths)) return rc;

@@ -185,6 +185,20 @@ def creation_reserves_only_tables_it_would_use(h):
     assert not any(x.startswith("malloc") and int(x.split()[1]) >= tables for x in h.log())
 
 
+def refused_creation_keeps_no_memory(h):
+    """A creation that ran out of memory gives back what it had taken."""
+    for granted in (1, 2):   # the parameters; those and the split weights
+        h.refuse_from(1 << 20, after=granted)
+        rc, _ = h.create("full")
+        assert rc == OOM
+        log = h.log()
+        assert any(x.startswith("malloc") for x in log)
+        assert (sorted(x.split()[1] for x in log if x.startswith("malloc"))
+                == sorted(x.split()[1] for x in log if x.startswith("free")))
+    h.refuse_from(0)
+    assert h.create("full")[0] == OK, h.lib.dpa4c_last_error()
+
+
 def nothing_is_queued_after_the_last_wait(h):
     """A dynamics call has waited for all it queued, however it ended."""
     for nvt in (False, True):
@@ -215,6 +229,7 @@ SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocatio
              list_after_a_refused_workspace, list_after_a_refused_larger_system,
              list_after_a_half_refused_list,
              creation_without_room_for_tables, creation_reserves_only_tables_it_would_use,
+             refused_creation_keeps_no_memory,
              nothing_is_queued_after_the_last_wait, noalloc_works_outside_the_workspace]
 
 
