@@ -86,9 +86,10 @@ def stage_work(name, spec, n_atoms, n_edges):
         channel), psi and psi' (2(1+R) FMA per channel), two channel
         contractions per accumulated entry (2 FMA each) and the angular
         gradient (3 FMA per entry of degree >= 1)
-      per-atom kernel      - matrix cores: forward and input-gradient
+      per-atom stage       - matrix cores: forward and input-gradient
         products of the MLP, 2 x 2 (D_out F + (L-1) F^2) flop per atom (the
-        readout and its VJP add ~1% VALU work, not counted)
+        readout and its VJP, kernels of their own in the stage's time, add ~1%
+        VALU work, not counted)
       forces               - HBM: per edge 4 B skin position of the compact
         slot, 16 B gradient, 8 B position of the reverse and 16 B gathered
         reverse gradient; per atom 12 B row bounds in, 24 B force out, and the
@@ -108,29 +109,30 @@ def stage_work(name, spec, n_atoms, n_edges):
         per_edge = 2 * (9 * (C0 + R) + 2 * (1 + R) * C0 + 2 * S + 3 * (S - C0))
         return "alu", per_edge * n_edges, "flop"
     if name == "atoms":
-        # per-atom kernels: forward and input-gradient products of the MLP
         return "mfma", 4 * (D * F + (nl - 1) * F * F) * n_atoms, "flop"
     if name == "forces":
         return "hbm", 44 * n_edges + (36 + 132) * n_atoms, "byte"
     return None
 
 
-# kernel behind each timed stage and the sources it is compiled from
+# kernels behind each timed stage, the one that names its traffic summary first,
+# and the sources they are compiled from
 STAGE_KERNELS = {
-    "atoms": ("chain_kernel", "mlp_chain.hip"),
-    "forward": ("forward_kernel", "forward.hip"),
-    "backward": ("backward_kernel", "backward.hip"),
-    "forces": ("forces_kernel", "assemble.hip"),
+    "atoms": (["chain_kernel", "row_readout_kernel", "row_vjp_kernel"],
+              ["mlp_chain.hip", "readout.hip"]),
+    "forward": (["forward_kernel"], ["forward.hip"]),
+    "backward": (["backward_kernel"], ["backward.hip"]),
+    "forces": (["forces_kernel"], ["assemble.hip"]),
 }
 
 
 def kernel_source_hash(stage):
-    """sha256 over the kernel's .hip file and every file it includes with
-    #include "..." (followed transitively), in a fixed order."""
+    """sha256 over the .hip files of the stage's kernels and every file they
+    include with #include "..." (followed transitively), in a fixed order."""
     import hashlib
     import re
     csrc = os.path.join(HERE, "paper_2608_19041_amd", "csrc")
-    todo, seen = [os.path.join(csrc, STAGE_KERNELS[stage][1])], []
+    todo, seen = [os.path.join(csrc, f) for f in STAGE_KERNELS[stage][1]], []
     while todo:
         f = os.path.normpath(todo.pop())
         if f in seen:
@@ -147,11 +149,12 @@ def kernel_source_hash(stage):
 
 
 def measured_traffic(stage, workload):
-    """HBM bytes per launch from the committed rocprofv3 counter summary, or
-    None when there is none or the kernel's sources changed since."""
+    """HBM bytes of one evaluation's launches of the stage from the committed
+    rocprofv3 counter summary, or None when there is none or the kernels' sources
+    changed since."""
     if stage not in STAGE_KERNELS:
         return None
-    path = os.path.join(HERE, "profiles", f"traffic_{STAGE_KERNELS[stage][0]}_{workload}.txt")
+    path = os.path.join(HERE, "profiles", f"traffic_{STAGE_KERNELS[stage][0][0]}_{workload}.txt")
     if not os.path.exists(path):
         return None
     kv = {}
@@ -552,7 +555,9 @@ def main():
             achieved = amount / avg_s / 1e9
             peak = PEAK_HBM_GBS
             u = "GB/s"
-        roof = {"bound": bound, "stage": dominant, "kernel": STAGE_KERNELS.get(dominant, ("?",))[0], "achieved": round(achieved, 3), "peak": peak,
+        # time and traffic are those of all the stage's kernels
+        roof = {"bound": bound, "stage": dominant, "kernel": " + ".join(STAGE_KERNELS[dominant][0]),
+                "achieved": round(achieved, 3), "peak": peak,
                 "unit": u, "frac": round(achieved / peak, 4),
                 "traffic": measured_traffic(dominant, args.workload),
                 "avg_launch_ms": round(avg_s * 1e3, 5), "launches": stage_cnt[dominant],
@@ -569,6 +574,9 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
+        "arithmetic": "float32 per edge and atom, float64 positions, forces and sums; MLP products "
+                      "as three float16 matrix products of split float32 operands (hi + lo), "
+                      "accumulated in float32",
         "data": "synthetic",
         "config": {"workload": args.workload, "description": DESCRIPTIONS[args.workload],
                    "atoms": system.n, "edges_within_rc": n_edges, "dt_fs": dt,

@@ -2,11 +2,13 @@
 // the edge recomputation of Methods "Fused execution and backward
 // recomputation".
 //
-// One wavefront per centre (four per 256-thread workgroup, never waiting for
-// each other).  For centre i the wave reads the node-state gradient
-// [dE/dS0, dE/dS1, dE/dY] (from the readout VJP), revisits the edges of
-// row i, recomputes the tabulated radial maps (value and derivative), the
-// pair coefficients and the envelope, and writes
+// One wavefront per centre above kSplitRows centres (four per 256-thread
+// workgroup, never waiting for each other), up to that many the four waves of a
+// workgroup for one centre, an even share of each round's edges each.  For
+// centre i a wave reads the node-state gradient [dE/dS0, dE/dS1, dE/dY]
+// (from the readout VJP), revisits the edges of row i, recomputes the tabulated
+// radial maps (value and derivative), the pair coefficients and the envelope,
+// and writes
 //     dE/dr_ij = (dE/drho) u + (I - u u^T)(dE/du) / rho,
 // with  dE/drho = sum_lmc Ybar_lmc B_lm d(chi_l psi_c)/drho
 //               + Sbar0 d(chi^2)/drho + Sbar1 d(chi^4)/drho,
@@ -18,9 +20,8 @@
 // and Q_k is a fixed polynomial per centre: v.u (degree one), u.W u (degree
 // two, W symmetric), a cubic (degree three) and a quartic (degree four).  Its
 // coefficients are formed once per centre, so per edge each lane evaluates
-// one short polynomial and
-// its gradient instead of every harmonic.  The LPE partial sums of an edge
-// are combined with a fixed DPP butterfly.
+// one short polynomial and its gradient instead of every harmonic.  The LPE
+// partial sums of an edge are combined with a fixed DPP butterfly.
 //
 // The row is taken in passes of 64 edges: each lane first forms one edge's
 // geometry, envelope and table row into the wave's LDS slice, so the groups
@@ -32,17 +33,20 @@
 // compact records, and keeps j in the fourth component; a pass's gradients
 // are stored together once its edges have run.  The passes run from the end
 // of the row to its start: a skin position is never before its compact
-// slot, so a gradient never lands on a record still to be read.  With VIR the
-// lane that forms a gradient also adds -g_e (x) r_e (float64) to its group's
-// slot in LDS; the slots are summed in group order into the atom's term W_i
-// of the virial of Eq. (forces).
+// slot, so a gradient never lands on a record still to be read.  Where four
+// waves share the row, one wave's gradients may land on records of its round
+// that another wave reads, so the workgroup waits until all four have read
+// theirs before any stores (round_sync).  With VIR the lane that forms a
+// gradient also adds -g_e (x) r_e (float64) to its group's slot in LDS; the
+// slots are summed in group order into the atom's term W_i of the virial of
+// Eq. (forces).
 //
 // What bounds it is the stream of table entries into the CUs, so it reads only
 // what a slope needs (fold.hip): 8 bytes a channel where the forward kernel
 // reads 12.  Backward over 24,000 water atoms (four tables, more than an L2)
-// 251 -> 168 us, 31,250 alloy atoms (25 tables) 435 -> 323 us, a million copper
+// 251 -> 166 us, 31,250 alloy atoms (25 tables) 435 -> 301 us, a million copper
 // atoms (one table) 5.86 -> 4.97 ms, 7,056 carbon atoms with the virial 89 ->
-// 82 us.
+// 83 us.
 #include <hip/hip_runtime.h>
 
 #include "../../include/dpa4c.h"
@@ -56,10 +60,10 @@ namespace {
 constexpr int kTeam = 256;
 constexpr int kWaves = kTeam / kWave;
 
-// Four waves per SIMD for the degree-three variants on folded tables (121 to 128
+// Four waves per SIMD for the degree-three variants on folded tables (at most 128
 // registers, none spilled; the virial's get there by themselves), three with the
 // pair coefficients of the separable tables; degree four would spill and keeps
-// its natural three.
+// its natural three, two on separable tables.
 template <class P, bool FOLD, bool VIR>
 constexpr int backward_min_waves() { return P::L < 4 && !VIR ? (FOLD ? 4 : 3) : 1; }
 

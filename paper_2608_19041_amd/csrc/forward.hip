@@ -10,15 +10,18 @@
 // their skin positions, no per-edge quantity is written to memory.
 // The readout follows in kernels of its own (readout.hip).
 //
-// Mapping: one wavefront per centre (four centres per 256-thread
-// workgroup; the waves never wait for each other).  The wave takes the skin
-// row in passes of 64 entries: each lane tests one entry (compact.h), and
-// each kept lane forms its edge's per-edge quantities once (envelope, table
-// row and offset, harmonics) into the wave's LDS slice.  The lanes then form
-// groups of LPE = C1 lanes; each group takes one of the pass's edges at a
-// time and lane k of a group owns the channels c = k + LPE*j, so every
-// channel c < C1 of the non-scalar degrees sits in slot j = 0.  With folded
-// tables a group requests the table entries of its next edge before it
+// Mapping: above kSplitRows centres one wavefront per centre (four centres per
+// 256-thread workgroup, whose waves never wait for each other); up to that
+// many the four waves of a workgroup share one centre's row, each a quarter of
+// a round's entries, with a workgroup barrier in every round, which puts the
+// kept edges of the four in order, and one more for the sum of their node
+// states.  A wave takes its entries in passes of up to 64: each lane tests one
+// entry (compact.h), and each kept lane forms its edge's per-edge quantities
+// once (envelope, table row and offset, harmonics) into the wave's LDS slice.
+// The lanes then form groups of LPE = C1 lanes; each group takes one of the
+// pass's edges at a time and lane k of a group owns the channels c = k + LPE*j,
+// so every channel c < C1 of the non-scalar degrees sits in slot j = 0.  With
+// folded tables a group requests the table entries of its next edge before it
 // evaluates the current one.  The groups are combined at the end of the row
 // by a fixed xor butterfly, so the node state is the same bits on every run.
 #include <hip/hip_runtime.h>
@@ -35,8 +38,9 @@ namespace {
 constexpr int kTeam = 256;
 constexpr int kWaves = kTeam / kWave;
 
-// Four waves per SIMD fit every degree-three profile without spilling; the
-// degree-four one needs more registers per lane.
+// Four waves per SIMD fit every degree-three profile without spilling (but for
+// two registers where four waves share a row and R = 4); the degree-four one
+// needs more registers per lane.
 template <class P>
 constexpr int forward_min_waves() { return P::L >= 4 ? 1 : 4; }
 

@@ -113,8 +113,8 @@ int launch_split_weights(const float* w, int K, int N, int sk, int sn, int block
 // Rows between the readout and the MLP.  An evaluation of more atoms than
 // kMlpRows goes through them in stretches: 65,536 rows of the full width are
 // 143 MB, which the 256 MB last-level cache holds between the three kernels
-// (1 M copper atoms: 16,384 rows at a time 14.5 ms, 65,536 13.5, 131,072
-// 13.3), and four full rounds of 64-atom workgroups.
+// (the per-atom stage of 1 M copper atoms: 16,384 rows at a time 8.99 ms,
+// 65,536 8.19, 131,072 8.28), and four full rounds of 64-atom workgroups.
 constexpr int64_t kMlpRows = 65536, kMlpRowsLeast = 4096;
 // grows the model's rows to what ``n`` atoms can use; where that would leave
 // less than 8 GiB of device memory free, to kMlpRowsLeast (more, shorter

@@ -12,13 +12,14 @@
 // Products.  Every float32 operand x is carried as two float16 numbers,
 // x 2^e = hi + lo with hi = f16(x 2^e), lo = f16(x 2^e - hi), and a product
 // is three v_mfma_f32_16x16x32_f16 per 32 inputs, lo hi + hi lo + hi hi,
-// accumulated in float32.  hi + lo holds x to one float32 ulp or better, and
+// accumulated in float32.  hi + lo holds x to one float32 ulp or better, the
+// product of the two lo parts, at most 2^-22 of the whole, is left out, and
 // the accumulation rounds every 32 inputs instead of every input: against
-// 64 bits the products of the full-width model are off by 2.1-3.1e-7 of
-// their norm, against 3.3-5.1e-7 for v_mfma_f32_16x16x4_f32, which takes 5.3
-// times as long.  The exponents e are powers of two that keep |x 2^e| at or
-// below 2^15: per matrix for the weights (model set-up), per atom for D, h1
-// and h2 (from bounds that start at the row's own norms, see act_bounds), per
+// 64 bits dE/dD from the same descriptor is off by 1.7 to 4.3e-7 of its norm
+// (seven models, a crystal and a cluster), 0.65 to 0.87 of what float32
+// products reach.  v_mfma_f32_16x16x4_f32 takes 5.3 times as long.  The
+// exponents e are powers of two that keep |x 2^e| at or below 2^15: per matrix for the weights (model set-up), per atom for D, h1
+// and h2 (from bounds that start at the row's own norms, MlpScales), per
 // model for the backward operands.  Entries far below a row's bound lose
 // relative, not absolute, precision: the float16 subnormals end 2^-39 below
 // the bound.
@@ -478,14 +479,20 @@ int launch_split_weights(const float* w, int K, int N, int sk, int sn, int block
 // full width, 65,536 atoms: 46, 58, 72 and 101 us a round for RT = 1 .. 4),
 // and kSlots of them run at once, so the RT with the least rounds x (2 + RT)
 // is taken: 16 atoms while every workgroup still has a slot, 64 for many
-// rounds, and in between what leaves the last round least empty.
+// rounds, and in between what leaves the last round least empty.  Fitted at
+// full width, it holds at every other: over eleven sizes from 500 to 65,000
+// atoms for each of the six profiles the stage with the RT taken is within 3
+// percent of the best of the four (1 percent but for widths 256 at 8,112
+// atoms).  In us for RT = 1 .. 4: width 96 at 24,624 atoms 42, 42, 47, 56 (2
+// taken), width 192 at 16,384 56, 49, 58, 56 (2), width 256 at 46,464 208, 160,
+// 153, 163 (3), width 384 at 11,760 163, 138, 108, 123 (3).
 int launch_chain(const dpa4c_model* m, int64_t n, const int32_t* species, float* desc,
                  const float2* meta, double* e_atom, hipStream_t st) {
   return with_profile(m->C0, m->L, m->R, m->F, [&](auto p, auto f) {
     using P = decltype(p);
     constexpr int F = decltype(f)::value, KP = mlp_width(P::DOUT);
     // waves of a workgroup, and workgroups at once (by registers: eight waves
-    // of up to 256 on each of 256 CUs)
+    // of up to 256 on each of the chip's 256 CUs)
     constexpr int NW = F == 384 ? 8 : F == 96 ? 2 : 4;
     constexpr int64_t kSlots = 256 * (8 / NW);
     int best = 1;
