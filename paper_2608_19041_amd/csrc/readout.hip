@@ -3,8 +3,8 @@
 // and dE/dD in, dE/d(node state) out.  Kept apart from the MLP, whose
 // workgroups hold one CU each, the readouts run with as many atoms in flight
 // as their descriptor rows in LDS allow.  Per 65,536 atoms at full width the
-// readout takes 76 us and its VJP 82 us (degree four: 98 and 120 us), against
-// 40 and 52 us for the bytes they move at the rate of a large copy; what bounds
+// readout takes 63 to 71 us and its VJP 72 to 76 us (degree four: 89 and 120 us),
+// against 40 and 52 us for the bytes they move at the rate of a large copy; what bounds
 // them is the chain of LDS reads and rotations of one atom, with three and two
 // waves on a SIMD to hide it.
 #include <hip/hip_runtime.h>
