@@ -18,12 +18,26 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("name,scale,r_list", [("mini", 1.0, 6.0), ("plus", 1.0, 9.5),
                                                ("plus", 0.62, 7.0), ("plus_l4", 0.62, 6.0)])
 def test_rows_of_several_rounds(name, scale, r_list):
+    check_rows(name, scale, r_list, 1)
+
+
+# six species or more are not folded: edges by neighbour type, over several rounds
+@pytest.mark.parametrize("name,scale,r_list", [("mini", 0.62, 6.0), ("plus", 0.62, 7.0),
+                                               ("plus_l4", 0.62, 6.0)])
+def test_rows_of_several_rounds_on_separable_tables(name, scale, r_list):
+    check_rows(name, scale, r_list, 8)
+
+
+def check_rows(name, scale, r_list, kinds):
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
     import paper_2608_19041_amd as dp
     spec, w = synth.model_weights(name)
     s = synth.fcc_copper(3, 0.06, seed=5)
     cell, pos = s.cell * scale, s.pos * scale
+    if kinds > 1:
+        types = np.array([28, 12, 26, 21, 77, 45, 7, 63][:kinds], np.int32)
+        s.species = types[np.random.Generator(np.random.PCG64(6)).integers(0, kinds, s.n)]
     model = dp.Model(synth.pack_blob(spec, w))
 
     def run(reps):

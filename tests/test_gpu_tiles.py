@@ -10,7 +10,7 @@ do not depend on which tile, lane or stretch it falls into.  So
   inherits the relative error that the descriptor is allowed, 15 times the
   1.8e-7 of the published check, so that is added in units of max |E_i|; and
 * a crystal tiled from one jittered 108-atom cell, at sizes that take every
-  workgroup shape and more than one stretch, has the E_i and forces of that
+  workgroup shape of every width and more than one stretch, has the E_i and forces of that
   cell in every copy.  The copies' positions are the cell's plus whole cell
   vectors, rounded to float64 (at most 6e-14 A in 500 A), which float32 edge
   vectors turn into at most one rounding of a component (6e-8 of 6 A) for the
@@ -65,6 +65,11 @@ def test_open_clusters_around_the_tile_edges(dp, name):
     ("air", [(4, 5, 6), (6, 6, 7)]),
     ("mini", [(5, 5, 5)]),
     ("nano", [(6, 6, 7)]),
+    # the rest of the four shapes of every width, and of degree four's descriptor
+    ("air", [(6, 8, 9)]),
+    ("mini", [(6, 6, 7), (6, 8, 9)]),
+    ("nano", [(6, 8, 9), (8, 8, 9)]),
+    ("plus_l4", [(3, 5, 5), (4, 5, 5), (5, 5, 5)]),
 ])
 def test_tiled_crystal_repeats_its_cell(dp, name, reps):
     spec, w = synth.model_weights(name)

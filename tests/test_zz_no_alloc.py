@@ -1,7 +1,7 @@
 """The entry point without device allocation against compute_energy_forces,
 through the C ABI: two calls in a row, the second with a smaller input, on
 the same model, and on a fresh model whose first call is the no-allocation
-one (separable tables).  Device memory in use does not change across the
+one.  Device memory in use does not change across the
 no-allocation calls, and an input beyond the scratch is refused."""
 import numpy as np
 import pytest
