@@ -181,11 +181,13 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
         ++n_used;
       }
     const size_t need = fold_bytes(m->n_rows, m->C0, m->C[1], n_used);
-    if (!m->fold_allowed || n_used > kMaxFoldTypes || need > kMaxFoldBytes) {
+    const bool folds = m->fold_allowed && n_used <= kMaxFoldTypes && need <= kMaxFoldBytes;
+    if (folds && !may_alloc && need > w.ftab.bytes)
+      return 0;        // this call only: separable tables, the folded state kept
+    if (w.last_fidx) m->last_n = -1;   // its tables go: the stages cannot run again
+    if (!folds) {
       std::memcpy(m->fold_types_mask, mask, sizeof(m->fold_types_mask));
       m->fold_n = 0;   // the separable tables are used
-    } else if (!may_alloc && need > w.ftab.bytes) {
-      return 0;        // this call only: separable tables, the folded state kept
     } else {
       // no set has tables until these are built: a refused allocation has
       // already given the old ones back

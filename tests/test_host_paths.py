@@ -119,6 +119,28 @@ def tables_after_a_refused_allocation(h):
     assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
 
 
+def stages_after_the_tables_went(h):
+    """The stages of the last evaluation read its tables: once another set took them
+    they are refused, not recomputed from the wrong tables."""
+    rc, m = h.create("full")
+    one, two = h.system([28] * 40), h.system([28, 12] * 20)
+    five, many = h.system([28, 12, 26, 21, 77] * 8), h.system([28, 12, 26, 21, 77, 45, 7, 63] * 5)
+    stages = lambda: h.lib.dpa4c_debug_stages(m, ctypes.c_int64(40), None, None, None, None)  # noqa: E731
+    assert rc == OK
+    for other in (one, many):
+        assert h.energy(m, two) == OK and stages() == OK
+        assert h.energy(m, two, "compute_energy_forces_noalloc") == OK and stages() == OK
+        assert h.energy(m, other, "compute_energy_forces_noalloc") == OK
+        assert stages() != OK
+        assert h.energy(m, other) == OK and stages() == OK
+    assert h.energy(m, one, "compute_energy_forces_noalloc") == OK
+    assert stages() == OK   # eight species ran on the separable tables, which stay
+    assert h.energy(m, two) == OK
+    h.refuse_from(100 << 20)
+    assert h.energy(m, five) == OOM
+    assert stages() != OK
+
+
 def list_after_a_refused_workspace(h):
     """The list of the last dynamics call lost its buffers to a larger evaluation."""
     rc, m = h.create("small")
@@ -226,6 +248,7 @@ def noalloc_works_outside_the_workspace(h):
 
 
 SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation,
+             stages_after_the_tables_went,
              list_after_a_refused_workspace, list_after_a_refused_larger_system,
              list_after_a_half_refused_list,
              creation_without_room_for_tables, creation_reserves_only_tables_it_would_use,
