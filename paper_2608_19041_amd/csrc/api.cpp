@@ -345,7 +345,7 @@ int dpa4c_model_create(const void* blob, size_t nbytes, int device, dpa4c_model*
   // separable tables take four times the bytes an edge.  Where they would be
   // above the limit or there is no memory for them, the model does without.
   const size_t first = fold_bytes((*out)->n_rows, (*out)->C0, (*out)->C[1], kFoldFirstTypes);
-  if ((*out)->fold_allowed && first <= kMaxFoldBytes) (void)w.ftab.ensure(first);
+  if ((*out)->fold_allowed && first <= kMaxFoldBytes) (void)w.ftab_first.ensure(first);
   rc = noalloc_setup(device);
   if (rc) {
     dpa4c_model_destroy(*out);
@@ -364,7 +364,7 @@ void dpa4c_model_destroy(dpa4c_model* m) {
   DevBuf* bufs[] = {&w.skin_row, &w.skin_j, &w.skin_shift, &w.skin_rev, &w.qbuild, &w.ecount,
                     &w.edge,     &w.cskin,  &w.node,
                     &w.mlp_buf,  &w.desc,     &w.node_grad, &w.epart,  &w.flags,      &w.inv_mass, &w.mass,
-                    &w.eatom,    &w.tailpart,  &w.backup,  &w.ftab,      &w.fold_map, &w.fold_mask,  &w.fidx,
+                    &w.eatom,    &w.tailpart,  &w.backup,  &w.ftab_first, &w.ftab,  &w.fold_map, &w.fold_mask,  &w.fidx,
                     &w.nb.qpos,  &w.nb.wrap, &w.nb.cell_of, &w.nb.cell_cnt, &w.nb.cell_start,
                     &w.nb.cell_rec, &w.nb.long_keys, &w.nb.counts,
                     &w.nb.partials,

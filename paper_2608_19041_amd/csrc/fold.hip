@@ -52,6 +52,7 @@
 // coefficients.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -182,7 +183,7 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
       }
     const size_t need = fold_bytes(m->n_rows, m->C0, m->C[1], n_used);
     const bool folds = m->fold_allowed && n_used <= kMaxFoldTypes && need <= kMaxFoldBytes;
-    if (folds && !may_alloc && need > w.ftab.bytes)
+    if (folds && !may_alloc && need > std::max(w.ftab_first.bytes, w.ftab.bytes))
       return 0;        // this call only: separable tables, the folded state kept
     if (w.last_fidx) m->last_n = -1;   // its tables go: the stages cannot run again
     if (!folds) {
@@ -192,15 +193,16 @@ int prepare_species(dpa4c_model* m, const uint32_t mask[4], const int32_t* speci
       // no set has tables until these are built: a refused allocation has
       // already given the old ones back
       m->fold_n = -1;
-      DPA4C_TRY(w.ftab.ensure(need));
+      DevBuf& room = need <= w.ftab_first.bytes ? w.ftab_first : w.ftab;
+      DPA4C_TRY(room.ensure(need));
+      w.tables = room.as<float>();
       int32_t* hmap = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(w.fold_host) + 64);
       std::memcpy(hmap, map.data(), 4 * size_t(T1));
       DPA4C_HIP_TRY(hipMemcpyAsync(w.fold_map.p, hmap, 4 * size_t(T1), hipMemcpyHostToDevice, st));
       hipLaunchKernelGGL(fold_build_kernel, dim3(m->n_rows + 1, n_used * n_used),
                          dim3(m->C0 < 256 ? m->C0 : 256), 0, st, m->gtab, m->qtab, m->pair, used,
                          n_used, T1, m->C0, m->R, m->C[1], m->n_rows, m->r_c, m->delta,
-                         make_float2(m->c_scale[0], m->c_scale[1]),
-                         w.ftab.as<float>());
+                         make_float2(m->c_scale[0], m->c_scale[1]), w.tables);
       DPA4C_HIP_TRY(hipGetLastError());
       std::memcpy(m->fold_types_mask, mask, sizeof(m->fold_types_mask));
       m->fold_n = n_used;

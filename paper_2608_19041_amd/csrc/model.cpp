@@ -671,7 +671,7 @@ dpa4c::ModelDev dpa4c_model::dev() const {
   d.inv_sigma = inv_sigma;
   d.E_ref = E_ref;
   d.row_tab = row_tab;
-  d.ftab = ws.ftab.as<float>();
+  d.ftab = ws.tables;
   d.fold_n = fold_n > 0 ? fold_n : 0;
   for (int q = 0; q < 4; ++q) d.c_inv[q] = 1.0f / c_scale[q];
   return d;

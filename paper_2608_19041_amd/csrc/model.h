@@ -93,7 +93,12 @@ struct Workspace {
   std::vector<double> host_mass;   // the masses that inv_mass and mass were formed from
   int64_t* host_flags = nullptr;          // pinned [8]
   // pair-folded tables of the species present (fold.hip)
-  DevBuf ftab;          // float [fold_n^2][n_rows + 1][fold_pitch]
+  // [fold_n^2][n_rows + 1][fold_pitch]: room for kFoldFirstTypes species from
+  // model creation, and for larger sets once a call needs it.  Two buffers, since
+  // to grow the one would free it in the first call with a larger set: 0.3 ms of
+  // waiting for the device and unmapping, more than that whole call takes.
+  DevBuf ftab_first, ftab;
+  float* tables = nullptr;   // the one that holds the set of fold_n
   DevBuf fold_map;      // int32 [T+1]: type -> folded index, or -1
   DevBuf fold_mask;     // uint32 [256][4]: partial masks of the species present
   DevBuf fidx;          // int32 [N]: folded index of every atom

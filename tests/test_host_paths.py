@@ -105,18 +105,35 @@ def refused_allocation_fails_one_call(h):
 
 
 def tables_after_a_refused_allocation(h):
-    """Five species' tables do not fit; the two species of before still run."""
-    rc, m = h.create("full")
-    assert rc == OK
-    two, five = h.system([28, 12] * 20), h.system([28, 12, 26, 21, 77] * 8)
-    assert h.energy(m, two) == OK
-    h.refuse_from(100 << 20)
-    assert h.energy(m, five) == OOM
-    h.refuse_from(0)
-    assert h.energy(m, two) == OK
-    log = h.log()
-    assert any("15backward_kernel" in x and x.endswith(" folded") for x in log), "not folded"
-    assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
+    """Five species' tables do not fit; the two or three species of before still run."""
+    for before in ([28, 12], [28, 12, 26]):
+        rc, m = h.create("full")
+        assert rc == OK
+        few, five = h.system(before * 20), h.system([28, 12, 26, 21, 77] * 8)
+        assert h.energy(m, few) == OK
+        h.refuse_from(100 << 20)
+        assert h.energy(m, five) == OOM
+        h.refuse_from(0)
+        h.log()
+        assert h.energy(m, few) == OK
+        log = h.log()
+        assert any("15backward_kernel" in x and x.endswith(" folded") for x in log), "not folded"
+        assert h.rt.fake_bad() == 0, [x for x in log if x.startswith("bad")]
+
+
+def first_call_gives_nothing_back(h):
+    """A free waits for the device and unmaps: the first call of a model grows its
+    buffers, whatever its species, without giving one up."""
+    for name in ("mini", "full"):
+        for species in ([28], [28, 12], [28, 12, 26], [28, 12, 26, 21, 77]):
+            rc, m = h.create(name)
+            s = h.system(species * 20)
+            h.log()
+            assert rc == OK and h.energy(m, s) == OK
+            log = h.log()
+            assert not any(x.startswith("free") for x in log), (name, len(species))
+            assert h.energy(m, s) == OK
+            assert not any(x.startswith(("malloc", "free")) for x in h.log())
 
 
 def stages_after_the_tables_went(h):
@@ -248,7 +265,7 @@ def noalloc_works_outside_the_workspace(h):
 
 
 SCENARIOS = [refused_allocation_fails_one_call, tables_after_a_refused_allocation,
-             stages_after_the_tables_went,
+             stages_after_the_tables_went, first_call_gives_nothing_back,
              list_after_a_refused_workspace, list_after_a_refused_larger_system,
              list_after_a_half_refused_list,
              creation_without_room_for_tables, creation_reserves_only_tables_it_would_use,
