@@ -312,8 +312,10 @@ int nvt_step(const dpa4c_model* model, double* pos, double* vel, const int32_t* 
  *   descriptor  float32 [N][D_out]: calibrated D       Eq. (calibration)
  *   edge_count  int32 [N]: edges within r_c per centre
  * The stages are recomputed from the inputs of that call (positions,
- * species and skin list), which must still hold the same values.
- * Synchronous on ``stream``.
+ * species and skin list), which must still hold the same values.  Refused
+ * (INVALID_ARG) once a later call, also one without allocation or one that
+ * failed, replaced the folded tables of that evaluation.  Synchronous on
+ * ``stream``.
  */
 int dpa4c_debug_stages(const dpa4c_model* model, int64_t N, float* node_state,
                        float* descriptor, int32_t* edge_count, void* stream);
